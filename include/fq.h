@@ -64,7 +64,11 @@ enum {
     FQ_FLAG_NO_DX = 1u,
     /* Backward: finish the per-channel scale gradient in a second small kernel instead
        of in the last block of each channel.  Same results bit for bit. */
-    FQ_FLAG_TWO_PASS = 2u
+    FQ_FLAG_TWO_PASS = 2u,
+    /* Backward: the wavefronts that gather a channel's partial sums do not poll for those that
+       are still missing (a few tens of microseconds at most otherwise); the unit that comes last
+       finishes the channel.  Same results bit for bit. */
+    FQ_FLAG_NO_POLL = 4u
 };
 
 enum { FQ_MODE_FORWARD = 1, FQ_MODE_BACKWARD = 2 };
@@ -129,10 +133,11 @@ fq_status fq_validate(const fq_tensor *ts, int n, int mode);
 typedef struct fq_layout_info {
     int64_t blocks;              /* grid blocks of the forward / backward kernel */
     int64_t units_per_channel;   /* partial sums combined per channel: 1 direct, 2 exchange, 3-4 exchange
-                                    tree, more: tickets (two-level when extra_slots >= 16) */
+                                    tree, more: gathered by the channel's last unit */
     int64_t unit_elems;          /* elements per unit (the last unit of a slab may be shorter) */
     int32_t wave_units;          /* 1: one wavefront per slab, four slabs to a block */
-    int32_t extra_slots;         /* 64-bit workspace slots per channel beside the channel's own */
+    int32_t extra_slots;         /* 64-bit workspace slots per channel beside the channel's own (from 17
+                                    units per channel on they are reserved, not used) */
 } fq_layout_info;
 fq_status fq_layout(const fq_tensor *t, fq_layout_info *info);
 
@@ -140,14 +145,15 @@ fq_status fq_layout(const fq_tensor *t, fq_layout_info *info);
  * Zero a workspace on `stream` (a fill kernel, not a memset, so it may be captured in a
  * HIP graph).  A workspace must be zeroed once before its first use by fq_backward /
  * fq_multi_tensor in backward mode (memory that is already all zero, e.g. torch.zeros,
- * qualifies).  The kernels rely on it: a ticket or exchange slot that is not zero reads as a
+ * qualifies).  The kernels rely on it: a slot or a partial sum that is not zero reads as a
  * unit that has already arrived, and the gradients of that channel come out wrong or are never
- * written (no kernel waits on a slot, so never a hang).  Every completed call leaves the slots
- * zero again, so the same tensor list (same shapes and flags, any pointers) may follow without
- * zeroing.  The partial sums and, for fq_multi_tensor and fq_plan_create, the descriptor table
- * stay where they were written, and where the slots lie depends on the list: before a workspace
- * serves a list of other shapes, zero it again.  One workspace must not be used by two calls
- * that can overlap in time.
+ * written (no kernel waits for a slot or a sum without a limit, so never a hang).  Every completed
+ * call leaves the slots and the partial sums zero again, so the same tensor list (same shapes and
+ * flags, any pointers) may follow without zeroing.  For fq_multi_tensor and fq_plan_create the
+ * descriptor table stays where it was written, and where the sums and slots lie depends on the
+ * list: before a workspace serves a list of other shapes, or after anything else has written to it
+ * (fq_distill_loss, say), zero it again.  One workspace must not be used by two calls that can
+ * overlap in time.
  */
 fq_status fq_workspace_init(void *workspace, size_t ws_bytes, void *hip_stream);
 
@@ -179,7 +185,7 @@ fq_status fq_backward(const fq_tensor *t, void *workspace, size_t ws_bytes, void
  * FQ_STATIC_MAX_UNITS partial sums (fq_layout: units_per_channel * channels) and
  * FQ_STATIC_MAX_SLOTS slots (channels * (1 + extra_slots)); a larger tensor is refused with
  * FQ_ERR_WORKSPACE before anything is enqueued.  The first call on a GPU looks the array's device
- * address up and zeroes its slots with a small fill kernel on `hip_stream`; make that call
+ * address up and zeroes it with a small fill kernel on `hip_stream`; make that call
  * outside any graph capture.  All calls on one GPU share that GPU's array: two calls that can
  * overlap in time (different streams, or graphs replayed concurrently) race; calls ordered on one
  * stream do not.
@@ -254,7 +260,7 @@ void fq_plan_destroy(fq_plan *plan);
  * contiguous [n, channels, inner]; gstudent may be exactly student or teacher (in place).  Two or
  * three launches; no atomics, fixed summation order.  A tensor without elements needs no workspace and
  * gives NaN for mse and loss (a mean of nothing); cosim is then NaN without positions and 0 with
- * positions but no channels.  The workspace need not be initialised and may be shared with other calls
+ * positions but no channels.  The workspace need not be initialised and may be shared with other such calls
  * that do not overlap in time.
  */
 typedef struct fq_distill {

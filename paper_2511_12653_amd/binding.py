@@ -16,7 +16,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libfq.so")
 
 FQ_F16, FQ_F32 = 0, 1
-FQ_FLAG_NO_DX, FQ_FLAG_TWO_PASS = 1, 2
+FQ_FLAG_NO_DX, FQ_FLAG_TWO_PASS, FQ_FLAG_NO_POLL = 1, 2, 4
 FQ_MODE_FORWARD, FQ_MODE_BACKWARD = 1, 2
 FLT_MIN = 1.1754943508222875e-38
 

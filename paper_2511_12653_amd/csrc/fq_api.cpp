@@ -46,7 +46,7 @@ bool overlap(const void *a, size_t abytes, const void *b, size_t bbytes)
 struct Plan {
     long long numel = 0;
     unsigned slabs = 0, cps = 0, chunk = 0;
-    unsigned sub = 0;            // extra slots per channel: pair slots (2) or first-level ticket slots (32)
+    unsigned sub = 0;            // extra slots per channel: pair slots (2) or reserved ones (16, 32)
     bool short_slabs = false;    // a slab fits one wavefront's chunk
     bool waves = false;          // short slabs in a launch with blocks to spare: one wavefront per slab,
                                  // four slabs to a block
@@ -54,12 +54,12 @@ struct Plan {
     long long units = 0;         // partial sums: one per block, or one per slab with `waves'
 };
 
-// Slots a channel needs beside its own, by the number of units (blocks or wavefronts) that
-// combine their sums for it: pair slots of the exchange tree, or first-level ticket slots.
+// Slots a channel has beside its own, by the number of units (blocks or wavefronts) that
+// combine their sums for it: pair slots of the exchange tree, or reserved ones.
 unsigned extra_slots(long long units_per_channel)
 {
-    if (units_per_channel > (long long)kTicketManyUnits) return kTicketManySubSlots;
-    if (units_per_channel > (long long)kTicketFanIn) return kTicketSubSlots;
+    if (units_per_channel > (long long)kReserveManyUnits) return kReserveManySlots;
+    if (units_per_channel > (long long)kReserveUnits) return kReserveSlots;
     if (units_per_channel > 2 && units_per_channel <= (long long)kTreeBlocks) return 2u;
     return 0u;
 }
@@ -174,7 +174,7 @@ struct Layout {
     std::vector<Plan> plans;
     long long blocks = 0;        // grid of the main kernel
     long long channels = 0;      // grid of the finalize kernel
-    long long slots = 0;         // 64-bit ticket / exchange slots (backward)
+    long long slots = 0;         // 64-bit slots (backward)
     long long partials = 0;      // doubles
     size_t table_bytes = 0, partial_off = 0, counter_off = 0, total = 0;
     bool any_empty_with_channels = false;

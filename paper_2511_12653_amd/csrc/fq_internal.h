@@ -14,13 +14,12 @@ constexpr int kComputeUnits = 256;   // MI355X; used by the host to balance bloc
 // A single-tensor backward launch of at most this many blocks has all of them resident at once
 // (three per compute unit) and takes the schedule made for one burst (backward_chunk, SHORT).
 constexpr unsigned kShortLaunchBlocks = 3 * kComputeUnits;
-// Units of a channel beyond kTicketFanIn draw their arrival tickets in two levels: that many
-// atomics on one address queue up at the memory-side atomic unit (60 units on one slot cost a
-// short-slab backward 17.4 us against 13.1 us with 16 first-level slots).
-constexpr unsigned kTicketFanIn = 16;
-constexpr unsigned kTicketSubSlots = 16;       // first-level slots per channel
-constexpr unsigned kTicketManyUnits = 256;     // beyond this many units per channel ...
-constexpr unsigned kTicketManySubSlots = 32;   // ... this many first-level slots
+// Channels with more units than this have 16 (32) further 64-bit slots in the workspace.  No kernel uses
+// them; they keep fq_workspace_bytes and fq_layout at the values that callers have sized memory by.
+constexpr unsigned kReserveUnits = 16;
+constexpr unsigned kReserveSlots = 16;
+constexpr unsigned kReserveManyUnits = 256;
+constexpr unsigned kReserveManySlots = 32;
 constexpr unsigned kTreeBlocks = 4;      // up to this many blocks per channel combine by atomic exchange alone
 
 // Scratch memory built into the library for fq_backward_static: [slots][partial sums].
@@ -40,9 +39,10 @@ struct DevTensor {
     void *gx;
     float *gs;
     float *gtheta;
-    double *partial;           // [slabs * cps] per-block partial sums of gy*t (backward)
-    unsigned long long *slot;  // [channels] exchange slot / arrival tickets, then [channels][sub] first-level
-                               // tickets; all zero between calls (backward)
+    double *partial;           // [channels][outer * cps] partial sums of gy*t, one per unit; all zero between
+                               // calls (backward)
+    unsigned long long *slot;  // [channels] exchange slot / state of the gathering, then [channels][sub];
+                               // all zero between calls (backward)
     long long inner;           // elements per slab
     unsigned slabs;            // outer * channels
     unsigned channels;
@@ -55,7 +55,7 @@ struct DevTensor {
                                // the tensor's blocks then number ceil(slabs / 4) and partial[] is per slab
     unsigned grid3;            // 1: launched alone with a grid of (cps, channels, outer) blocks (see own_chunk)
     unsigned sub;              // extra slots per channel after the [channels] main ones: 0, 2 (pair slots of
-                               // the exchange tree, 3 or 4 blocks per channel) or kTicketSubSlots
+                               // the exchange tree, 3 or 4 units per channel) or the unused kReserve...
     int dtype;                 // 0 = FP16, 1 = FP32
     float lo, hi;              // (float)qmin, (float)qmax
     float eps, s_min, s_max;

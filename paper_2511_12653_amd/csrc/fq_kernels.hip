@@ -6,7 +6,7 @@
 // [outer, channel] slab, so the scale is uniform over the block; lanes move 128-bit vectors
 // (global_load/store_dwordx4, non-temporal), FP16 is widened/narrowed in registers.  Backward adds
 // a DPP wavefront reduction, an LDS block reduction and a fixed-order combination of the blocks
-// of a channel (direct, by atomic exchange, or by ticket: see combine); no float atomics.
+// of a channel (direct, by atomic exchange, or gathered by one of them: see combine); no float atomics.
 // Tensors whose slabs are short are cut per wavefront instead (one slab per wavefront, four to a
 // block, no barrier: forward_dispatch, backward_waves) when the launch has blocks to spare.
 #include <hip/hip_runtime.h>
@@ -201,16 +201,12 @@ __device__ __forceinline__ float ste_terms(float x, const QParams &p, bool &in_r
 // has been acknowledged; the "memory" clobber keeps the compiler from moving accesses across it.
 __device__ __forceinline__ void wait_stores_acknowledged() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// Finisher side of the tickets.  Every partial sum of the channel was acknowledged at agent scope
-// before its unit drew a ticket, and the finisher has received the last ticket, so all of them are
-// in memory when it starts reading.  It reads them with agent-scope atomic loads (global_load ...
-// sc1), which are served from the level all XCDs share and never from a line cached by this XCD;
-// the hardware issues a wavefront's memory operations in program order and the branch on the
-// ticket's value needs the atomic's result, so the loads are issued after the ticket has returned.
-// All that is left to enforce is that the compiler keeps them behind the ticket.  (An acquire
+// Collector side of the partial sums.  They are read with agent-scope atomic loads (global_load ...
+// sc1), which are served from the level all XCDs share and never from a line cached by this XCD.
+// This keeps the compiler from moving such reads to the other side of a publication.  (An acquire
 // fence at agent scope would also invalidate this XCD's L2 under the blocks still streaming
 // through it: measured 41 -> 45 us on a 15x128x120x160 FP16 tensor, for nothing.)
-__device__ __forceinline__ void acquire_partials() { asm volatile("" ::: "memory"); }
+__device__ __forceinline__ void order_accesses() { asm volatile("" ::: "memory"); }
 
 // Keeps the computation of a value at this point of the program: the compiler would otherwise
 // sink it to its first use, behind the wait for a later load.  Emits no instruction.
@@ -225,6 +221,7 @@ __device__ __forceinline__ unsigned wave_index() { return (unsigned)__builtin_am
 // Chunk addressing shared by forward and backward.
 struct Chunk {
     unsigned slab, channel;
+    unsigned j;        // index of this unit among its channel's units
     long long first;   // flat element index of the chunk's first element
     int n;             // elements in the chunk
 };
@@ -234,7 +231,9 @@ __device__ __forceinline__ Chunk locate_chunk(const DevTensor &d, unsigned local
     Chunk c;
     c.slab = local_block / d.cps;
     unsigned k = local_block - c.slab * d.cps;
-    c.channel = c.slab % d.channels;
+    const unsigned o = c.slab / d.channels;
+    c.channel = c.slab - o * d.channels;
+    c.j = o * d.cps + k;
     long long e0 = (long long)k * d.chunk;
     long long rem = d.inner - e0;
     c.n = rem < (long long)d.chunk ? (int)rem : (int)d.chunk;
@@ -245,17 +244,14 @@ __device__ __forceinline__ Chunk locate_chunk(const DevTensor &d, unsigned local
 // The chunk of this block in a single-tensor launch.  Such a launch normally has a grid of
 // (chunks per slab, channels, outer), which names the chunk without any division (two integer
 // divisions sit between a block's start and its first load otherwise); tensors with more than
-// 65535 channels or outer slices keep the linear grid.  `unit` receives the chunk's linear index.
-__device__ __forceinline__ Chunk own_chunk(const DevTensor &d, unsigned &unit)
+// 65535 channels or outer slices keep the linear grid.
+__device__ __forceinline__ Chunk own_chunk(const DevTensor &d)
 {
-    if (!d.grid3) {
-        unit = blockIdx.x;
-        return locate_chunk(d, unit);
-    }
+    if (!d.grid3) return locate_chunk(d, blockIdx.x);
     Chunk c;
     c.channel = blockIdx.y;
     c.slab = blockIdx.z * d.channels + blockIdx.y;
-    unit = c.slab * d.cps + blockIdx.x;
+    c.j = blockIdx.z * d.cps + blockIdx.x;
     const long long e0 = (long long)blockIdx.x * d.chunk;
     const long long rem = d.inner - e0;
     c.n = rem < (long long)d.chunk ? (int)rem : (int)d.chunk;
@@ -647,7 +643,7 @@ __device__ __forceinline__ void write_channel_grads(const DevTensor &d, unsigned
     if (d.gs) st_global(d.gs + c, (float)total);
     if (d.gtheta) st_global(d.gtheta + c, g);
     if (d.s) st_global(d.s + c, bs.s);
-    if (d.adam_m) {
+    if (__builtin_expect(d.adam_m != nullptr, 0)) {
         // One Adam step on theta_c (Kingma & Ba, Algorithm 1), binary32, each operation rounded
         // on its own.  Every block of this channel has finished reading theta_c by now (this
         // code runs after all of them have handed in their sums), so theta may be updated in
@@ -666,32 +662,67 @@ __device__ __forceinline__ void write_channel_grads(const DevTensor &d, unsigned
     }
 }
 
-// Sum the per-block partials of channel c in a fixed order (thread-strided binary64 sums, fixed
-// tree).  Block-wide; lds holds kBlock/64 doubles.  Partials are read with agent-scope loads:
-// they may have been written by a block running on another XCD, whose L2 is not this one.
-__device__ __forceinline__ void finalize_channel(const DevTensor &d, unsigned c, const BlockScale &bs, double *lds)
+// The partial sums of channel c: one per unit, in index order.
+__device__ __forceinline__ double *partials_of(const DevTensor &d, unsigned c)
+{
+    return d.partial + (size_t)c * (d.outer * d.cps);
+}
+
+__device__ __forceinline__ unsigned long long bits_of(double v) { return __builtin_bit_cast(unsigned long long, v); }
+
+// A published sum differs from an empty (all zero) place: +0.0 travels as -0.0, which adds the same.
+__device__ __forceinline__ double published(double v) { return bits_of(v) == 0ull ? -0.0 : v; }
+
+// This thread's share of the partial sums of channel c, for a block: thread t adds the sums t, t+256,
+// t+512, ... in that order, eight loads in flight.  `present` becomes false where a sum is still zero,
+// that is, not published yet.  own >= 0: unit `own` is the caller's; its sum is `mine`, not in memory.
+__device__ __forceinline__ double add_partials_block(const DevTensor &d, unsigned c, unsigned own, double mine,
+                                                     bool &present)
 {
     const unsigned bpc = d.outer * d.cps;
-    double acc = 0.0;
-    // thread t adds sums t, t+256, t+512, ... in that order; eight loads are kept in flight
     constexpr unsigned kBatch = 8;
+    double *const parts = partials_of(d, c);
+    double acc = 0.0;
+    present = true;
     for (unsigned j0 = threadIdx.x; j0 < bpc; j0 += kBlock * kBatch) {
         double part[kBatch];
 #pragma unroll
         for (unsigned i = 0; i < kBatch; ++i) {
             const unsigned j = j0 + i * kBlock;
-            part[i] = 0.0;
-            if (j < bpc) {
-                const unsigned o = j / d.cps;
-                const unsigned k = j - o * d.cps;
-                const size_t idx = ((size_t)o * d.channels + c) * d.cps + k;
-                part[i] = __hip_atomic_load(&d.partial[idx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            part[i] = mine;
+            if (j < bpc && j != own)
+                part[i] = __hip_atomic_load(&parts[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
 #pragma unroll
-        for (unsigned i = 0; i < kBatch; ++i) acc += part[i];
+        for (unsigned i = 0; i < kBatch; ++i) {
+            const unsigned j = j0 + i * kBlock;
+            if (j < bpc) {
+                acc += part[i];
+                present = present && (j == own || bits_of(part[i]) != 0ull);
+            }
+        }
     }
-    acc = wave_sum(acc);
+    return acc;
+}
+
+// Put the partial sums of channel c back to zero, for the next call.
+template <int G>
+__device__ __forceinline__ void clear_partials(const DevTensor &d, unsigned c)
+{
+    const unsigned bpc = d.outer * d.cps;
+    double *const parts = partials_of(d, c);
+    for (unsigned j = threadIdx.x & (G - 1); j < bpc; j += G)
+        __hip_atomic_store(&parts[j], 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Second launch of the two-launch mode: the sum of all partial sums of channel c (thread-strided
+// binary64 sums, fixed tree), the channel's gradients, and the partial sums back to zero.
+// Block-wide; lds holds kBlock/64 doubles.
+__device__ __forceinline__ void finalize_channel(const DevTensor &d, unsigned c, const BlockScale &bs, double *lds)
+{
+    bool present;
+    const double acc = wave_sum(add_partials_block(d, c, ~0u, 0.0, present));
+    clear_partials<kBlock>(d, c);
     if ((threadIdx.x & 63) == kSumLane) lds[threadIdx.x >> 6] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -700,7 +731,6 @@ __device__ __forceinline__ void finalize_channel(const DevTensor &d, unsigned c,
         for (int w = 0; w < kBlock / 64; ++w) total += lds[w];
         write_channel_grads(d, c, total, bs);
     }
-    __syncthreads();
 }
 
 // value of v in the given lane, as a wavefront-uniform scalar
@@ -712,26 +742,31 @@ __device__ __forceinline__ double read_lane(double v, int lane)
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
-// The same sum, bit for bit, by a single wavefront (for tensors whose units are wavefronts): the
-// block-wide version gives thread t the sums t, t+256, ... and adds wavefront 0's tree to
-// wavefront 1's, 2's and 3's in that order; here the one wavefront plays the four in turn.
-__device__ __forceinline__ void finalize_channel_wave(const DevTensor &d, unsigned c, const BlockScale &bs)
+// The same sum, bit for bit, by a single wavefront: the block-wide version gives thread t the sums
+// t, t+256, ... and adds wavefront 0's tree to wavefront 1's, 2's and 3's in that order; here the
+// one wavefront plays the four in turn.  `present` is uniform: all sums of the channel are there.
+__device__ __forceinline__ double add_partials_wave(const DevTensor &d, unsigned c, unsigned own, double mine,
+                                                    bool &present)
 {
     const unsigned bpc = d.outer * d.cps;
     const unsigned lane = threadIdx.x & 63;
+    double *const parts = partials_of(d, c);
     double total = 0.0;
-    for (unsigned w = 0; w < kBlock / 64; ++w) {
+    bool here = true;
+    for (unsigned w = 0; w * 64 < bpc && w < kBlock / 64; ++w) {       // (an empty one would add +0.0)
         double acc = 0.0;
         for (unsigned j = w * 64 + lane; j < bpc; j += kBlock) {
-            const unsigned o = j / d.cps;
-            const unsigned k = j - o * d.cps;
-            const size_t idx = ((size_t)o * d.channels + c) * d.cps + k;
-            acc += __hip_atomic_load(&d.partial[idx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            double part = mine;
+            if (j != own) {
+                part = __hip_atomic_load(&parts[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                here = here && bits_of(part) != 0ull;
+            }
+            acc += part;
         }
-        acc = wave_sum(acc);
-        total += read_lane(acc, kSumLane);
+        total += read_lane(wave_sum(acc), kSumLane);
     }
-    if (lane == kSumLane) write_channel_grads(d, c, total, bs);
+    present = __builtin_amdgcn_ballot_w64(!here) == 0ull;
+    return total;
 }
 
 // How the units (blocks, or wavefronts of short-slab tensors) of a channel combine their sums
@@ -741,50 +776,39 @@ __device__ __forceinline__ void finalize_channel_wave(const DevTensor &d, unsign
 //                         its partner's sum there adds the two (a+b = b+a) and clears the slot:
 //                         one atomic round trip, the payload travels in the atomic itself;
 //   3 or 4                two rounds of that exchange, pairs first (two more slots per channel);
-//   more                  each unit stores its sum, waits for that store, then draws a ticket
-//                         from the slot; the unit with the last ticket has all sums re-read in
-//                         index order and clears the slot.  Beyond kTicketFanIn units per channel
-//                         the tickets are drawn in two levels (d.sub first-level slots).
-// The slots are zero between calls.  (A sum of +0.0 is swapped in as -0.0 so that it differs from
-// an empty slot; it adds the same.)
+//   more                  each unit publishes its sum in partial[] and the channel's last unit in
+//                         index order, its collector, gathers them: see publish and collect.
+// Slots and partial sums are zero between calls.
 // Without FUSED the sums are only stored and finalize_kernel adds them in a second launch.
 //
-// Called by one lane per unit with the unit's total.  Returns 1 if the caller drew the last
-// ticket, i.e. its block must now run finalize_channel for ck.channel.
+// Called by one lane per unit with the unit's total, for up to kTreeBlocks units per channel and
+// without FUSED.
 template <bool FUSED>
-__device__ __forceinline__ unsigned combine(const DevTensor &d, const Chunk &ck, unsigned unit, double total,
-                                            const BlockScale &bs)
+__device__ __forceinline__ void combine(const DevTensor &d, const Chunk &ck, double total, const BlockScale &bs)
 {
     const unsigned bpc = d.outer * d.cps;
-    unsigned last = 0u;
     if (!FUSED) {
-        __hip_atomic_store(&d.partial[unit], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&partials_of(d, ck.channel)[ck.j], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else if (bpc == 1u) {
         write_channel_grads(d, ck.channel, total, bs);
     } else if (bpc == 2u) {
-        unsigned long long mine = __builtin_bit_cast(unsigned long long, total);
-        if (mine == 0ull) mine = 0x8000000000000000ull;
-        const unsigned long long theirs = __hip_atomic_exchange(&d.slot[ck.channel], mine, __ATOMIC_RELAXED,
-                                                                __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long theirs = __hip_atomic_exchange(&d.slot[ck.channel], bits_of(published(total)),
+                                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (theirs != 0ull) {
             __hip_atomic_store(&d.slot[ck.channel], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const double both = (__builtin_bit_cast(double, theirs) + total) + 0.0;
             write_channel_grads(d, ck.channel, both, bs);
         }
-    } else if (bpc <= kTreeBlocks) {
+    } else {
         // Three or four units: two rounds of the same exchange, associated as finalize_channel
         // associates its sums, (p0 + p1) + (p2 + p3) with an absent p3 counting as +0.0, so the
-        // bits equal those of the two-launch mode.  Unlike the tickets below this needs no wait
-        // for the unit's own gx stores and no re-read of the partial sums.
-        const unsigned o = ck.slab / d.channels;
-        const unsigned j = o * d.cps + (unit - ck.slab * d.cps);
+        // bits equal those of the two-launch mode.
+        const unsigned j = ck.j;
         double pair_sum = total + 0.0;                 // unit 2 of 3 has no partner
         bool carry_on = true;
         if (!(bpc == 3u && j == 2u)) {
             unsigned long long *pair = d.slot + d.channels + (size_t)ck.channel * 2u + (j >> 1);
-            unsigned long long mine = __builtin_bit_cast(unsigned long long, total);
-            if (mine == 0ull) mine = 0x8000000000000000ull;
-            const unsigned long long theirs = __hip_atomic_exchange(pair, mine, __ATOMIC_RELAXED,
+            const unsigned long long theirs = __hip_atomic_exchange(pair, bits_of(published(total)), __ATOMIC_RELAXED,
                                                                     __HIP_MEMORY_SCOPE_AGENT);
             carry_on = theirs != 0ull;
             if (carry_on) {
@@ -793,61 +817,98 @@ __device__ __forceinline__ unsigned combine(const DevTensor &d, const Chunk &ck,
             }
         }
         if (carry_on) {
-            unsigned long long mine = __builtin_bit_cast(unsigned long long, pair_sum);
-            if (mine == 0ull) mine = 0x8000000000000000ull;
-            const unsigned long long theirs = __hip_atomic_exchange(&d.slot[ck.channel], mine, __ATOMIC_RELAXED,
-                                                                    __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long theirs = __hip_atomic_exchange(&d.slot[ck.channel], bits_of(published(pair_sum)),
+                                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (theirs != 0ull) {
                 __hip_atomic_store(&d.slot[ck.channel], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const double all = (__builtin_bit_cast(double, theirs) + pair_sum) + 0.0;
                 write_channel_grads(d, ck.channel, all, bs);
             }
         }
-    } else {
-        // Publish, then draw.  The sum goes out with an agent-scope store (global_store ... sc1:
-        // written through to the memory level that all XCDs share).  Stores count in vmcnt on this
-        // target and an agent-scope store is acknowledged only once it has reached that level, so
-        // after s_waitcnt vmcnt(0) the sum is visible to every XCD; the ticket atomic is issued
-        // after the wait and therefore reaches the memory side after the sum it announces.  A
-        // release fence at agent scope would give the same order but also writes back the whole
-        // L2 (the unit's gx stores), once per unit; only the partial has to be published.
-        __hip_atomic_store(&d.partial[unit], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        wait_stores_acknowledged();
-        unsigned long long *top = &d.slot[ck.channel];
-        unsigned long long expected = bpc;
-        bool draw_top = true;
-        if (d.sub) {
-            // Hundreds of units drawing from one address queue up behind each other at the
-            // memory-side atomic unit.  Unit j of the channel draws from sub-slot j mod sub
-            // first; only the last arrival there goes on to the channel's own slot.
-            const unsigned o = ck.slab / d.channels;
-            const unsigned j = o * d.cps + (unit - ck.slab * d.cps);
-            const unsigned k = j % d.sub;
-            const unsigned long long arrivals = (bpc - k + d.sub - 1u) / d.sub;
-            unsigned long long *first = d.slot + d.channels + (size_t)ck.channel * d.sub + k;
-            const unsigned long long t1 = __hip_atomic_fetch_add(first, 1ull, __ATOMIC_RELAXED,
-                                                                 __HIP_MEMORY_SCOPE_AGENT);
-            draw_top = t1 == arrivals - 1ull;
-            if (draw_top) __hip_atomic_store(first, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            expected = d.sub;                      // bpc > sub, so every sub-slot is in use
-        }
-        if (draw_top) {
-            const unsigned long long ticket = __hip_atomic_fetch_add(top, 1ull, __ATOMIC_RELAXED,
-                                                                     __HIP_MEMORY_SCOPE_AGENT);
-            last = (ticket == expected - 1ull) ? 1u : 0u;
-            if (last) __hip_atomic_store(top, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
     }
-    return last;
+}
+
+// More than kTreeBlocks units per channel.  What bounds the end of such a launch is the number of
+// dependent trips to memory behind the last unit's sum, about 0.5 us each: with arrival tickets there
+// were four (store acknowledged, first-level ticket, top ticket, sums re-read).  Here there are two: the
+// unit's sum reaches memory, and the collector, which is polling the channel's sums (eight per thread and
+// trip), sees it.  A sum announces itself: its place was zero and a published sum never is.  A channel's
+// sums lie next to each other, so a trip is one or two cache lines.  Measured against the tickets (graph
+// of back-to-back launches): one scale, 153600 FP32 elements in 150 units 6.0 -> 4.7 us; 2457600 FP16 in
+// 240 units 7.9 -> 6.4; 39321600 FP16 in 3840 units 44.4 -> 43.0; 15x128x19200 FP16, 30 units per channel
+// 40.1 -> 39.8; 15x384x1200 FP16, 15 wavefront units 11.9 -> 11.5.  Waiting between the rounds (s_sleep
+// 4, 20) is no faster (4.7, 4.7 and 6.7, 6.9 us on the first two).
+//
+// No wait is without end and nothing rests on the order in which blocks are dispatched: the collector
+// polls at most kPollRounds times (a few tens of microseconds; normally one to three).  If a sum is still
+// missing then, it publishes its own, raises the channel's slot to kGivenUp, and looks once more after the
+// flag has been acknowledged.  Every unit reads the flag after its own sum has been acknowledged, so
+// either the collector's last look sees that sum or the unit sees the flag; a unit that sees the flag
+// looks at all sums itself, and the last one to arrive finds them complete.  Whoever finds them complete
+// after the flag was raised claims the channel by a compare-exchange of the slot, so that one of them
+// writes the gradients, and puts the slot back to zero.
+constexpr unsigned long long kGivenUp = 1ull, kClaimed = 2ull;
+constexpr unsigned kPollRounds = 32;
+
+// The flag is up: one wavefront looks at all sums (`own`: none, all are in memory) and finishes the
+// channel if they are complete and no other unit has claimed it.
+__device__ __forceinline__ void finish_if_complete(const DevTensor &d, unsigned c, const BlockScale &bs)
+{
+    bool present;
+    const double total = add_partials_wave(d, c, ~0u, 0.0, present);
+    if (!present) return;
+    unsigned won = 0u;
+    if ((threadIdx.x & 63) == 0) {
+        unsigned long long expected = kGivenUp;
+        won = __hip_atomic_compare_exchange_strong(&d.slot[c], &expected, kClaimed, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT) ? 1u : 0u;
+    }
+    if (!__builtin_amdgcn_readfirstlane((int)won)) return;
+    order_accesses();
+    clear_partials<64>(d, c);
+    if ((threadIdx.x & 63) == 0) {
+        write_channel_grads(d, c, total, bs);
+        __hip_atomic_store(&d.slot[c], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// A unit that is not its channel's collector (one wavefront; total is uniform).  The sum goes out with an
+// agent-scope store (global_store ... sc1: written through to the memory level that all XCDs share).
+// Stores count in vmcnt on this target and an agent-scope store is acknowledged only once it has reached
+// that level, so after s_waitcnt vmcnt(0) the sum is visible to every XCD, and the flag is read after
+// that.  A release fence at agent scope would give the same order but also write back the whole L2.
+__device__ __forceinline__ void publish(const DevTensor &d, const Chunk &ck, double total, const BlockScale &bs)
+{
+    if ((threadIdx.x & 63) == 0)
+        __hip_atomic_store(&partials_of(d, ck.channel)[ck.j], published(total), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    wait_stores_acknowledged();
+    const unsigned long long flag = __hip_atomic_load(&d.slot[ck.channel], __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)(unsigned)flag) == (int)kGivenUp, 0))
+        finish_if_complete(d, ck.channel, bs);
+}
+
+// The collector has stopped polling (one wavefront; total is uniform).
+__device__ __forceinline__ void give_up(const DevTensor &d, const Chunk &ck, double total, const BlockScale &bs)
+{
+    if ((threadIdx.x & 63) == 0)
+        __hip_atomic_store(&partials_of(d, ck.channel)[ck.j], published(total), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    wait_stores_acknowledged();
+    if ((threadIdx.x & 63) == 0)
+        __hip_atomic_store(&d.slot[ck.channel], kGivenUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    wait_stores_acknowledged();
+    finish_if_complete(d, ck.channel, bs);
 }
 
 // One block of the backward grid, owning one chunk of one slab.
 template <typename T, bool FUSED, bool SHORT = false>
-__device__ __forceinline__ void backward_block(const DevTensor &d, const Chunk &ck, unsigned local_block)
+__device__ __forceinline__ void backward_block(const DevTensor &d, const Chunk &ck)
 {
     __shared__ double wave_part[kBlock / 64];
     __shared__ double fin_part[kBlock / 64];
-    __shared__ unsigned is_last;
+    __shared__ unsigned missing[kBlock / 64];
 
     const bool write_gx = !(d.flags & 1u);
     BlockScale bs;
@@ -858,23 +919,54 @@ __device__ __forceinline__ void backward_block(const DevTensor &d, const Chunk &
     sum = wave_sum(sum);
     if ((threadIdx.x & 63) == kSumLane) wave_part[threadIdx.x >> 6] = sum;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double total = 0.0;
+    const unsigned bpc = d.outer * d.cps;
+    const bool gathered = FUSED && !SHORT && bpc > kTreeBlocks;     // (SHORT: see launch_backward_shaped)
+    // the channel's last unit in index order: normally dispatched after the others
+    const bool collector = gathered && ck.j + 1u == bpc;
+    if (!collector && threadIdx.x >= (gathered ? 64u : 1u)) return;
+    double total = 0.0;
 #pragma unroll
-        for (int w = 0; w < kBlock / 64; ++w) total += wave_part[w];
-        is_last = combine<FUSED>(d, ck, local_block, total, bs);
+    for (int w = 0; w < kBlock / 64; ++w) total += wave_part[w];
+    if (!gathered) {
+        combine<FUSED>(d, ck, total, bs);
+        return;
     }
-    if (FUSED && d.outer * d.cps > kTreeBlocks) {
-        __syncthreads();
-        if (is_last) {
-            acquire_partials();
-            finalize_channel(d, ck.channel, bs, fin_part);
-        }
+    if (!collector) {
+        publish(d, ck, total, bs);
+        return;
     }
+    // Poll: every thread until the sums it adds are all there.
+    const unsigned rounds = d.flags & 4u ? 0u : kPollRounds;      // FQ_FLAG_NO_POLL
+    bool present = false;
+    double acc = 0.0;
+    for (unsigned round = 0; round < rounds && !present; ++round) {
+        order_accesses();
+        acc = add_partials_block(d, ck.channel, bpc - 1u, total, present);
+    }
+    acc = wave_sum(acc);
+    const bool wave_missing = __builtin_amdgcn_ballot_w64(!present) != 0ull;
+    if ((threadIdx.x & 63) == kSumLane) {
+        fin_part[threadIdx.x >> 6] = acc;
+        missing[threadIdx.x >> 6] = wave_missing ? 1u : 0u;
+    }
+    __syncthreads();
+    unsigned any_missing = 0u;
+    double all = 0.0;
+#pragma unroll
+    for (int w = 0; w < kBlock / 64; ++w) {
+        any_missing |= missing[w];
+        all += fin_part[w];
+    }
+    if (__builtin_expect(any_missing != 0u, 0)) {
+        if (threadIdx.x < 64) give_up(d, ck, total, bs);
+        return;
+    }
+    if (threadIdx.x == 0) write_channel_grads(d, ck.channel, all, bs);
+    clear_partials<kBlock>(d, ck.channel);
 }
 
 // One block of the backward grid for a tensor with short slabs: every wavefront owns a slab (a
-// unit) of its own -- scale, sum, combination and, if it draws the last ticket of its channel,
+// unit) of its own -- scale, sum, combination and, if it is its channel's collector,
 // the final sum, all per wavefront; the block never meets at a barrier.
 template <typename T, bool FUSED>
 __device__ __forceinline__ void backward_waves(const DevTensor &d, unsigned local_block)
@@ -885,22 +977,36 @@ __device__ __forceinline__ void backward_waves(const DevTensor &d, unsigned loca
     const Chunk ck = locate_chunk(d, unit);
     BlockScale bs;
     double sum = write_gx ? backward_chunk<T, true, 64>(d, ck, bs) : backward_chunk<T, false, 64>(d, ck, bs);
-    sum = wave_sum(sum);
-    unsigned last = 0u;
-    if ((threadIdx.x & 63) == kSumLane) last = combine<FUSED>(d, ck, unit, sum, bs);
-    if (FUSED && d.outer * d.cps > kTreeBlocks) {
-        if (__builtin_amdgcn_readlane((int)last, kSumLane)) {
-            acquire_partials();
-            finalize_channel_wave(d, ck.channel, bs);
-        }
+    const double total = read_lane(wave_sum(sum), kSumLane);
+    const unsigned bpc = d.outer * d.cps;
+    if (!FUSED || bpc <= kTreeBlocks) {
+        if ((threadIdx.x & 63) == 0) combine<FUSED>(d, ck, total, bs);
+        return;
     }
+    if (ck.j + 1u != bpc) {
+        publish(d, ck, total, bs);
+        return;
+    }
+    const unsigned rounds = d.flags & 4u ? 0u : kPollRounds;      // FQ_FLAG_NO_POLL
+    bool present = false;
+    double all = 0.0;
+    for (unsigned round = 0; round < rounds && !present; ++round) {
+        order_accesses();
+        all = add_partials_wave(d, ck.channel, bpc - 1u, total, present);
+    }
+    if (__builtin_expect(!present, 0)) {
+        give_up(d, ck, total, bs);
+        return;
+    }
+    if ((threadIdx.x & 63) == 0) write_channel_grads(d, ck.channel, all, bs);
+    clear_partials<64>(d, ck.channel);
 }
 
 template <typename T, bool FUSED>
 __device__ __forceinline__ void backward_dispatch(const DevTensor &d, unsigned local_block)
 {
     if (d.wave_units) backward_waves<T, FUSED>(d, local_block);
-    else backward_block<T, FUSED>(d, locate_chunk(d, local_block), local_block);
+    else backward_block<T, FUSED>(d, locate_chunk(d, local_block));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -947,8 +1053,7 @@ __global__ void __launch_bounds__(kBlock) forward_kernel(const DevTensor d)
         const unsigned unit = blockIdx.x * (kBlock / 64) + wave_index();
         if (unit < d.slabs * d.cps) forward_chunk<T, WRITE_Y, EMIT_Q, 64>(d, locate_chunk(d, unit));
     } else {
-        unsigned unit;
-        forward_chunk<T, WRITE_Y, EMIT_Q, kBlock>(d, own_chunk(d, unit));
+        forward_chunk<T, WRITE_Y, EMIT_Q, kBlock>(d, own_chunk(d));
     }
 }
 
@@ -984,9 +1089,7 @@ __global__ void __launch_bounds__(kBlock) backward_kernel(const DevTensor d)
     if (SHAPE == 1) {
         backward_waves<T, FUSED>(d, blockIdx.x);
     } else {
-        unsigned unit;
-        const Chunk ck = own_chunk(d, unit);
-        backward_block<T, FUSED, SHAPE == 2>(d, ck, unit);
+        backward_block<T, FUSED, SHAPE == 2>(d, own_chunk(d));
     }
 }
 
@@ -1090,9 +1193,8 @@ void *scratch_ptr[kMaxDevices];     // per device; nullptr until the first call 
 }  // namespace
 
 // Device address of the scratch array on the current device (0 = success, else a hipError_t).
-// The first call on a device also zeroes the slot region with a fill kernel on `stream`; the
-// loader has zeroed it already and every completed backward leaves it zero, this only makes the
-// starting state explicit.
+// The first call on a device also zeroes it with a fill kernel on `stream`; the loader has zeroed
+// it already and every completed backward leaves it zero, this only makes the starting state explicit.
 int static_scratch(void **ptr, void *stream)
 {
     int device = -1;
@@ -1105,7 +1207,7 @@ int static_scratch(void **ptr, void *stream)
         e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
         if (e != hipSuccess) return (int)e;
         if (!p) return (int)hipErrorInvalidSymbol;
-        const int rc = launch_fill_zero(p, kStaticSlotBytes, stream);
+        const int rc = launch_fill_zero(p, kStaticScratchBytes, stream);
         if (rc != 0) return rc;
         scratch_ptr[device] = p;
     }
@@ -1163,12 +1265,13 @@ static void launch_backward_typed(const DevTensor &d, unsigned blocks, bool fuse
 template <typename T>
 static void launch_backward_shaped(const DevTensor &d, unsigned blocks, bool fused_finalize, hipStream_t st)
 {
-    // The burst schedule stores gx at the very end of a chunk.  Channels that combine by tickets
-    // must wait for their stores before they may draw one, so there it would lengthen the tail it
-    // is meant to shorten (a 1x128x30x40 FP32 tensor with one scale: 6.7 us instead of 5.7).
-    const bool tickets = fused_finalize && d.outer * d.cps > kTreeBlocks;
+    // The burst schedule stores gx at the very end of a chunk, in front of the unit's sum.  Where the
+    // sums are gathered, that would lengthen the tail it is meant to shorten (one scale for 153600
+    // FP32 elements: 5.4 us instead of 4.7; for 2457600 FP16: 7.2 instead of 6.4), so there it is not
+    // used, and the kernel with it leaves the gathering out.
+    const bool gathered = fused_finalize && d.outer * d.cps > kTreeBlocks;
     if (d.wave_units) launch_backward_typed<T, 1>(d, blocks, fused_finalize, st);
-    else if (blocks <= kShortLaunchBlocks && !tickets) launch_backward_typed<T, 2>(d, blocks, fused_finalize, st);
+    else if (blocks <= kShortLaunchBlocks && !gathered) launch_backward_typed<T, 2>(d, blocks, fused_finalize, st);
     else launch_backward_typed<T, 0>(d, blocks, fused_finalize, st);
 }
 
