@@ -11,9 +11,11 @@ constexpr int kVecBytes = 16;        // one 128-bit global load/store per lane
 constexpr int kChunkVecs = 1280;     // at most this many 128-bit vectors per block (20 KiB)
 constexpr int kWaveChunkVecs = kChunkVecs / (kBlock / 64);   // what one wavefront covers: 320 vectors
 constexpr int kComputeUnits = 256;   // MI355X; used by the host to balance blocks over the chip
-// A single-tensor backward launch of at most this many blocks has all of them resident at once
-// (three per compute unit) and takes the schedule made for one burst (backward_chunk, SHORT).
-constexpr unsigned kShortLaunchBlocks = 3 * kComputeUnits;
+// Single-tensor backward launches that take the schedule made for one burst (launch_backward_shaped has
+// the figures): all blocks resident at once, and enough of them and of data.
+constexpr unsigned kBurstMostBlocks = 3 * kComputeUnits;
+constexpr unsigned kBurstLeastBlocksF16 = 640, kBurstLeastBlocksF32 = 400;
+constexpr unsigned kBurstLeastVecsF16 = 900, kBurstLeastVecsF32 = 600;
 // Channels with more units than this have 16 (32) further 64-bit slots in the workspace.  No kernel uses
 // them; they keep fq_workspace_bytes and fq_layout at the values that callers have sized memory by.
 constexpr unsigned kReserveUnits = 16;

@@ -13,6 +13,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "fq_device.h"
 #include "fq_internal.h"
@@ -33,7 +34,7 @@ template <> struct VecOf<_Float16> {
     typedef _Float16 type __attribute__((ext_vector_type(8)));
 };
 
-constexpr int kUnroll = kChunkVecs / kBlock;   // vectors per thread per chunk
+constexpr int kMaxRows = kChunkVecs / kBlock;   // vectors per thread per chunk, at most
 static_assert(kChunkVecs % kBlock == 0, "chunk must be a whole number of block-wide vector rows");
 
 // ---------------------------------------------------------------------------------------------
@@ -266,6 +267,28 @@ template <typename T> __device__ __forceinline__ int head_elems(const void *p, i
     return h < n ? h : n;
 }
 
+// The elements of a chunk that no whole vector covers: `head` of them before the first 16-byte
+// boundary and the rest behind the last whole vector, fewer than two vectors in all.  Lane i < count
+// takes the i-th of them.  They are read together with the vectors, because reading them afterwards
+// adds one dependent trip to memory for either end to every misaligned chunk (3x131x4819 FP16: forward
+// 4.3 us against 3.6, backward 7.15 against 6.1).
+// They stay bit patterns in a register of their own (pin_here) until the vectors are done: the compiler
+// would otherwise convert them where they are read, and wait for them there.
+struct Edges {
+    int count;     // 0 also where nothing can be read as vectors (the caller then goes element by element)
+    int skip;      // elements covered by the vectors
+
+    __device__ __forceinline__ int at(int lane, int head) const { return lane < head ? lane : skip + lane; }
+};
+
+__device__ __forceinline__ unsigned ld_bits(const float *p) { return ld_global((const unsigned *)p); }
+__device__ __forceinline__ unsigned ld_bits(const _Float16 *p) { return ld_global((const unsigned short *)p); }
+template <typename T> __device__ __forceinline__ T from_bits(unsigned b)
+{
+    typedef typename std::conditional<sizeof(T) == 2, unsigned short, unsigned>::type U;
+    return __builtin_bit_cast(T, (U)b);
+}
+
 // Scale of this group's channel (G = 256: the block; G = 64: one wavefront).  Callers issue their
 // first global loads before this, so the evaluation sits in the shadow of the memory latency.
 // A block lets one wavefront (rotating with the block index, so the work spreads over the four
@@ -309,16 +332,16 @@ __device__ __forceinline__ QParams block_params(const DevTensor &d, float theta,
 // ---------------------------------------------------------------------------------------------
 // Forward.
 template <typename T, bool WRITE_Y, bool EMIT_Q>
-__device__ __forceinline__ void forward_elem(const T *x, T *y, int8_t *q, int i, const QParams &p)
+__device__ __forceinline__ void forward_elem(T x, T *y, int8_t *q, int i, const QParams &p)
 {
-    const float v = quotient((float)ld_global(x + i), p);
+    const float v = quotient((float)x, p);
     if (WRITE_Y) st_global(y + i, (T)fq_value(v, p));
     if (EMIT_Q) st_global(q + i, (int8_t)fq_code(v, p));
 }
 
 // WRITE_Y: write the dequantized tensor y.  EMIT_Q: write the int8 codes, N per lane packed into
 // one 64-bit (FP16 input) or 32-bit (FP32 input) store.  At least one of the two.
-template <typename T, bool WRITE_Y, bool EMIT_Q, int G>
+template <typename T, bool WRITE_Y, bool EMIT_Q, int G, int ROWS>
 __device__ __forceinline__ void forward_chunk(const DevTensor &d, const Chunk &ck)
 {
     typedef typename VecOf<T>::type VT;
@@ -336,80 +359,74 @@ __device__ __forceinline__ void forward_chunk(const DevTensor &d, const Chunk &c
     const VT *xv = (const VT *)(x + head);
     VT *yv = WRITE_Y ? (VT *)(y + head) : nullptr;
     const bool q_packed = EMIT_Q && ((uintptr_t)(q + head) % N) == 0;
+    const Edges edges = {vector_ok ? ck.n - nvec * N : 0, nvec * N};
 
     // Issue the first row of loads (straight-line: out-of-range lanes re-read the last vector)
     // before the long binary64 scale evaluation, which then runs under the memory latency.
-    VT r[kUnroll];
+    VT r[ROWS];
     if (nvec > 0) {
         const int last = nvec - 1;
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < ROWS; ++u) {
             int v = u * G + tid;
             r[u] = ld_stream(xv + (v < last ? v : last));
         }
     }
+    unsigned ex = 0u;
+    if (tid < edges.count) ex = ld_bits(x + edges.at(tid, head));
 
     BlockScale bs;
     const QParams p = block_params<false, G>(d, theta, bs);
     if (d.s && ck.first == (long long)ck.channel * d.inner && tid == 0) st_global(d.s + ck.channel, p.s);
 
-    for (int v0 = 0; v0 < nvec;) {
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            int v = v0 + u * G + tid;
-            if (v < nvec) {
-                float quot[N];
+    for (int u = 0; u < ROWS; ++u) {
+        const int v = u * G + tid;
+        if (v < nvec) {
+            float quot[N];
 #pragma unroll
-                for (int e = 0; e < N; ++e) quot[e] = quotient((float)r[u][e], p);
-                if (WRITE_Y) {
-                    // A NaN quotient must come out as NaN, and the clip swallows it.  Instead of a
-                    // compare and a select per element, the row's quotients are tested in pairs
-                    // (one unordered compare sees a NaN in either operand) and only a lane that
-                    // has found one goes back over its row.
-                    VT o;
-                    bool any_nan = false;
+            for (int e = 0; e < N; ++e) quot[e] = quotient((float)r[u][e], p);
+            if (WRITE_Y) {
+                // A NaN quotient must come out as NaN, and the clip swallows it.  Instead of a
+                // compare and a select per element, the row's quotients are tested in pairs
+                // (one unordered compare sees a NaN in either operand) and only a lane that
+                // has found one goes back over its row.
+                VT o;
+                bool any_nan = false;
 #pragma unroll
-                    for (int e = 0; e < N; e += 2) any_nan |= __builtin_isunordered(quot[e], quot[e + 1]);
+                for (int e = 0; e < N; e += 2) any_nan |= __builtin_isunordered(quot[e], quot[e + 1]);
 #pragma unroll
-                    for (int e = 0; e < N; ++e) o[e] = (T)fq_value_finite(quot[e], p);
-                    if (__builtin_expect(any_nan, 0)) {
-                        asm volatile("" ::: "memory");       // keep this a branch: it is almost never taken
+                for (int e = 0; e < N; ++e) o[e] = (T)fq_value_finite(quot[e], p);
+                if (__builtin_expect(any_nan, 0)) {
+                    asm volatile("" ::: "memory");       // keep this a branch: it is almost never taken
 #pragma unroll
-                        for (int e = 0; e < N; ++e) o[e] = (T)fq_value(quot[e], p);
-                    }
-                    st_stream(yv + v, o);
+                    for (int e = 0; e < N; ++e) o[e] = (T)fq_value(quot[e], p);
                 }
-                if (EMIT_Q) {
-                    int c[N];
+                st_stream(yv + v, o);
+            }
+            if (EMIT_Q) {
+                int c[N];
 #pragma unroll
-                    for (int e = 0; e < N; ++e) c[e] = fq_code(quot[e], p);
-                    if (q_packed) {
-                        QV codes;
+                for (int e = 0; e < N; ++e) c[e] = fq_code(quot[e], p);
+                if (q_packed) {
+                    QV codes;
 #pragma unroll
-                        for (int g = 0; g < N / 4; ++g)
-                            codes[g] = pack_codes4(c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]);
-                        st_stream((QV *)(q + head + v * N), codes);
-                    } else {
+                    for (int g = 0; g < N / 4; ++g)
+                        codes[g] = pack_codes4(c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]);
+                    st_stream((QV *)(q + head + v * N), codes);
+                } else {
 #pragma unroll
-                        for (int e = 0; e < N; ++e) st_global(q + head + v * N + e, (int8_t)c[e]);
-                    }
+                    for (int e = 0; e < N; ++e) st_global(q + head + v * N + e, (int8_t)c[e]);
                 }
             }
         }
-        v0 += kUnroll * G;
-        if (v0 >= nvec) break;
-        const int last = nvec - 1;
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            int v = v0 + u * G + tid;
-            r[u] = ld_stream(xv + (v < last ? v : last));
-        }
     }
 
-    // scalar head (before the first 16-byte boundary, or the whole chunk if x and y are
-    // misaligned relative to each other) and tail (after the last whole vector)
-    for (int i = tid; i < head; i += G) forward_elem<T, WRITE_Y, EMIT_Q>(x, y, q, i, p);
-    for (int i = head + nvec * N + tid; i < ck.n; i += G) forward_elem<T, WRITE_Y, EMIT_Q>(x, y, q, i, p);
+    pin_here(ex);
+    if (tid < edges.count) forward_elem<T, WRITE_Y, EMIT_Q>(from_bits<T>(ex), y, q, edges.at(tid, head), p);
+    if (!vector_ok) {               // x and y are misaligned relative to each other
+        for (int i = tid; i < ck.n; i += G) forward_elem<T, WRITE_Y, EMIT_Q>(ld_global(x + i), y, q, i, p);
+    }
 }
 
 // what one tensor asks of the forward pass: y only, y and codes, or codes only
@@ -417,9 +434,9 @@ template <typename T, int G>
 __device__ __forceinline__ void forward_variants(const DevTensor &d, unsigned unit)
 {
     const Chunk ck = locate_chunk(d, unit);
-    if (!d.q) forward_chunk<T, true, false, G>(d, ck);
-    else if (d.y) forward_chunk<T, true, true, G>(d, ck);
-    else forward_chunk<T, false, true, G>(d, ck);
+    if (!d.q) forward_chunk<T, true, false, G, kMaxRows>(d, ck);
+    else if (d.y) forward_chunk<T, true, true, G, kMaxRows>(d, ck);
+    else forward_chunk<T, false, true, G, kMaxRows>(d, ck);
 }
 
 // Tensors whose slabs are short (d.wave_units) give every wavefront a slab of its own: four
@@ -440,19 +457,17 @@ __device__ __forceinline__ void forward_dispatch(const DevTensor &d, unsigned lo
 // gy*t is exact in binary64 (two 24-bit significands), so the per-channel sum differs from a
 // sequential binary64 sum only by binary64 rounding, however badly the terms cancel.
 template <typename T, bool WRITE_GX>
-__device__ __forceinline__ double backward_elem(const T *x, const T *gy, T *gx, int i, const QParams &p,
-                                                double acc)
+__device__ __forceinline__ double backward_elem(T x, T g, T *gx, int i, const QParams &p, double acc)
 {
     bool in_range, is_nan;
-    T g = ld_global(gy + i);
-    float t = ste_terms((float)ld_global(x + i), p, in_range, is_nan);
+    float t = ste_terms((float)x, p, in_range, is_nan);
     if (WRITE_GX) st_global(gx + i, in_range ? g : (T)0.0f);
     acc = __builtin_fma((double)(float)g, (double)t, acc);
     return is_nan ? __builtin_nan("") : acc;
 }
 
 // Per-thread sum of gy*t over this thread's elements of the chunk (binary64).
-template <typename T, bool WRITE_GX, int G>
+template <typename T, bool WRITE_GX, int G, int ROWS>
 __device__ __forceinline__ double backward_chunk(const DevTensor &d, const Chunk &ck, BlockScale &bs)
 {
     typedef typename VecOf<T>::type VT;
@@ -471,62 +486,60 @@ __device__ __forceinline__ double backward_chunk(const DevTensor &d, const Chunk
     const VT *xv = (const VT *)(x + head);
     const VT *gv = (const VT *)(gy + head);
     VT *ov = WRITE_GX ? (VT *)(gx + head) : nullptr;
+    const Edges edges = {vector_ok ? ck.n - nvec * N : 0, nvec * N};
 
-    VT rx[kUnroll], rg[kUnroll];
+    VT rx[ROWS], rg[ROWS];
     if (nvec > 0) {
         const int last = nvec - 1;
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < ROWS; ++u) {
             int v = u * G + tid;
             v = v < last ? v : last;
             rx[u] = ld_stream(xv + v);
             rg[u] = ld_stream(gv + v);
         }
     }
+    unsigned ex = 0u, eg = 0u;
+    if (tid < edges.count) {
+        ex = ld_bits(x + edges.at(tid, head));
+        eg = ld_bits(gy + edges.at(tid, head));
+    }
 
     const QParams p = block_params<true, G>(d, theta, bs);
 
-    double acc[kUnroll];
+    double acc[ROWS];
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) acc[u] = 0.0;
+    for (int u = 0; u < ROWS; ++u) acc[u] = 0.0;
 
-    for (int v0 = 0; v0 < nvec;) {
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            int v = v0 + u * G + tid;
-            if (v < nvec) {
-                VT o;
-                bool any_nan = false;
+    for (int u = 0; u < ROWS; ++u) {
+        const int v = u * G + tid;
+        if (v < nvec) {
+            VT o;
+            bool any_nan = false;
 #pragma unroll
-                for (int e = 0; e < N; ++e) {
-                    bool in_range, is_nan;
-                    float t = ste_terms((float)rx[u][e], p, in_range, is_nan);
-                    o[e] = in_range ? rg[u][e] : (T)0.0f;
-                    acc[u] = __builtin_fma((double)(float)rg[u][e], (double)t, acc[u]);
-                    any_nan |= is_nan;
-                }
-                if (any_nan) acc[u] = __builtin_nan("");   // a NaN quotient poisons its channel
-                if (WRITE_GX) st_stream(ov + v, o);
+            for (int e = 0; e < N; ++e) {
+                bool in_range, is_nan;
+                float t = ste_terms((float)rx[u][e], p, in_range, is_nan);
+                o[e] = in_range ? rg[u][e] : (T)0.0f;
+                acc[u] = __builtin_fma((double)(float)rg[u][e], (double)t, acc[u]);
+                any_nan |= is_nan;
             }
-        }
-        v0 += kUnroll * G;
-        if (v0 >= nvec) break;
-        const int last = nvec - 1;
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            int v = v0 + u * G + tid;
-            v = v < last ? v : last;
-            rx[u] = ld_stream(xv + v);
-            rg[u] = ld_stream(gv + v);
+            if (any_nan) acc[u] = __builtin_nan("");   // a NaN quotient poisons its channel
+            if (WRITE_GX) st_stream(ov + v, o);
         }
     }
 
     double sum = 0.0;
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) sum += acc[u];
-    for (int i = tid; i < head; i += G) sum = backward_elem<T, WRITE_GX>(x, gy, gx, i, p, sum);
-    for (int i = head + nvec * N + tid; i < ck.n; i += G)
-        sum = backward_elem<T, WRITE_GX>(x, gy, gx, i, p, sum);
+    for (int u = 0; u < ROWS; ++u) sum += acc[u];
+    pin_here(ex);
+    pin_here(eg);
+    if (tid < edges.count) sum = backward_elem<T, WRITE_GX>(from_bits<T>(ex), from_bits<T>(eg), gx, edges.at(tid, head), p, sum);
+    if (!vector_ok) {               // x, gy and gx are misaligned relative to each other
+        for (int i = tid; i < ck.n; i += G)
+            sum = backward_elem<T, WRITE_GX>(ld_global(x + i), ld_global(gy + i), gx, i, p, sum);
+    }
     return sum;
 }
 
@@ -542,7 +555,7 @@ __device__ __forceinline__ double backward_chunk(const DevTensor &d, const Chunk
 // three wavefronts per SIMD), which costs a large launch more than the schedule gains (a
 // 15x128x120x160 FP16 tensor: 44.5 us instead of 40.7), so larger launches interleave as before.
 // The arithmetic and its order are the same in both schedules; so are the bits.
-template <typename T, bool WRITE_GX, int G>
+template <typename T, bool WRITE_GX, int G, int ROWS>
 __device__ __forceinline__ double backward_chunk_short(const DevTensor &d, const Chunk &ck, BlockScale &bs)
 {
     typedef typename VecOf<T>::type VT;
@@ -561,34 +574,39 @@ __device__ __forceinline__ double backward_chunk_short(const DevTensor &d, const
     const VT *xv = (const VT *)(x + head);
     const VT *gv = (const VT *)(gy + head);
     VT *ov = WRITE_GX ? (VT *)(gx + head) : nullptr;
+    const Edges edges = {vector_ok ? ck.n - nvec * N : 0, nvec * N};
 
-    VT rx[kUnroll], rg[kUnroll];
-    auto request = [&](int v0) {      // out-of-range lanes re-read the last vector
+    VT rx[ROWS], rg[ROWS];
+    if (nvec > 0) {                   // out-of-range lanes re-read the last vector
         const int last = nvec - 1;
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int v = v0 + u * G + tid;
+        for (int u = 0; u < ROWS; ++u) {
+            const int v = u * G + tid;
             rx[u] = ld_stream(xv + (v < last ? v : last));
         }
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int v = v0 + u * G + tid;
+        for (int u = 0; u < ROWS; ++u) {
+            const int v = u * G + tid;
             rg[u] = ld_stream(gv + (v < last ? v : last));
         }
-    };
-    if (nvec > 0) request(0);
+    }
+    unsigned ex = 0u, eg = 0u;
+    if (tid < edges.count) {
+        ex = ld_bits(x + edges.at(tid, head));
+        eg = ld_bits(gy + edges.at(tid, head));
+    }
 
     const QParams p = block_params<true, G>(d, theta, bs);
 
-    double acc[kUnroll];
+    double acc[ROWS];
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) acc[u] = 0.0;
+    for (int u = 0; u < ROWS; ++u) acc[u] = 0.0;
 
-    for (int v0 = 0; v0 < nvec;) {
-        float t[kUnroll][N];
-        unsigned inside[kUnroll], nan_row[kUnroll];
+    if (nvec > 0) {
+        float t[ROWS][N];
+        unsigned inside[ROWS], nan_row[ROWS];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < ROWS; ++u) {
             inside[u] = 0u;
             nan_row[u] = 0u;
 #pragma unroll
@@ -600,10 +618,11 @@ __device__ __forceinline__ double backward_chunk_short(const DevTensor &d, const
                 pin_here(t[u][e]);
             }
             pin_here(inside[u]);
+            __builtin_amdgcn_sched_barrier(0);     // row by row: each waits for its own x alone
         }
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int v = v0 + u * G + tid;
+        for (int u = 0; u < ROWS; ++u) {
+            const int v = u * G + tid;
             if (v < nvec) {
                 VT o;
 #pragma unroll
@@ -617,22 +636,23 @@ __device__ __forceinline__ double backward_chunk_short(const DevTensor &d, const
         }
         if (WRITE_GX) {
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                const int v = v0 + u * G + tid;
+            for (int u = 0; u < ROWS; ++u) {
+                const int v = u * G + tid;
                 if (v < nvec) st_stream(ov + v, rg[u]);
             }
         }
-        v0 += kUnroll * G;
-        if (v0 >= nvec) break;
-        request(v0);
     }
 
     double sum = 0.0;
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) sum += acc[u];
-    for (int i = tid; i < head; i += G) sum = backward_elem<T, WRITE_GX>(x, gy, gx, i, p, sum);
-    for (int i = head + nvec * N + tid; i < ck.n; i += G)
-        sum = backward_elem<T, WRITE_GX>(x, gy, gx, i, p, sum);
+    for (int u = 0; u < ROWS; ++u) sum += acc[u];
+    pin_here(ex);
+    pin_here(eg);
+    if (tid < edges.count) sum = backward_elem<T, WRITE_GX>(from_bits<T>(ex), from_bits<T>(eg), gx, edges.at(tid, head), p, sum);
+    if (!vector_ok) {               // x, gy and gx are misaligned relative to each other
+        for (int i = tid; i < ck.n; i += G)
+            sum = backward_elem<T, WRITE_GX>(ld_global(x + i), ld_global(gy + i), gx, i, p, sum);
+    }
     return sum;
 }
 
@@ -903,7 +923,7 @@ __device__ __forceinline__ void give_up(const DevTensor &d, const Chunk &ck, dou
 }
 
 // One block of the backward grid, owning one chunk of one slab.
-template <typename T, bool FUSED, bool SHORT = false>
+template <typename T, bool FUSED, int ROWS, bool SHORT = false>
 __device__ __forceinline__ void backward_block(const DevTensor &d, const Chunk &ck)
 {
     __shared__ double wave_part[kBlock / 64];
@@ -913,8 +933,8 @@ __device__ __forceinline__ void backward_block(const DevTensor &d, const Chunk &
     const bool write_gx = !(d.flags & 1u);
     BlockScale bs;
     double sum;
-    if (SHORT) sum = write_gx ? backward_chunk_short<T, true, kBlock>(d, ck, bs) : backward_chunk_short<T, false, kBlock>(d, ck, bs);
-    else sum = write_gx ? backward_chunk<T, true, kBlock>(d, ck, bs) : backward_chunk<T, false, kBlock>(d, ck, bs);
+    if (SHORT) sum = write_gx ? backward_chunk_short<T, true, kBlock, ROWS>(d, ck, bs) : backward_chunk_short<T, false, kBlock, ROWS>(d, ck, bs);
+    else sum = write_gx ? backward_chunk<T, true, kBlock, ROWS>(d, ck, bs) : backward_chunk<T, false, kBlock, ROWS>(d, ck, bs);
 
     sum = wave_sum(sum);
     if ((threadIdx.x & 63) == kSumLane) wave_part[threadIdx.x >> 6] = sum;
@@ -968,7 +988,7 @@ __device__ __forceinline__ void backward_block(const DevTensor &d, const Chunk &
 // One block of the backward grid for a tensor with short slabs: every wavefront owns a slab (a
 // unit) of its own -- scale, sum, combination and, if it is its channel's collector,
 // the final sum, all per wavefront; the block never meets at a barrier.
-template <typename T, bool FUSED>
+template <typename T, bool FUSED, int ROWS>
 __device__ __forceinline__ void backward_waves(const DevTensor &d, unsigned local_block)
 {
     const unsigned unit = local_block * (kBlock / 64) + wave_index();
@@ -976,7 +996,7 @@ __device__ __forceinline__ void backward_waves(const DevTensor &d, unsigned loca
     const bool write_gx = !(d.flags & 1u);
     const Chunk ck = locate_chunk(d, unit);
     BlockScale bs;
-    double sum = write_gx ? backward_chunk<T, true, 64>(d, ck, bs) : backward_chunk<T, false, 64>(d, ck, bs);
+    double sum = write_gx ? backward_chunk<T, true, 64, ROWS>(d, ck, bs) : backward_chunk<T, false, 64, ROWS>(d, ck, bs);
     const double total = read_lane(wave_sum(sum), kSumLane);
     const unsigned bpc = d.outer * d.cps;
     if (!FUSED || bpc <= kTreeBlocks) {
@@ -1005,8 +1025,8 @@ __device__ __forceinline__ void backward_waves(const DevTensor &d, unsigned loca
 template <typename T, bool FUSED>
 __device__ __forceinline__ void backward_dispatch(const DevTensor &d, unsigned local_block)
 {
-    if (d.wave_units) backward_waves<T, FUSED>(d, local_block);
-    else backward_block<T, FUSED>(d, locate_chunk(d, local_block));
+    if (d.wave_units) backward_waves<T, FUSED, kMaxRows>(d, local_block);
+    else backward_block<T, FUSED, kMaxRows>(d, locate_chunk(d, local_block));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1045,15 +1065,16 @@ __device__ __forceinline__ DevTensor fetch(const DevTensor *table, int i)
 }
 
 // Single tensor: descriptor in the kernel arguments (SGPRs), dtype fixed at compile time.
-// WAVES: the tensor's slabs are short and every wavefront owns one (chosen by the launcher).
-template <typename T, bool WRITE_Y, bool EMIT_Q, bool WAVES>
+// WAVES: the tensor's slabs are short and every wavefront owns one (chosen by the launcher).  ROWS: the
+// vectors per lane that a whole chunk of this tensor has.
+template <typename T, bool WRITE_Y, bool EMIT_Q, bool WAVES, int ROWS>
 __global__ void __launch_bounds__(kBlock) forward_kernel(const DevTensor d)
 {
     if (WAVES) {
         const unsigned unit = blockIdx.x * (kBlock / 64) + wave_index();
-        if (unit < d.slabs * d.cps) forward_chunk<T, WRITE_Y, EMIT_Q, 64>(d, locate_chunk(d, unit));
+        if (unit < d.slabs * d.cps) forward_chunk<T, WRITE_Y, EMIT_Q, 64, ROWS>(d, locate_chunk(d, unit));
     } else {
-        forward_chunk<T, WRITE_Y, EMIT_Q, kBlock>(d, own_chunk(d));
+        forward_chunk<T, WRITE_Y, EMIT_Q, kBlock, ROWS>(d, own_chunk(d));
     }
 }
 
@@ -1070,26 +1091,26 @@ __global__ void __launch_bounds__(kBlock) forward_multi_kernel(const DevTensor *
         if (d.wave_units) {
             const unsigned unit = local * (kBlock / 64) + wave_index();
             if (unit < d.slabs * d.cps) {
-                if (d.dtype == 0) forward_chunk<_Float16, true, false, 64>(d, locate_chunk(d, unit));
-                else forward_chunk<float, true, false, 64>(d, locate_chunk(d, unit));
+                if (d.dtype == 0) forward_chunk<_Float16, true, false, 64, kMaxRows>(d, locate_chunk(d, unit));
+                else forward_chunk<float, true, false, 64, kMaxRows>(d, locate_chunk(d, unit));
             }
         } else if (d.dtype == 0) {
-            forward_chunk<_Float16, true, false, kBlock>(d, locate_chunk(d, local));
+            forward_chunk<_Float16, true, false, kBlock, kMaxRows>(d, locate_chunk(d, local));
         } else {
-            forward_chunk<float, true, false, kBlock>(d, locate_chunk(d, local));
+            forward_chunk<float, true, false, kBlock, kMaxRows>(d, locate_chunk(d, local));
         }
     }
 }
 
 // SHAPE: 0 = one chunk per block; 1 = one slab per wavefront (short slabs); 2 = one chunk per block
-// in a launch of at most kShortLaunchBlocks blocks (see backward_chunk, SHORT).
-template <typename T, bool FUSED, int SHAPE>
+// with the burst schedule (see backward_chunk_short and launch_backward_shaped).
+template <typename T, bool FUSED, int SHAPE, int ROWS>
 __global__ void __launch_bounds__(kBlock) backward_kernel(const DevTensor d)
 {
     if (SHAPE == 1) {
-        backward_waves<T, FUSED>(d, blockIdx.x);
+        backward_waves<T, FUSED, ROWS>(d, blockIdx.x);
     } else {
-        backward_block<T, FUSED, SHAPE == 2>(d, own_chunk(d));
+        backward_block<T, FUSED, ROWS, SHAPE == 2>(d, own_chunk(d));
     }
 }
 
@@ -1231,12 +1252,41 @@ static void launch_tensor(K kernel, unsigned blocks, hipStream_t st, const DevTe
     hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, st, d);
 }
 
+// Vectors in a whole chunk, and how many of them a lane has at most: 1 to kMaxRows.
+template <typename T> static unsigned chunk_vecs(const DevTensor &d) { return (d.chunk + VecOf<T>::N - 1) / VecOf<T>::N; }
+template <typename T> static int chunk_rows(const DevTensor &d)
+{
+    const unsigned lanes = d.wave_units ? 64u : (unsigned)kBlock;
+    return (int)((chunk_vecs<T>(d) + lanes - 1) / lanes);
+}
+
+// Calls f with a number of rows as a compile-time constant: `rows` itself, or kMaxRows from MOST + 1 on.
+// A kernel built for exactly the rows of the tensor issues no loads past the end of a chunk and runs
+// through less code; short chunks feel both.
+template <int MOST, typename F> static void with_rows(int rows, F f)
+{
+    if (rows == 1) return f(std::integral_constant<int, 1>());
+    if (rows == 2) return f(std::integral_constant<int, 2>());
+    if (MOST >= 3 && rows == 3) return f(std::integral_constant<int, MOST >= 3 ? 3 : kMaxRows>());
+    if (MOST >= 4 && rows == 4) return f(std::integral_constant<int, MOST >= 4 ? 4 : kMaxRows>());
+    return f(std::integral_constant<int, kMaxRows>());
+}
+
+// Forward, us before -> with exactly one or two rows: 153600 FP32 elements 2.47 -> 2.31; 64x147 FP32 3.05 ->
+// 2.65; 384x3456 FP32 3.31 -> 3.19.  With three rows exactness loses (3x128x4800 FP16: 3.42 -> 3.48), and
+// so it does for wavefront units (15x384x1200 FP16: 6.70 -> 6.94), so those take kMaxRows.
 template <typename T, bool WAVES>
 static void launch_forward_single(const DevTensor &d, unsigned blocks, hipStream_t st)
 {
-    if (!d.q) launch_tensor(forward_kernel<T, true, false, WAVES>, blocks, st, d);
-    else if (d.y) launch_tensor(forward_kernel<T, true, true, WAVES>, blocks, st, d);
-    else launch_tensor(forward_kernel<T, false, true, WAVES>, blocks, st, d);
+    if (WAVES || d.q) {
+        if (!d.q) launch_tensor(forward_kernel<T, true, false, WAVES, kMaxRows>, blocks, st, d);
+        else if (d.y) launch_tensor(forward_kernel<T, true, true, WAVES, kMaxRows>, blocks, st, d);
+        else launch_tensor(forward_kernel<T, false, true, WAVES, kMaxRows>, blocks, st, d);
+        return;
+    }
+    with_rows<2>(chunk_rows<T>(d), [&](auto rows) {
+        launch_tensor(forward_kernel<T, true, false, false, decltype(rows)::value>, blocks, st, d);
+    });
 }
 
 int launch_forward(const KArgs &a, unsigned blocks, bool emit_q, void *stream)
@@ -1255,24 +1305,48 @@ int launch_forward(const KArgs &a, unsigned blocks, bool emit_q, void *stream)
     return (int)hipGetLastError();
 }
 
+// Backward, us before -> with exactly the tensor's rows: 1x512x4800 FP16 (three rows) 5.1 -> 4.6; 64x576 FP32
+// (one) 3.3 -> 2.9; 15x384x1200 FP16 (three, wavefront units) 11.5 -> 10.9.
 template <typename T, int SHAPE>
 static void launch_backward_typed(const DevTensor &d, unsigned blocks, bool fused_finalize, hipStream_t st)
 {
-    if (fused_finalize) launch_tensor(backward_kernel<T, true, SHAPE>, blocks, st, d);
-    else launch_tensor(backward_kernel<T, false, SHAPE>, blocks, st, d);
+    if (!fused_finalize) {
+        launch_tensor(backward_kernel<T, false, SHAPE, kMaxRows>, blocks, st, d);
+        return;
+    }
+    with_rows<4>(chunk_rows<T>(d), [&](auto rows) {
+        launch_tensor(backward_kernel<T, true, SHAPE, decltype(rows)::value>, blocks, st, d);
+    });
+}
+
+// The burst schedule (backward_chunk_short) pays in launches that are resident at once (at most three
+// blocks per compute unit) and move much data: its arithmetic lies in front of the last loads, but it is
+// more arithmetic and more registers.  Measured against the interleaved schedule, us, burst / interleaved:
+//   FP16  768 blocks x 1200 vectors 9.2 / 9.65   768 x 1000 7.8 / 8.2   700 x 1200 9.2 / 9.2
+//         600 x 1200 8.7 / 8.3   768 x 800 7.2 / 7.1   768 x 600 6.2 / 5.7   400 x 1200 7.1 / 6.3
+//   FP32  768 x 1200 8.5 / 8.9   512 x 1200 6.2 / 6.5   400 x 1200 5.4 / 5.9   768 x 600 4.95 / 5.3
+//         512 x 600 4.2 / 4.3   400 x 600 4.1 / 4.0   768 x 432 5.0 / 4.9   64 x 144 3.0 / 2.9
+// It stores gx at the very end of a chunk, in front of the unit's sum.  Where the sums are gathered, that
+// would lengthen the tail it is meant to shorten (one scale for 153600 FP32 elements: 5.4 instead of 4.7;
+// for 2457600 FP16: 7.2 instead of 6.4), so there it is not used, and the kernel with it leaves the
+// gathering out.
+template <typename T> static bool burst_pays(const DevTensor &d, unsigned blocks)
+{
+    const bool half = sizeof(T) == 2;
+    return blocks <= kBurstMostBlocks && blocks >= (half ? kBurstLeastBlocksF16 : kBurstLeastBlocksF32) &&
+           chunk_vecs<T>(d) >= (half ? kBurstLeastVecsF16 : kBurstLeastVecsF32);
 }
 
 template <typename T>
 static void launch_backward_shaped(const DevTensor &d, unsigned blocks, bool fused_finalize, hipStream_t st)
 {
-    // The burst schedule stores gx at the very end of a chunk, in front of the unit's sum.  Where the
-    // sums are gathered, that would lengthen the tail it is meant to shorten (one scale for 153600
-    // FP32 elements: 5.4 us instead of 4.7; for 2457600 FP16: 7.2 instead of 6.4), so there it is not
-    // used, and the kernel with it leaves the gathering out.
     const bool gathered = fused_finalize && d.outer * d.cps > kTreeBlocks;
     if (d.wave_units) launch_backward_typed<T, 1>(d, blocks, fused_finalize, st);
-    else if (blocks <= kShortLaunchBlocks && !gathered) launch_backward_typed<T, 2>(d, blocks, fused_finalize, st);
-    else launch_backward_typed<T, 0>(d, blocks, fused_finalize, st);
+    else if (fused_finalize && !gathered && burst_pays<T>(d, blocks)) {
+        if (chunk_rows<T>(d) <= 3) launch_tensor(backward_kernel<T, true, 2, 3>, blocks, st, d);
+        else if (chunk_rows<T>(d) == 4) launch_tensor(backward_kernel<T, true, 2, 4>, blocks, st, d);
+        else launch_tensor(backward_kernel<T, true, 2, kMaxRows>, blocks, st, d);
+    } else launch_backward_typed<T, 0>(d, blocks, fused_finalize, st);
 }
 
 static void launch_backward_single(const DevTensor &d, unsigned blocks, bool fused_finalize, hipStream_t st)
