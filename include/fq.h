@@ -257,8 +257,8 @@ void fq_plan_destroy(fq_plan *plan);
  * gstudent = upstream * dloss/dstudent in the tensors' dtype (rounded once from binary64; a
  * clamped norm counts as a constant).  `upstream` is the factor in front of this pair's loss in
  * the total (Eq. (7) sums the pairs: 1, or the loss scale of an FP16 run).  student / teacher are
- * contiguous [n, channels, inner]; gstudent may be exactly student or teacher (in place).  Two or
- * three launches; no atomics, fixed summation order.  A tensor without elements needs no workspace and
+ * contiguous [n, channels, inner]; gstudent may be exactly student or teacher (in place).  One or
+ * two launches; fixed summation order.  A tensor without elements needs no workspace and
  * gives NaN for mse and loss (a mean of nothing); cosim is then NaN without positions and 0 with
  * positions but no channels.  The workspace need not be initialised and may be shared with other such calls
  * that do not overlap in time.
@@ -272,11 +272,12 @@ typedef struct fq_distill {
     double *out;                      /* out: 3 doubles, 8-byte aligned */
 } fq_distill;
 size_t fq_distill_workspace_bytes(const fq_distill *d);   /* 0 if d does not validate; host only */
-/* How often fq_distill_loss reads the pair from memory for this descriptor: 1 (one fused kernel
-   holds a tile of the pair in registers from the statistics to the gradient: up to 512 channels,
-   inner a multiple of 4, pointers aligned to 4 elements; also when no gradient is asked for) or 2
-   (a statistics kernel, then a gradient kernel); 0 if d does not validate or has no elements.
-   Pure host function. */
+/* How often at most fq_distill_loss reads a line of the pair from memory for this descriptor: 1 (one
+   fused kernel holds a tile of the pair in registers from the statistics to the gradient: up to 512
+   channels, inner a multiple of 4, pointers aligned to 4 elements; also when no gradient is asked
+   for) or 2 (the fused kernel on rows off that grid, whose tiles share the lines at their ends, or,
+   with more channels, a statistics kernel and then a gradient kernel); 0 if d does not validate or
+   has no elements.  Pure host function. */
 int fq_distill_reads_of_pair(const fq_distill *d);
 fq_status fq_distill_loss(const fq_distill *d, void *workspace, size_t ws_bytes, void *hip_stream);
 

@@ -7,29 +7,41 @@
 // stride is M elements, so the layout is read the way it lies in memory, without transposition and
 // without atomics.  Two ways, chosen on the host:
 //
-// One read of the pair (fused kernel; channel counts up to 512, M a multiple of 4): a block owns a
-// tile of all channels x one 128-byte run of positions (64 FP16 or 32 FP32 positions); a lane holds
-// 4 consecutive positions of up to 16 channels IN REGISTERS, adds its four sums (a.b, a.a, b.b,
-// (a-b)^2) per position, the block adds the lanes' sums through LDS in a fixed order, forms cos and
-// the two gradient coefficients per position, and every lane then writes the gradient of the
-// elements it still holds.  HBM traffic: read a, read b, write ga -- the algorithmic 3 bytes-widths
-// per element.
+// One pass (fused kernel; channel counts up to 512): a block owns a tile of all channels x one run of
+// positions, 128 bytes of each channel (64 FP16 or 32 FP32 positions; 512 threads) or 256 bytes (1024
+// threads); a lane holds 4 consecutive positions of up to 16 channels IN REGISTERS, adds its three sums
+// (a.b, a.a, b.b) per position and its one sum of (a-b)^2, the wavefront adds its rows by lane exchanges,
+// the block adds the wavefronts through LDS in a fixed order, forms cos and the two gradient coefficients
+// per position, and every lane then writes the gradient of the elements it still holds.  HBM traffic:
+// read a, read b, write ga -- the algorithmic 3 bytes-widths per element -- where the rows lie on the
+// 4-element grid.  Rows that do not are read at any address, and the lines at a tile's ends come twice;
+// neighbouring tiles then go to one XCD, so that its L2 has them.
+//   Measured, us, before -> now: 1x384x19200 FP16 15.9 -> 12.6 (the sums over rows went through LDS in two
+//   passes of 32 dependent additions, and a second launch added the tiles), 1x128x1200 7.1 -> 5.0,
+//   15x128x19200 45.3 -> 43.7, 1x384x19200 FP32 25.9 -> 22.3, 4x128x19200 FP32 29.9 -> 25.5; off the grid,
+//   where two kernels used to read the pair: 2x128x4819 FP32 13.1 -> 6.6, 4x256x9601 FP32 55.9 -> 35.3,
+//   8x250x5001 FP16 39.7 -> 21.9.
 //
-// Two reads (any shape): a wavefront owns 64 lanes x V consecutive positions (one coalesced row per
-// channel) and walks over a group of channels, every lane keeping the four sums of its V positions
+// Two reads (more than 512 channels): a wavefront owns 64 lanes x V consecutive positions (one coalesced
+// row per channel) and walks over a group of channels, every lane keeping the four sums of its V positions
 // in binary64 registers:
 //   stats kernel   one block per position tile, one wavefront per channel group (up to 16); the
 //                  wavefronts add their sums through LDS in a fixed tree, then the block forms
 //                  cos and the two coefficients of the gradient for its positions and leaves
 //                  its sums of cos and of the squared error
 //   grad kernel    elementwise: ga = k1 (a - b) - cB b + cA a, rounded once to the I/O type
-// In both, the last small step adds the per-block sums in index order into the 3 results.
+// The last small step adds the per-block sums in a fixed order into the 3 results: in the fused kernel
+// itself up to 256 tiles (gather_tiles), in a kernel of its own (distill_finish_kernel) or in the
+// gradient kernel otherwise.
 // All arithmetic is binary64 (two conversions and five fused multiply-adds per element pair, well
 // under the memory time), so results do not depend on how the channels were grouped beyond
 // rounding at the 1e-16 level, and are reproducible run to run.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+
+#include <atomic>
+#include <chrono>
 
 #include "../../include/fq.h"
 #include "fq_device.h"
@@ -55,9 +67,11 @@ struct DistillArgs {
     void *ga;
     double *coef;       // [positions][2]
     double *blocksum;   // [tiles][2]: per-block sums of cos and of (a-b)^2
+    unsigned long long *records;   // [tiles][4] and a flag: the same for a kernel that gathers them itself
+    unsigned long long nonce;      // this call's number; 0: a second kernel adds the tiles' sums
     double *out;        // mse, cosim, loss
     long long M, P;     // positions per image, positions in total
-    unsigned C, groups, per_group, tiles_per_n, tiles;
+    unsigned C, groups, per_group, tiles_per_n, tiles, poll_rounds;
     double k1u, k2u, eps, lambda, inv_ncm, inv_nm;
 };
 
@@ -380,53 +394,211 @@ __global__ __launch_bounds__(kThreads) void distill_grad_kernel(DistillArgs k, u
 }
 
 // ---------------------------------------------------------------------------------------------
-// One read of the pair.  Block: kFusedThreads threads = R rows of L lanes; lane l of row r holds
+// One pass over the pair.  A block of THREADS threads = R rows of L lanes; lane l of row r holds
 // positions 4l .. 4l+3 of the tile for channels r, r + R, r + 2R, ... (KCH of them at most).
-constexpr int kFusedThreads = 512;
 constexpr int kFusedVec = 4;                     // positions per lane
 constexpr int kFusedMaxKch = 16;                 // channels per lane the registers hold (FP16; half for FP32)
-// A tile's rows are 128 bytes of each channel, a whole cache line.  (Rows of 64 bytes would cut a
-// 1x384x120x160 pair into 600 tiles instead of 300 and spread them more evenly over the 256
-// compute units, but half-line accesses cost more than the balance gains: 24.4 us against 16.9.)
-template <typename T> struct FusedShape {
-    static constexpr int L = 128 / (kFusedVec * (int)sizeof(T));   // lanes per row: 16 (FP16), 8 (FP32)
-    static constexpr int P = kFusedVec * L;                        // positions per tile: 64 / 32
-    static constexpr int R = kFusedThreads / L;                    // channel rows: 32 / 64
+constexpr int kNarrowThreads = 512, kWideThreads = 1024;
+// A narrow tile's rows are 128 bytes of each channel, a whole cache line, a wide tile's two lines.
+// (Rows of 64 bytes would cut a 1x384x120x160 pair into 600 tiles and spread them more evenly over the
+// 256 compute units, but half-line accesses cost more than the balance gains: 24.4 us against 16.9.)
+template <typename T, int THREADS> struct FusedShape {
+    static constexpr int L = THREADS / 4 / (kFusedVec * (int)sizeof(T));   // lanes per row
+    static constexpr int P = kFusedVec * L;                                // positions per tile
+    static constexpr int R = THREADS / L;                                  // channel rows: 32 (FP16), 64 (FP32)
 };
 
-template <typename T, int KCH, bool WANT_GRAD>
-__global__ __launch_bounds__(kFusedThreads, 4) void distill_fused_kernel(DistillArgs k)
-{
-    typedef FusedShape<T> Shape;
-    constexpr int V = kFusedVec, L = Shape::L, P = Shape::P, R = Shape::R;
-    typedef typename Pack<T, V>::type VT;
-    __shared__ double red[8 * kFusedThreads];     // half of the lanes' sums at a time: [value][thread]
-    __shared__ double stat[P * 4];                // per position: a.b, a.a, b.b, (a-b)^2
-    __shared__ double coefs[P * 2];               // per position: the two gradient coefficients
+// Four positions of one channel.  QUADS: rows lie on the 4-element grid.  Otherwise a row starts at
+// any element, and the compiler is told so: the target reads and writes 8 or 16 bytes at any address.
+template <typename T, bool QUADS> struct Quad {
+    typedef T Regs __attribute__((ext_vector_type(4)));
+    typedef T Memory __attribute__((ext_vector_type(4), aligned(QUADS ? 4 * sizeof(T) : sizeof(T))));
+    static __device__ __forceinline__ Regs load(const T *p) { return __builtin_nontemporal_load((const FQ_GLOBAL Memory *)p); }
+    static __device__ __forceinline__ void store(T *p, Regs v) { __builtin_nontemporal_store(v, (FQ_GLOBAL Memory *)p); }
+};
 
-    const unsigned lane = threadIdx.x % L, row = threadIdx.x / L;
-    const unsigned tile = blockIdx.x;
+// One step of adding the rows of a wavefront: afterwards a + b is, in the lanes of the even rows, the sum of
+// a over two rows, and in those of the odd rows the sum of b (rows of 32 lanes or of 16).  Two values and
+// two rows become one value per lane for two instructions per 32 bits and one addition.
+__device__ __forceinline__ void swap_halves(double &a, double &b, bool rows_of_32)
+{
+    unsigned long long ua = __builtin_bit_cast(unsigned long long, a), ub = __builtin_bit_cast(unsigned long long, b);
+    unsigned al = (unsigned)ua, ah = (unsigned)(ua >> 32), bl = (unsigned)ub, bh = (unsigned)(ub >> 32);
+    if (rows_of_32) {
+        const auto l = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+        al = l[0]; bl = l[1]; ah = h[0]; bh = h[1];
+    } else {
+        const auto l = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+        al = l[0]; bl = l[1]; ah = h[0]; bh = h[1];
+    }
+    a = __builtin_bit_cast(double, ((unsigned long long)ah << 32) | al);
+    b = __builtin_bit_cast(double, ((unsigned long long)bh << 32) | bl);
+}
+
+constexpr int kStats = 3 * kFusedVec;            // per lane: a.b, a.a, b.b of four positions
+
+// The three results out of the tiles' sums, by one wavefront, in the kernel that makes them (at most
+// kGatherTiles tiles).  A tile's record is {cos, cos ^ N, sq, sq ^ N} with a number N of this call's own: the
+// workspace may hold anything, and a record that does not fit together with N has not arrived.
+// The protocol is that of the backward's sums (kPollRounds rounds, then a flag, here N, and the tile that
+// arrives last finishes; whoever claims the call puts ~N into the flag); records are invalid again
+// afterwards, because a graph replays N.
+constexpr unsigned kGatherTiles = 256;
+constexpr unsigned kPollRounds = 32;
+
+__device__ __forceinline__ unsigned long long bits_of(double v) { return __builtin_bit_cast(unsigned long long, v); }
+__device__ __forceinline__ void wait_stores_acknowledged() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+__device__ __forceinline__ bool gather_tiles(const DistillArgs &k, double &sc, double &ss)
+{
+    const unsigned lane = threadIdx.x & 63;
+    constexpr unsigned kEach = kGatherTiles / 64;
+    unsigned long long w[kEach][4];
+#pragma unroll
+    for (unsigned i = 0; i < kEach; ++i) {
+        const unsigned tile = lane + 64 * i;
+        if (tile < k.tiles) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                w[i][j] = __hip_atomic_load(k.records + (size_t)tile * 4 + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    bool here = true;
+    sc = ss = 0.0;
+#pragma unroll
+    for (unsigned i = 0; i < kEach; ++i) {
+        if (lane + 64 * i < k.tiles) {
+            here = here && (w[i][0] ^ w[i][1]) == k.nonce && (w[i][2] ^ w[i][3]) == k.nonce;
+            sc += __builtin_bit_cast(double, w[i][0]);
+            ss += __builtin_bit_cast(double, w[i][2]);
+        }
+    }
+    sc = wave_sum(sc);
+    ss = wave_sum(ss);
+    return __builtin_amdgcn_ballot_w64(!here) == 0ull;
+}
+
+__device__ __forceinline__ void write_results(const DistillArgs &k, double sc, double ss)
+{
+    const double mse = ss * k.inv_ncm, cosim = sc * k.inv_nm;
+    st_global(k.out + 0, mse);
+    st_global(k.out + 1, cosim);
+    st_global(k.out + 2, mse + k.lambda * (1.0 - cosim));
+}
+
+__device__ __forceinline__ void finish_gathered(const DistillArgs &k, double sc, double ss)
+{
+    const unsigned lane = threadIdx.x & 63;
+    if (lane == kSumLane) write_results(k, sc, ss);
+    for (unsigned tile = lane; tile < k.tiles; tile += 64) {
+        __hip_atomic_store(k.records + (size_t)tile * 4, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(k.records + (size_t)tile * 4 + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+__device__ __forceinline__ void finish_if_complete(const DistillArgs &k, unsigned long long *flag)
+{
+    double sc, ss;
+    if (!gather_tiles(k, sc, ss)) return;
+    unsigned won = 0u;
+    if ((threadIdx.x & 63) == 0) {
+        unsigned long long expected = k.nonce;
+        won = __hip_atomic_compare_exchange_strong(flag, &expected, ~k.nonce, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT) ? 1u : 0u;
+    }
+    if (!__builtin_amdgcn_readfirstlane((int)won)) return;
+    finish_gathered(k, sc, ss);
+    if ((threadIdx.x & 63) == 0) __hip_atomic_store(flag, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One wavefront of every block, when its own work is done; the block's record is on its way.
+__device__ __forceinline__ void gather_or_leave(const DistillArgs &k)
+{
+    unsigned long long *flag = k.records + (size_t)k.tiles * 4;
+    if (blockIdx.x + 1u != k.tiles) {
+        wait_stores_acknowledged();
+        const unsigned long long f = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__builtin_expect(f == k.nonce, 0)) finish_if_complete(k, flag);
+        return;
+    }
+    double sc, ss;
+    for (unsigned round = 0; round < k.poll_rounds; ++round) {
+        asm volatile("" ::: "memory");
+        if (gather_tiles(k, sc, ss)) {
+            finish_gathered(k, sc, ss);
+            return;
+        }
+    }
+    wait_stores_acknowledged();
+    if ((threadIdx.x & 63) == 0) __hip_atomic_store(flag, k.nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    wait_stores_acknowledged();
+    finish_if_complete(k, flag);
+}
+
+// Blocks go to the eight XCDs in turn; this gives each XCD a run of neighbouring tiles.  One to one.
+// Only for rows off the grid, us without / with: 4x256x9601 FP32 40.2 / 35.3, 8x250x5001 FP16 26.6 / 21.9; on
+// the grid neighbours share no line, and it loses: 15x128x19200 FP16 44.3 / 47.4.
+__device__ __forceinline__ unsigned tile_of_block(unsigned block, unsigned tiles)
+{
+    constexpr unsigned kXcds = 8;
+    const unsigned each = tiles / kXcds, more = tiles % kXcds, xcd = block % kXcds;
+    return xcd * each + (xcd < more ? xcd : more) + block / kXcds;
+}
+
+template <typename T, int THREADS, int KCH, bool QUADS, bool WANT_GRAD>
+__global__ __launch_bounds__(THREADS, 4) void distill_fused_kernel(DistillArgs k)
+{
+    typedef FusedShape<T, THREADS> Shape;
+    constexpr int V = kFusedVec, L = Shape::L, P = Shape::P, R = Shape::R, W = THREADS / 64, S = 64 / L;
+    constexpr int HELD = S >= 4 ? kStats / 4 : kStats / 2;      // sums a lane is left with
+    typedef Quad<T, QUADS> Q;
+    typedef typename Q::Regs Regs;
+    __shared__ double red[W * 3 * P];             // per wavefront, statistic and position
+    __shared__ double red_sq[W];                  // per wavefront: (a-b)^2
+    __shared__ double coefs[P * 2];               // per position: the two gradient coefficients
+    __shared__ double cosines[P];
+
+    const unsigned lane = threadIdx.x % L, row = threadIdx.x / L, wave = threadIdx.x >> 6;
+    const unsigned tile = QUADS ? blockIdx.x : tile_of_block(blockIdx.x, k.tiles);
     const unsigned n = tile / k.tiles_per_n, tn = tile - n * k.tiles_per_n;
     const long long tile_m = (long long)tn * P;
     long long m0 = tile_m + (long long)lane * V;
-    const bool lane_valid = m0 < k.M;
-    if (!lane_valid) m0 = k.M - V;                // lanes past the end re-read the last quad; results dropped
+    // positions of this lane that exist; QUADS: four or none (none: re-read the last quad, results dropped)
+    const int valid = m0 >= k.M ? 0 : (m0 + V <= k.M ? V : (int)(k.M - m0));
+    if (QUADS && !valid) m0 = k.M - V;
+    const bool whole = QUADS || valid == V;
     const long long base = (long long)n * k.C * k.M + m0;
     const T *a = (const T *)k.a + base;
     const T *b = (const T *)k.b + base;
 
-    VT ra[KCH], rb[KCH];
+    Regs ra[KCH], rb[KCH];
+    if (whole) {
 #pragma unroll
-    for (int j = 0; j < KCH; ++j) {
-        unsigned c = row + (unsigned)j * R;
-        c = c < k.C ? c : k.C - 1;                // rows past the last channel re-read it; results dropped
-        ra[j] = ld_stream((const VT *)(a + (long long)c * k.M));
-        rb[j] = ld_stream((const VT *)(b + (long long)c * k.M));
+        for (int j = 0; j < KCH; ++j) {
+            unsigned c = row + (unsigned)j * R;
+            c = c < k.C ? c : k.C - 1;            // rows past the last channel re-read it; results dropped
+            ra[j] = Q::load(a + (long long)c * k.M);
+            rb[j] = Q::load(b + (long long)c * k.M);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < KCH; ++j) {
+            unsigned c = row + (unsigned)j * R;
+            c = c < k.C ? c : k.C - 1;
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                ra[j][e] = e < valid ? ld_global(a + (long long)c * k.M + e) : (T)0.0f;
+                rb[j][e] = e < valid ? ld_global(b + (long long)c * k.M + e) : (T)0.0f;
+            }
+        }
     }
 
-    double acc[V * 4];
+    // acc[e * 3 + s]: statistic s of position e
+    double acc[kStats], sq = 0.0;
 #pragma unroll
-    for (int i = 0; i < V * 4; ++i) acc[i] = 0.0;
+    for (int i = 0; i < kStats; ++i) acc[i] = 0.0;
 #pragma unroll
     for (int j = 0; j < KCH; ++j) {
         if (row + (unsigned)j * R < k.C) {
@@ -435,83 +607,119 @@ __global__ __launch_bounds__(kFusedThreads, 4) void distill_fused_kernel(Distill
                 const double x = (double)(float)ra[j][e];
                 const double y = (double)(float)rb[j][e];
                 const double d = x - y;
-                acc[e * 4 + 0] = __builtin_fma(x, y, acc[e * 4 + 0]);
-                acc[e * 4 + 1] = __builtin_fma(x, x, acc[e * 4 + 1]);
-                acc[e * 4 + 2] = __builtin_fma(y, y, acc[e * 4 + 2]);
-                acc[e * 4 + 3] = __builtin_fma(d, d, acc[e * 4 + 3]);
+                acc[e * 3 + 0] = __builtin_fma(x, y, acc[e * 3 + 0]);
+                acc[e * 3 + 1] = __builtin_fma(x, x, acc[e * 3 + 1]);
+                acc[e * 3 + 2] = __builtin_fma(y, y, acc[e * 3 + 2]);
+                sq = __builtin_fma(d, d, sq);
             }
         }
     }
+    if (QUADS && !valid) sq = 0.0;                // (a re-read quad; without QUADS absent positions hold zeros)
 
-    // Sum over the R rows, in row order, eight of the sixteen values at a time.
+    // Over the rows of the wavefront, then over the wavefronts.
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) red[i * kFusedThreads + threadIdx.x] = acc[half * 8 + i];
-        __syncthreads();
-        if (threadIdx.x < 8 * L) {
-            const unsigned i = threadIdx.x / L, l = threadIdx.x % L;
-            double sum = 0.0;
-            for (unsigned r = 0; r < (unsigned)R; ++r) sum += red[i * kFusedThreads + r * L + l];
-            const unsigned value = half * 8 + i;                 // = e * 4 + which sum
-            stat[(l * V + value / 4) * 4 + value % 4] = sum;
-        }
-        __syncthreads();
+    for (int i = 0; i < kStats / 2; ++i) {
+        swap_halves(acc[i], acc[i + kStats / 2], true);
+        acc[i] += acc[i + kStats / 2];
     }
-
-    // One thread per position (all in the first wavefront): cos, the gradient's coefficients, and
-    // the tile's sums of cos and of the squared error.
-    if (threadIdx.x < 64) {
-        double cos_sum = 0.0, sq_sum = 0.0;
-        const unsigned pp = threadIdx.x;
-        if (pp < (unsigned)P && tile_m + pp < k.M) {
-            const double dot = stat[pp * 4 + 0], na = stat[pp * 4 + 1], nb = stat[pp * 4 + 2];
-            const double ra_ = sqrt(na), rb_ = sqrt(nb);
-            // a NaN norm stays NaN, so a non-finite input poisons its whole position visibly
-            const double ca = ra_ < k.eps ? k.eps : ra_, cb = rb_ < k.eps ? k.eps : rb_;
-            const double inv = 1.0 / (ca * cb);
-            const double cosp = dot / (ca * cb);
-            const double self = ra_ > k.eps ? cosp / na : 0.0;
-            coefs[pp * 2 + 0] = k.k2u * inv;
-            coefs[pp * 2 + 1] = k.k2u * self;
-            cos_sum = cosp;
-            sq_sum = stat[pp * 4 + 3];
+    unsigned e0 = (threadIdx.x & 32) ? 2 : 0;     // the first of the positions whose sums this lane is left with
+    if (S >= 4) {
+#pragma unroll
+        for (int i = 0; i < kStats / 4; ++i) {
+            swap_halves(acc[i], acc[i + kStats / 4], false);
+            acc[i] += acc[i + kStats / 4];
         }
+        e0 += (threadIdx.x & 16) ? 1 : 0;
+    }
+    if (S == 8) {                                 // rows of eight lanes: add the other one of the sixteen
+#pragma unroll
+        for (int i = 0; i < kStats / 4; ++i) acc[i] += dpp_move<0x128, 0xf>(acc[i]);      // row_ror:8
+    }
+    if (S < 8 || (threadIdx.x & 8) == 0) {
+#pragma unroll
+        for (int i = 0; i < HELD; ++i) red[(wave * 3 + i % 3) * P + lane * V + e0 + i / 3] = acc[i];
+    }
+    sq = wave_sum(sq);
+    if ((threadIdx.x & 63) == kSumLane) red_sq[wave] = sq;
+    __syncthreads();
+
+    // One thread per position: cos and the gradient's coefficients.
+    if (threadIdx.x < (unsigned)P) {
+        const unsigned pp = threadIdx.x;
+        double dot = 0.0, na = 0.0, nb = 0.0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            dot += red[(w * 3 + 0) * P + pp];
+            na += red[(w * 3 + 1) * P + pp];
+            nb += red[(w * 3 + 2) * P + pp];
+        }
+        const double ra_ = sqrt(na), rb_ = sqrt(nb);
+        // a NaN norm stays NaN, so a non-finite input poisons its whole position visibly
+        const double ca = ra_ < k.eps ? k.eps : ra_, cb = rb_ < k.eps ? k.eps : rb_;
+        const double inv = 1.0 / (ca * cb);
+        const double cosp = dot / (ca * cb);
+        const double self = ra_ > k.eps ? cosp / na : 0.0;
+        coefs[pp * 2 + 0] = k.k2u * inv;
+        coefs[pp * 2 + 1] = k.k2u * self;
+        cosines[pp] = tile_m + pp < k.M ? cosp : 0.0;
+    }
+    __syncthreads();
+
+    if (wave == 0) {                              // the tile's sums of cos and of the squared error
+        double cos_sum = threadIdx.x < (unsigned)P ? cosines[threadIdx.x] : 0.0;
+        if (P > 64) cos_sum += cosines[64 + threadIdx.x];
+        double sq_sum = threadIdx.x < (unsigned)W ? red_sq[threadIdx.x] : 0.0;
         cos_sum = wave_sum(cos_sum);
         sq_sum = wave_sum(sq_sum);
         if (threadIdx.x == kSumLane) {
-            double2v o = {cos_sum, sq_sum};
-            st_global((double2v *)k.blocksum + tile, o);
-        }
-    }
-    if (!WANT_GRAD) return;
-    __syncthreads();
-
-    if (!lane_valid) return;
-    double cb[V], ca[V];
+            if (k.nonce) {
+                unsigned long long *r = k.records + (size_t)tile * 4;
+                const unsigned long long w[4] = {bits_of(cos_sum), bits_of(cos_sum) ^ k.nonce, bits_of(sq_sum),
+                                                 bits_of(sq_sum) ^ k.nonce};
 #pragma unroll
-    for (int e = 0; e < V; ++e) {
-        cb[e] = coefs[(lane * V + e) * 2 + 0];
-        ca[e] = coefs[(lane * V + e) * 2 + 1];
-    }
-    T *ga = (T *)k.ga + base;
-#pragma unroll
-    for (int j = 0; j < KCH; ++j) {
-        const unsigned c = row + (unsigned)j * R;
-        if (c < k.C) {
-            VT o;
-#pragma unroll
-            for (int e = 0; e < V; ++e) {
-                const double x = (double)(float)ra[j][e];
-                const double y = (double)(float)rb[j][e];
-                double g = k.k1u * (x - y);
-                g = __builtin_fma(-cb[e], y, g);
-                g = __builtin_fma(ca[e], x, g);
-                o[e] = (T)(float)g;
+                for (int j = 0; j < 4; ++j)
+                    __hip_atomic_store(r + j, w[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+                double2v o = {cos_sum, sq_sum};
+                st_global((double2v *)k.blocksum + tile, o);
             }
-            st_stream((VT *)(ga + (long long)c * k.M), o);
         }
     }
+
+    if (WANT_GRAD && valid) {
+        double cb[V], ca[V];
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            cb[e] = coefs[(lane * V + e) * 2 + 0];
+            ca[e] = coefs[(lane * V + e) * 2 + 1];
+        }
+        T *ga = (T *)k.ga + base;
+#pragma unroll
+        for (int j = 0; j < KCH; ++j) {
+            const unsigned c = row + (unsigned)j * R;
+            if (c < k.C) {
+                Regs o;
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    const double x = (double)(float)ra[j][e];
+                    const double y = (double)(float)rb[j][e];
+                    double g = k.k1u * (x - y);
+                    g = __builtin_fma(-cb[e], y, g);
+                    g = __builtin_fma(ca[e], x, g);
+                    o[e] = (T)(float)g;
+                }
+                T *to = ga + (long long)c * k.M;
+                if (whole) {
+                    Q::store(to, o);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < V; ++e)
+                        if (e < valid) st_global(to + e, (T)o[e]);
+                }
+            }
+        }
+    }
+    if (k.nonce && wave == 0) gather_or_leave(k);
 }
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -519,25 +727,31 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 struct Plan {
     int vec;                 // elements per lane
     int fused_kch;           // > 0: the fused kernel with this many channels per lane; 0: two kernels
+    bool quads, wide;        // fused: see Quad; wide tiles
+    bool one_launch;         // fused: the kernel adds its tiles' sums itself
     unsigned tiles_per_n, tiles, groups, per_group, grad_groups, grad_per_group;
     size_t stats_lds, off_blocksum, bytes;
 };
 
 // Channels per lane the fused kernel would need for this pair, rounded up to a width it is built
-// for; 0 if the pair does not qualify (positions not in whole quads, a pointer off the quad's
-// alignment, or more channels than a lane's registers hold).
+// for; 0 if there are more channels than a lane's registers hold.
 int fused_channels_per_lane(const fq_distill *d)
 {
-    const size_t esz = d->dtype == FQ_F16 ? 2 : 4;
-    const uintptr_t addr_bits = (uintptr_t)d->student | (uintptr_t)d->teacher | (uintptr_t)d->gstudent;
-    if (d->inner % kFusedVec || addr_bits % (kFusedVec * esz)) return 0;
-    const long long rows = d->dtype == FQ_F16 ? FusedShape<_Float16>::R : FusedShape<float>::R;
+    const long long rows = d->dtype == FQ_F16 ? FusedShape<_Float16, kNarrowThreads>::R : FusedShape<float, kNarrowThreads>::R;
     const long long need = (d->channels + rows - 1) / rows;
     const long long cap = d->dtype == FQ_F16 ? kFusedMaxKch : kFusedMaxKch / 2;
     if (need > cap) return 0;
     for (int kch : {2, 4, 6, 8, 12, 16})
         if (kch >= need) return kch;
     return 0;
+}
+
+// Whether all rows of the pair lie on the 4-element grid.
+bool on_quads(const fq_distill *d)
+{
+    const size_t esz = d->dtype == FQ_F16 ? 2 : 4;
+    const uintptr_t addr_bits = (uintptr_t)d->student | (uintptr_t)d->teacher | (uintptr_t)d->gstudent;
+    return d->inner % kFusedVec == 0 && addr_bits % (kFusedVec * esz) == 0;
 }
 
 fq_status make_plan(const fq_distill *d, Plan &pl)
@@ -570,16 +784,27 @@ fq_status make_plan(const fq_distill *d, Plan &pl)
             }
         }
     }
+    pl = Plan{};
     if (empty) {
-        pl = Plan{};
         pl.vec = 1;
         pl.bytes = 256;
         return FQ_OK;
     }
     pl.fused_kch = fused_channels_per_lane(d);
     if (pl.fused_kch) {
-        const long long per_tile = d->dtype == FQ_F16 ? FusedShape<_Float16>::P : FusedShape<float>::P;
-        const long long tpn = (d->inner + per_tile - 1) / per_tile;
+        pl.quads = on_quads(d);
+        const bool half = d->dtype == FQ_F16;
+        const long long narrow = half ? FusedShape<_Float16, kNarrowThreads>::P : FusedShape<float, kNarrowThreads>::P;
+        const long long narrow_tpn = (d->inner + narrow - 1) / narrow, wide_tpn = (d->inner + 2 * narrow - 1) / (2 * narrow);
+        // Wide tiles where that leaves few enough of them for one launch (1x384x19200 FP16: 15.9 -> 12.6 us),
+        // and for FP32, whose wide rows are worth more than the finer grain (us, narrow / wide: 4x128x19200 28.3 /
+        // 25.2, 3x384x19200 61 / 55, 4x256x9601 53 / 40; 8x256x4800 23.9 / 25.7).  A wide FP16 tile fills a
+        // compute unit by itself, with nothing to stream while it reduces (15x256x19200 85 / 95, 8x250x5001 26.6 / 29;
+        // 4x128x9601 15.1 / 14.4).
+        const bool many = narrow_tpn * d->n > (long long)kGatherTiles;
+        pl.wide = many && (!half || wide_tpn * d->n <= (long long)kGatherTiles);
+        const long long tpn = pl.wide ? wide_tpn : narrow_tpn;
+        pl.one_launch = tpn * d->n <= (long long)kGatherTiles;
         if (tpn * d->n > 0x3fffffffLL) return FQ_ERR_SHAPE;
         pl.vec = kFusedVec;
         pl.tiles_per_n = (unsigned)tpn;
@@ -587,7 +812,8 @@ fq_status make_plan(const fq_distill *d, Plan &pl)
         pl.groups = pl.per_group = pl.grad_groups = pl.grad_per_group = 0;
         pl.stats_lds = 0;
         pl.off_blocksum = 0;                       // no per-position coefficients leave the block
-        pl.bytes = align256((size_t)pl.tiles * 2 * sizeof(double));
+        pl.bytes = pl.one_launch ? align256(((size_t)pl.tiles * 4 + 1) * sizeof(unsigned long long))
+                           : align256((size_t)pl.tiles * 2 * sizeof(double));
         if (pl.bytes < 256) pl.bytes = 256;
         return FQ_OK;
     }
@@ -656,13 +882,24 @@ fq_status launch(const DistillArgs &k, const Plan &pl, bool want_grad, hipStream
     return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_LAUNCH;
 }
 
+template <typename T, int KCH, bool QUADS>
+fq_status launch_fused(const DistillArgs &k, const Plan &pl, bool want_grad, hipStream_t st)
+{
+    if (pl.wide) {
+        if (want_grad) distill_fused_kernel<T, kWideThreads, KCH, QUADS, true><<<pl.tiles, kWideThreads, 0, st>>>(k);
+        else distill_fused_kernel<T, kWideThreads, KCH, QUADS, false><<<pl.tiles, kWideThreads, 0, st>>>(k);
+    } else {
+        if (want_grad) distill_fused_kernel<T, kNarrowThreads, KCH, QUADS, true><<<pl.tiles, kNarrowThreads, 0, st>>>(k);
+        else distill_fused_kernel<T, kNarrowThreads, KCH, QUADS, false><<<pl.tiles, kNarrowThreads, 0, st>>>(k);
+    }
+    if (!pl.one_launch) distill_finish_kernel<<<1, 1024, 0, st>>>(k);
+    return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_LAUNCH;
+}
+
 template <typename T, int KCH>
 fq_status launch_fused(const DistillArgs &k, const Plan &pl, bool want_grad, hipStream_t st)
 {
-    if (want_grad) distill_fused_kernel<T, KCH, true><<<pl.tiles, kFusedThreads, 0, st>>>(k);
-    else distill_fused_kernel<T, KCH, false><<<pl.tiles, kFusedThreads, 0, st>>>(k);
-    distill_finish_kernel<<<1, 1024, 0, st>>>(k);
-    return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_LAUNCH;
+    return pl.quads ? launch_fused<T, KCH, true>(k, pl, want_grad, st) : launch_fused<T, KCH, false>(k, pl, want_grad, st);
 }
 
 template <typename T>
@@ -680,6 +917,22 @@ fq_status launch_fused_width(const DistillArgs &k, const Plan &pl, bool want_gra
     return FQ_ERR_SHAPE;                           // not reached: make_plan offers only the widths above
 }
 
+// A number that no other call of this process has, and that memory does not hold by chance: a counter from
+// an arbitrary start through a mixing function that is one-to-one (splitmix64's).
+unsigned long long next_nonce()
+{
+    static std::atomic<unsigned long long> counter{
+        (unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9e3779b97f4a7c15ull ^
+        (unsigned long long)(uintptr_t)&counter};
+    for (;;) {
+        unsigned long long z = counter.fetch_add(0x9e3779b97f4a7c15ull, std::memory_order_relaxed);
+        z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+        z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+        z ^= z >> 31;
+        if (z != 0ull && ~z != 0ull) return z;     // 0 is an empty flag
+    }
+}
+
 }  // namespace
 }  // namespace fq
 
@@ -690,7 +943,7 @@ int fq_distill_reads_of_pair(const fq_distill *d)
     fq::Plan pl;
     if (fq::make_plan(d, pl) != FQ_OK) return 0;
     if (d->n * d->inner == 0 || d->channels == 0) return 0;
-    return pl.fused_kch ? 1 : (d->gstudent ? 2 : 1);
+    return pl.fused_kch && pl.quads ? 1 : (d->gstudent ? 2 : 1);
 }
 
 size_t fq_distill_workspace_bytes(const fq_distill *d)
@@ -736,6 +989,9 @@ fq_status fq_distill_loss(const fq_distill *d, void *workspace, size_t ws_bytes,
     k.inv_ncm = 1.0 / ncm;
     k.inv_nm = 1.0 / nm;
     const bool grad = d->gstudent != nullptr;
+    k.records = (unsigned long long *)workspace;
+    k.nonce = pl.one_launch ? next_nonce() : 0ull;
+    k.poll_rounds = kPollRounds;
     if (pl.fused_kch) {
         k.coef = nullptr;
         return d->dtype == FQ_F16 ? launch_fused_width<_Float16>(k, pl, grad, st)
