@@ -203,8 +203,8 @@ fq_status fq_backward_static(const fq_tensor *t, void *hip_stream);
  * workspace on `stream` and may be reused as soon as the call returns.  n = 0 is a no-op.
  * FQ_FLAG_TWO_PASS on any tensor selects the two-launch backward for the whole list.
  *
- * Host-side behaviour of the table copy (also in fq_plan_create and, when the step changes, in
- * fq_plan_run_adam): the table is staged in one of eight pinned host buffers that the library
+ * Host-side behaviour of the table copy (also in fq_plan_create and, when the step changes and the
+ * tensors' betas differ, in fq_plan_run_adam): the table is staged in one of eight pinned host buffers that the library
  * keeps for the life of the process.  A buffer is allocated (hipHostMalloc) the first time it is
  * used or when a larger table comes along, and a call that finds its buffer still being read by a
  * copy enqueued eight such calls earlier waits on the host for that one copy to finish
@@ -230,10 +230,11 @@ fq_status fq_multi_tensor(const fq_tensor *ts, int n, int mode,
  * change freely between runs.  fq_plan_destroy frees the host-side plan only (NULL is allowed).
  *
  * Backward plans whose descriptors carry a fused Adam step: fq_plan_run repeats the step number
- * the plan was created with; fq_plan_run_adam(plan, step, stream) first brings the bias
- * corrections 1-beta^step of every such tensor up to date (one small asynchronous copy of the
- * table on `stream`, skipped when `step` is the one already in place), then launches.  It is the
- * call for a training loop: step = 1, 2, 3, ...  (It does host work beyond the launch, so capture
+ * the plan was created with; fq_plan_run_adam(plan, step, stream) brings the bias corrections
+ * 1-beta^step of every such tensor up to date, also for the fq_plan_run that follow, and launches.
+ * Where all tensors have the same betas the launch itself does that; otherwise it is one small
+ * asynchronous copy of the table on `stream` in front of it (skipped when `step` is the one
+ * already in place).  It is the call for a training loop: step = 1, 2, 3, ...  (It does host work beyond the launch, so capture
  * fq_plan_run, not this, in a graph.)
  */
 typedef struct fq_plan fq_plan;

@@ -211,7 +211,7 @@ fq_status make_layout(const fq_tensor *ts, int n, int mode, Layout &L)
             L.slots += ts[i].channels * (1 + (long long)p.sub);
         }
     }
-    L.table_bytes = round_up((size_t)n * sizeof(DevTensor), kAlign);
+    L.table_bytes = round_up((size_t)n * kTableEntryBytes, kAlign);
     L.partial_off = L.table_bytes;
     L.counter_off = L.partial_off;
     L.total = L.table_bytes;
@@ -228,6 +228,17 @@ fq_status make_layout(const fq_tensor *ts, int n, int mode, Layout &L)
 struct Cursor {
     long long block = 0, chan = 0, slot = 0, unit = 0;
 };
+
+Divisor divisor(unsigned d)
+{
+    Divisor r = {0u, 0, 0};
+    if (d == 0) return r;                         // an empty tensor: never divided by
+    const unsigned s = d > 1 ? 32u - (unsigned)__builtin_clz(d - 1) : 0u;
+    r.multiplier = (unsigned)((((1ull << s) - d) << 32) / d + 1ull);
+    r.shift1 = (unsigned short)(s < 1 ? s : 1);
+    r.shift2 = (unsigned short)(s > 0 ? s - 1 : 0);
+    return r;
+}
 
 // Device descriptor of one tensor; `partials` / `slots` are the launch's arrays of partial sums and
 // of 64-bit slots (nullptr: forward, nothing is reduced).
@@ -248,9 +259,11 @@ DevTensor describe(const fq_tensor &t, const Plan &p, int mode, double *partials
     d.chunk = p.chunk;
     d.block_begin = (unsigned)at.block;
     d.chan_begin = (unsigned)at.chan;
-    d.sub = p.sub;
-    d.wave_units = p.waves ? 1u : 0u;
-    d.dtype = t.dtype;
+    d.sub = (unsigned char)p.sub;
+    d.wave_units = p.waves ? 1 : 0;
+    d.dtype = (unsigned char)t.dtype;
+    const unsigned vecs = p.chunk / (kVecBytes / (t.dtype == FQ_F16 ? 2 : 4)), lanes = p.waves ? 64 : kBlock;
+    d.rows = (unsigned char)((vecs + lanes - 1) / lanes);
     d.lo = (float)t.qmin;
     d.hi = (float)t.qmax;
     d.eps = t.eps; d.s_min = t.s_min; d.s_max = t.s_max;
@@ -268,12 +281,20 @@ DevTensor describe(const fq_tensor &t, const Plan &p, int mode, double *partials
     return d;
 }
 
+// What a kernel needs to find a chunk by its linear index.
+void set_divisors(DevTensor &d)
+{
+    d.by_cps = divisor(d.cps);
+    d.by_channels = divisor(d.channels);
+}
+
 // A tensor launched on its own gets a three-dimensional grid (chunks per slab, channels, outer)
 // unless its slabs go one to a wavefront or an extent exceeds the grid's y/z limit.
 void set_grid_shape(DevTensor &d)
 {
     d.grid3 = (!d.wave_units && d.cps > 0 && d.channels > 0 && d.outer > 0 && d.channels <= 65535u &&
-               d.outer <= 65535u) ? 1u : 0u;
+               d.outer <= 65535u) ? 1 : 0;
+    if (!d.grid3) set_divisors(d);
 }
 
 // Fill the device descriptors; partial/counter pointers are carved out of the workspace.
@@ -288,6 +309,7 @@ void build_table(const fq_tensor *ts, int n, int mode, const Layout &L, char *wo
         const fq_tensor &t = ts[i];
         const Plan &p = L.plans[(size_t)i];
         out[(size_t)i] = describe(t, p, mode, partials, slots, at);
+        set_divisors(out[(size_t)i]);
         at.block += p.blocks;
         at.unit += p.units;
         at.chan += t.channels;
@@ -382,8 +404,13 @@ fq_status prepare(const fq_tensor *ts, int n, int mode, bool use_table, void *wo
     build_table(ts, n, mode, L, (char *)workspace, table);
     if (use_table) {
         P.args.table = (const DevTensor *)workspace;
-        if (copy_table_async(workspace, table.data(), (size_t)n * sizeof(DevTensor), stream) != 0)
-            return FQ_ERR_LAUNCH;
+        // the descriptors, and behind them their first blocks packed
+        std::vector<char> image((size_t)n * kTableEntryBytes);
+        std::memcpy(image.data(), table.data(), (size_t)n * sizeof(DevTensor));
+        for (int i = 0; i < n; ++i)
+            std::memcpy(image.data() + (size_t)n * sizeof(DevTensor) + (size_t)i * sizeof(unsigned),
+                        &table[(size_t)i].block_begin, sizeof(unsigned));
+        if (copy_table_async(workspace, image.data(), image.size(), stream) != 0) return FQ_ERR_LAUNCH;
     } else {
         P.args.one = table[0];
         set_grid_shape(P.args.one);
@@ -396,9 +423,14 @@ fq_status prepare(const fq_tensor *ts, int n, int mode, bool use_table, void *wo
     return FQ_OK;
 }
 
-fq_status launch_prepared(const Prepared &P, void *stream)
+fq_status launch_prepared(const Prepared &P, void *stream, const AdamBias *bias = nullptr)
 {
     if (P.args.n == 0) return FQ_OK;
+    if (bias) {                                   // (a backward table without a second launch)
+        KArgs args = P.args;
+        args.bias = *bias;
+        return launch_backward(args, (unsigned)P.blocks, true, stream) != 0 ? FQ_ERR_LAUNCH : FQ_OK;
+    }
     if (P.mode == FQ_MODE_FORWARD) {
         if (P.blocks > 0 && launch_forward(P.args, (unsigned)P.blocks, P.emit_q, stream) != 0) return FQ_ERR_LAUNCH;
         // tensors without elements never reach a block: write the scales of all channels in a
@@ -621,18 +653,36 @@ fq_status fq_plan_run_adam(fq_plan *plan, int64_t step, void *hip_stream)
     if (step < 1) return FQ_ERR_OPTIMIZER;
     // (no container grows here: the table and the per-tensor vectors keep their size)
     if (step != plan->step) {
-        bool any = false;
+        // The corrections of all tensors are the same two numbers where their betas are: they ride along
+        // with the launch, which also puts them into the table on the device.  (A copy of the table in front
+        // of the launch, needed otherwise, costs a 22-tensor list 5 us of host time and as much on the stream.)
         std::vector<fq::DevTensor> &table = plan->prepared.table;
-        for (size_t i = 0; i < table.size(); ++i) {
+        const size_t n = table.size();
+        size_t first = n;
+        bool same = true;
+        for (size_t i = 0; i < n; ++i) {
             if (!plan->has_adam[i]) continue;
-            any = true;
-            table[i].adam_bc1 = (float)(1.0 - std::pow(plan->beta1[i], (double)step));
-            table[i].adam_bc2 = (float)(1.0 - std::pow(plan->beta2[i], (double)step));
+            if (first == n) first = i;
+            same = same && plan->beta1[i] == plan->beta1[first] && plan->beta2[i] == plan->beta2[first];
+            if (i == first || plan->beta1[i] != plan->beta1[first] || plan->beta2[i] != plan->beta2[first]) {
+                table[i].adam_bc1 = (float)(1.0 - std::pow(plan->beta1[i], (double)step));
+                table[i].adam_bc2 = (float)(1.0 - std::pow(plan->beta2[i], (double)step));
+            } else {
+                table[i].adam_bc1 = table[first].adam_bc1;
+                table[i].adam_bc2 = table[first].adam_bc2;
+            }
         }
-        if (any && fq::copy_table_async(plan->workspace, table.data(), table.size() * sizeof(fq::DevTensor),
-                                        hip_stream) != 0)
-            return FQ_ERR_LAUNCH;
         plan->step = step;
+        if (first < n && same && !plan->prepared.two_pass && plan->prepared.blocks > 0) {
+            const fq::AdamBias bias = {table[first].adam_bc1, table[first].adam_bc2, 1u};
+            const fq_status st = fq::launch_prepared(plan->prepared, hip_stream, &bias);
+            if (st != FQ_OK) plan->step = 0;     // the table on the device may be behind
+            return st;
+        }
+        if (first < n && fq::copy_table_async(plan->workspace, table.data(), n * sizeof(fq::DevTensor), hip_stream) != 0) {
+            plan->step = 0;
+            return FQ_ERR_LAUNCH;
+        }
     }
     return fq::launch_prepared(plan->prepared, hip_stream);
 }

@@ -29,6 +29,20 @@ constexpr size_t kStaticScratchBytes = 1u << 20;                 // per GPU
 constexpr size_t kStaticSlotBytes = 256u << 10;                  // 32768 64-bit slots
 constexpr size_t kStaticPartialBytes = kStaticScratchBytes - kStaticSlotBytes;   // 98304 partial sums
 
+// Division of 32-bit numbers by one d > 0 that the host knows (Granlund and Montgomery 1994, Fig. 4.1), exact for
+// all n: s = ceil(log2 d), multiplier = floor(2^32 (2^s - d) / d) + 1, shift1 = min(s, 1), shift2 = max(s - 1, 0);
+// t = high half of n * multiplier; n / d = (t + ((n - t) >> shift1)) >> shift2.
+struct Divisor {
+    unsigned multiplier;
+    unsigned short shift1, shift2;
+};
+
+// Bias corrections 1 - beta^t of an Adam step that a launch brings with it (set != 0).
+struct AdamBias {
+    float bc1, bc2;
+    unsigned set;
+};
+
 // Device-side view of one tensor.  Built on the host; passed as a kernel argument for
 // single-tensor calls, or as an array in device memory for the multi-tensor launch.
 struct DevTensor {
@@ -53,12 +67,14 @@ struct DevTensor {
     unsigned chunk;            // elements per chunk, a multiple of the vector width
     unsigned block_begin;      // first block of this tensor in the grid
     unsigned chan_begin;       // first channel of this tensor in the finalize grid
-    unsigned wave_units;       // 1: slabs are short, every wavefront owns one (cps = 1, chunk = the slab);
+    Divisor by_cps, by_channels;
+    unsigned char wave_units;  // 1: slabs are short, every wavefront owns one (cps = 1, chunk = the slab);
                                // the tensor's blocks then number ceil(slabs / 4) and partial[] is per slab
-    unsigned grid3;            // 1: launched alone with a grid of (cps, channels, outer) blocks (see own_chunk)
-    unsigned sub;              // extra slots per channel after the [channels] main ones: 0, 2 (pair slots of
+    unsigned char grid3;       // 1: launched alone with a grid of (cps, channels, outer) blocks (see own_chunk)
+    unsigned char sub;         // extra slots per channel after the [channels] main ones: 0, 2 (pair slots of
                                // the exchange tree, 3 or 4 units per channel) or the unused kReserve...
-    int dtype;                 // 0 = FP16, 1 = FP32
+    unsigned char dtype;       // 0 = FP16, 1 = FP32
+    unsigned char rows;        // vectors that a lane has in a whole chunk, 1 to kChunkVecs / kBlock
     float lo, hi;              // (float)qmin, (float)qmax
     float eps, s_min, s_max;
     unsigned flags;
@@ -68,10 +84,14 @@ struct DevTensor {
     float adam_bc1, adam_bc2;      // 1 - beta1^t, 1 - beta2^t
 };
 
+constexpr size_t kTableEntryBytes = sizeof(DevTensor) + sizeof(unsigned);   // descriptor and packed first block
+
 struct KArgs {
     DevTensor one;             // used when table == nullptr
-    const DevTensor *table;    // device array of n descriptors (multi-tensor launch)
+    const DevTensor *table;    // device array of n descriptors, and behind it of their n first blocks
+                               // (multi-tensor launch)
     int n;
+    AdamBias bias;             // backward of a table
 };
 
 // Launchers; each returns the hipError_t value as int (0 = success).
