@@ -64,6 +64,12 @@ template <typename U> __device__ __forceinline__ void st_stream(U *p, U v)
     *(FQ_GLOBAL U *)p = v;
 #endif
 }
+// A load that is issued where it is written.  (The compiler moves an ordinary one down to its first use, and
+// theta's is inside the branch of the wavefront that evaluates the scale, behind the request of the rows.)
+__device__ __forceinline__ float ld_early(const float *p)
+{
+    return __hip_atomic_load((const FQ_GLOBAL float *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
 template <typename U> __device__ __forceinline__ U ld_uniform(const U *p) { return *(const FQ_CONST U *)p; }
 
 }  // namespace dev

@@ -11,9 +11,10 @@ constexpr int kVecBytes = 16;        // one 128-bit global load/store per lane
 constexpr int kChunkVecs = 1280;     // at most this many 128-bit vectors per block (20 KiB)
 constexpr int kWaveChunkVecs = kChunkVecs / (kBlock / 64);   // what one wavefront covers: 320 vectors
 constexpr int kComputeUnits = 256;   // MI355X; used by the host to balance blocks over the chip
-// Single-tensor backward launches that take the schedule made for one burst (launch_backward_shaped has
-// the figures): all blocks resident at once, and enough of them and of data.
-constexpr unsigned kBurstMostBlocks = 3 * kComputeUnits;
+// Up to this many blocks a launch has all of them resident at once (three per compute unit).
+constexpr unsigned kResidentBlocks = 3 * kComputeUnits;
+// Backward launches of at most that many blocks take the schedule made for one burst from here on
+// (launch_backward_shaped has the figures): enough blocks and enough of data.
 constexpr unsigned kBurstLeastBlocksF16 = 640, kBurstLeastBlocksF32 = 400;
 constexpr unsigned kBurstLeastVecsF16 = 900, kBurstLeastVecsF32 = 600;
 // Channels with more units than this have 16 (32) further 64-bit slots in the workspace.  No kernel uses

@@ -314,9 +314,8 @@ __device__ __forceinline__ QParams block_params(const DevTensor &d, float theta,
         bs.clip_active = sc.clip_active ? 1u : 0u;
     } else {
         __shared__ BlockScale shared_scale;
-        // (the block's linear index in the grid, whatever the grid's shape)
-        const unsigned linear = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-        if ((threadIdx.x >> 6) == (linear & (kBlock / 64 - 1))) {
+        // (the sum of the indices, not the linear index: that takes the grid's extents, one more load)
+        if ((threadIdx.x >> 6) == ((blockIdx.x + blockIdx.y + blockIdx.z) & (kBlock / 64 - 1))) {
             const Scale sc = compute_scale<NEED_SIGMOID>(theta, d.eps, d.s_min, d.s_max);
             if ((threadIdx.x & 63) == 0) {
                 shared_scale.s = sc.s;
@@ -351,7 +350,13 @@ __device__ __forceinline__ void forward_elem(T x, T *y, int8_t *q, int i, const 
 // WRITE_Y: write the dequantized tensor y.  EMIT_Q: write the int8 codes, N per lane packed into
 // one 64-bit (FP16 input) or 32-bit (FP32 input) store.  At least one of the two.
 // G: lanes that share the chunk, 0: `group`, known at run time only.
-template <typename T, bool WRITE_Y, bool EMIT_Q, int G, int ROWS>
+// EARLY: theta is requested in front of the rows, and all rows have to be there when the scale is.  That is
+// for launches of more blocks than are resident at once, whose blocks then read while others write.
+// Measured on buffers that no cache holds, us, without / with: 512x19200 FP16 (1024 blocks) 8.7 / 8.1, 8x64x19200 FP16
+// (1024) 8.4 / 7.7, 15x128x19200 FP16 (3840) 26.35 / 25.9, 2x384x19200 FP32 (3072) 21.1 / 20.8, 64 mixed tensors of
+// 1 GiB forward + backward 930 / 918; but 384x19200 FP16 (768) 6.4 / 6.7, one scale 2457600 FP16 (240) 3.7 / 4.2, and
+// wavefront units 15x384x1200 FP16 6.99 / 7.07.  (The backward gains nothing by it: 384x19200 FP16 9.1 / 9.8.)
+template <typename T, bool WRITE_Y, bool EMIT_Q, int G, int ROWS, bool EARLY>
 __device__ __forceinline__ void forward_chunk(const DevTensor &d, const Chunk &ck, const int group = G)
 {
     typedef typename VecOf<T>::type VT;
@@ -361,7 +366,7 @@ __device__ __forceinline__ void forward_chunk(const DevTensor &d, const Chunk &c
     T *y = WRITE_Y ? (T *)d.y + ck.first : nullptr;
     int8_t *q = EMIT_Q ? d.q + ck.first : nullptr;
     const int tid = threadIdx.x & (group - 1);
-    const float theta = ld_uniform(d.theta + ck.channel);
+    const float theta = EARLY ? ld_early(d.theta + ck.channel) : ld_uniform(d.theta + ck.channel);
 
     const bool vector_ok = !WRITE_Y || (((uintptr_t)x ^ (uintptr_t)y) & (kVecBytes - 1)) == 0;
     const int head = vector_ok ? head_elems<T>(x, ck.n) : ck.n;
@@ -444,9 +449,9 @@ template <typename T, int G>
 __device__ __forceinline__ void forward_variants(const DevTensor &d, unsigned unit)
 {
     const Chunk ck = locate_chunk(d, unit);
-    if (!d.q) forward_chunk<T, true, false, G, kMaxRows>(d, ck);
-    else if (d.y) forward_chunk<T, true, true, G, kMaxRows>(d, ck);
-    else forward_chunk<T, false, true, G, kMaxRows>(d, ck);
+    if (!d.q) forward_chunk<T, true, false, G, kMaxRows, true>(d, ck);
+    else if (d.y) forward_chunk<T, true, true, G, kMaxRows, true>(d, ck);
+    else forward_chunk<T, false, true, G, kMaxRows, true>(d, ck);
 }
 
 // Tensors whose slabs are short (d.wave_units) give every wavefront a slab of its own: four
@@ -1095,14 +1100,14 @@ __device__ __forceinline__ DevTensor fetch(const DevTensor *table, int i)
 // Single tensor: descriptor in the kernel arguments (SGPRs), dtype fixed at compile time.
 // WAVES: the tensor's slabs are short and every wavefront owns one (chosen by the launcher).  ROWS: the
 // vectors per lane that a whole chunk of this tensor has.
-template <typename T, bool WRITE_Y, bool EMIT_Q, bool WAVES, int ROWS>
+template <typename T, bool WRITE_Y, bool EMIT_Q, bool WAVES, int ROWS, bool EARLY>
 __global__ void __launch_bounds__(kBlock) forward_kernel(const DevTensor d)
 {
     if (WAVES) {
         const unsigned unit = blockIdx.x * (kBlock / 64) + wave_index();
-        if (unit < d.slabs * d.cps) forward_chunk<T, WRITE_Y, EMIT_Q, 64, ROWS>(d, locate_chunk(d, unit));
+        if (unit < d.slabs * d.cps) forward_chunk<T, WRITE_Y, EMIT_Q, 64, ROWS, EARLY>(d, locate_chunk(d, unit));
     } else {
-        forward_chunk<T, WRITE_Y, EMIT_Q, kBlock, ROWS>(d, own_chunk(d));
+        forward_chunk<T, WRITE_Y, EMIT_Q, kBlock, ROWS, EARLY>(d, own_chunk(d));
     }
 }
 
@@ -1118,7 +1123,7 @@ template <typename F> __device__ __forceinline__ void for_rows(int rows, F f)
 }
 
 // ANY_Q = false: no tensor of the list wants codes (the usual case; keeps the kernel lean)
-template <bool ANY_Q>
+template <bool ANY_Q, bool EARLY>
 __global__ void __launch_bounds__(kBlock) forward_multi_kernel(const DevTensor *table, int n)
 {
     const DevTensor d = fetch(table, find_by_block(table, n, blockIdx.x));
@@ -1133,8 +1138,8 @@ __global__ void __launch_bounds__(kBlock) forward_multi_kernel(const DevTensor *
     const Chunk ck = locate_chunk(d, unit);
     const int group = d.wave_units ? 64 : kBlock;
     for_rows(d.rows, [&](auto rows) {
-        if (d.dtype == 0) forward_chunk<_Float16, true, false, 0, decltype(rows)::value>(d, ck, group);
-        else forward_chunk<float, true, false, 0, decltype(rows)::value>(d, ck, group);
+        if (d.dtype == 0) forward_chunk<_Float16, true, false, 0, decltype(rows)::value, EARLY>(d, ck, group);
+        else forward_chunk<float, true, false, 0, decltype(rows)::value, EARLY>(d, ck, group);
     });
 }
 
@@ -1312,47 +1317,51 @@ static void launch_tensor(K kernel, unsigned blocks, hipStream_t st, const DevTe
 // Vectors in a whole chunk.
 template <typename T> static unsigned chunk_vecs(const DevTensor &d) { return (d.chunk + VecOf<T>::N - 1) / VecOf<T>::N; }
 
-// Calls f with a number of rows as a compile-time constant: `rows` itself, or kMaxRows from MOST + 1 on.
-// A kernel built for exactly the rows of the tensor issues no loads past the end of a chunk and runs
-// through less code; short chunks feel both.
-template <int MOST, typename F> static void with_rows(int rows, F f)
+// Calls f with the number of rows as a compile-time constant.  A kernel built for exactly the rows of the
+// tensor issues no loads past the end of a chunk and runs through less code; short chunks feel both.
+template <typename F> static void with_rows(int rows, F f)
 {
-    if (rows == 1) return f(std::integral_constant<int, 1>());
-    if (rows == 2) return f(std::integral_constant<int, 2>());
-    if (MOST >= 3 && rows == 3) return f(std::integral_constant<int, MOST >= 3 ? 3 : kMaxRows>());
-    if (MOST >= 4 && rows == 4) return f(std::integral_constant<int, MOST >= 4 ? 4 : kMaxRows>());
-    return f(std::integral_constant<int, kMaxRows>());
+    switch (rows) {
+    case 1: return f(std::integral_constant<int, 1>());
+    case 2: return f(std::integral_constant<int, 2>());
+    case 3: return f(std::integral_constant<int, 3>());
+    case 4: return f(std::integral_constant<int, 4>());
+    default: return f(std::integral_constant<int, kMaxRows>());
+    }
 }
 
 // Forward, us before -> with exactly one or two rows: 153600 FP32 elements 2.47 -> 2.31; 64x147 FP32 3.05 ->
 // 2.65; 384x3456 FP32 3.31 -> 3.19.  With three rows exactness loses (3x128x4800 FP16: 3.42 -> 3.48), and
 // so it does for wavefront units (15x384x1200 FP16: 6.70 -> 6.94), so those take kMaxRows.
-template <typename T, bool WAVES>
+template <typename T, bool WAVES, bool EARLY>
+static void launch_forward_full(const DevTensor &d, unsigned blocks, hipStream_t st)
+{
+    if (!d.q) launch_tensor(forward_kernel<T, true, false, WAVES, kMaxRows, EARLY>, blocks, st, d);
+    else if (d.y) launch_tensor(forward_kernel<T, true, true, WAVES, kMaxRows, EARLY>, blocks, st, d);
+    else launch_tensor(forward_kernel<T, false, true, WAVES, kMaxRows, EARLY>, blocks, st, d);
+}
+
+template <typename T>
 static void launch_forward_single(const DevTensor &d, unsigned blocks, hipStream_t st)
 {
-    if (WAVES || d.q) {
-        if (!d.q) launch_tensor(forward_kernel<T, true, false, WAVES, kMaxRows>, blocks, st, d);
-        else if (d.y) launch_tensor(forward_kernel<T, true, true, WAVES, kMaxRows>, blocks, st, d);
-        else launch_tensor(forward_kernel<T, false, true, WAVES, kMaxRows>, blocks, st, d);
-        return;
-    }
-    with_rows<2>(d.rows, [&](auto rows) {
-        launch_tensor(forward_kernel<T, true, false, false, decltype(rows)::value>, blocks, st, d);
-    });
+    if (d.wave_units) launch_forward_full<T, true, false>(d, blocks, st);
+    else if (!d.q && d.rows == 1) launch_tensor(forward_kernel<T, true, false, false, 1, false>, blocks, st, d);
+    else if (!d.q && d.rows == 2) launch_tensor(forward_kernel<T, true, false, false, 2, false>, blocks, st, d);
+    else if (blocks > kResidentBlocks) launch_forward_full<T, false, true>(d, blocks, st);
+    else launch_forward_full<T, false, false>(d, blocks, st);
 }
 
 int launch_forward(const KArgs &a, unsigned blocks, bool emit_q, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
     if (a.table) {
-        if (emit_q) launch(forward_multi_kernel<true>, blocks, st, a.table, a.n);
-        else launch(forward_multi_kernel<false>, blocks, st, a.table, a.n);
+        if (emit_q) launch(forward_multi_kernel<true, true>, blocks, st, a.table, a.n);
+        else if (blocks > kResidentBlocks) launch(forward_multi_kernel<false, true>, blocks, st, a.table, a.n);
+        else launch(forward_multi_kernel<false, false>, blocks, st, a.table, a.n);
     } else if (a.one.dtype == 0) {
-        if (a.one.wave_units) launch_forward_single<_Float16, true>(a.one, blocks, st);
-        else launch_forward_single<_Float16, false>(a.one, blocks, st);
+        launch_forward_single<_Float16>(a.one, blocks, st);
     } else {
-        if (a.one.wave_units) launch_forward_single<float, true>(a.one, blocks, st);
-        else launch_forward_single<float, false>(a.one, blocks, st);
+        launch_forward_single<float>(a.one, blocks, st);
     }
     return (int)hipGetLastError();
 }
@@ -1366,7 +1375,7 @@ static void launch_backward_typed(const DevTensor &d, unsigned blocks, bool fuse
         launch_tensor(backward_kernel<T, false, SHAPE, kMaxRows>, blocks, st, d);
         return;
     }
-    with_rows<4>(d.rows, [&](auto rows) {
+    with_rows(d.rows, [&](auto rows) {
         launch_tensor(backward_kernel<T, true, SHAPE, decltype(rows)::value>, blocks, st, d);
     });
 }
@@ -1385,7 +1394,7 @@ static void launch_backward_typed(const DevTensor &d, unsigned blocks, bool fuse
 template <typename T> static bool burst_pays(const DevTensor &d, unsigned blocks)
 {
     const bool half = sizeof(T) == 2;
-    return blocks <= kBurstMostBlocks && blocks >= (half ? kBurstLeastBlocksF16 : kBurstLeastBlocksF32) &&
+    return blocks <= kResidentBlocks && blocks >= (half ? kBurstLeastBlocksF16 : kBurstLeastBlocksF32) &&
            chunk_vecs<T>(d) >= (half ? kBurstLeastVecsF16 : kBurstLeastVecsF32);
 }
 
