@@ -801,8 +801,13 @@ fq_status make_plan(const fq_distill *d, Plan &pl)
         // 25.2, 3x384x19200 61 / 55, 4x256x9601 53 / 40; 8x256x4800 23.9 / 25.7).  A wide FP16 tile fills a
         // compute unit by itself, with nothing to stream while it reduces (15x256x19200 85 / 95, 8x250x5001 26.6 / 29;
         // 4x128x9601 15.1 / 14.4).
+        // Not where the narrow ones are all resident at once and the wide ones need a second round (FP32 on the grid,
+        // 3x134x6588: 14.0 / 15.2; its registers let a compute unit hold 4, 3 or 2 narrow tiles, 2 or 1 wide ones).
         const bool many = narrow_tpn * d->n > (long long)kGatherTiles;
-        pl.wide = many && (!half || wide_tpn * d->n <= (long long)kGatherTiles);
+        const long long held_narrow = pl.fused_kch <= 2 ? 4 : pl.fused_kch <= 4 ? 3 : 2, held_wide = pl.fused_kch <= 2 ? 2 : 1;
+        const bool second_round = pl.quads && narrow_tpn * d->n <= held_narrow * kComputeUnits &&
+                                  wide_tpn * d->n > held_wide * kComputeUnits;
+        pl.wide = many && (wide_tpn * d->n <= (long long)kGatherTiles || (!half && !second_round));
         const long long tpn = pl.wide ? wide_tpn : narrow_tpn;
         pl.one_launch = tpn * d->n <= (long long)kGatherTiles;
         if (tpn * d->n > 0x3fffffffLL) return FQ_ERR_SHAPE;
