@@ -72,6 +72,7 @@ struct DistillArgs {
     double *out;        // mse, cosim, loss
     long long M, P;     // positions per image, positions in total
     unsigned C, groups, per_group, tiles_per_n, tiles, poll_rounds;
+    unsigned neighbours;           // see tile_of_block
     double k1u, k2u, eps, lambda, inv_ncm, inv_nm;
 };
 
@@ -538,8 +539,9 @@ __device__ __forceinline__ void gather_or_leave(const DistillArgs &k)
 }
 
 // Blocks go to the eight XCDs in turn; this gives each XCD a run of neighbouring tiles.  One to one.
-// Only for rows off the grid, us without / with: 4x256x9601 FP32 40.2 / 35.3, 8x250x5001 FP16 26.6 / 21.9; on
-// the grid neighbours share no line, and it loses: 15x128x19200 FP16 44.3 / 47.4.
+// Only where rows are no whole number of 128-byte lines, so that neighbours share the lines at their ends, us
+// without / with: 4x256x9601 FP32 40.2 / 35.3, 8x250x5001 FP16 26.6 / 21.9, 3x134x6588 FP32 14.9 / 12.4, 6x200x3300
+// FP32 18.4 / 16.3; otherwise it loses: 15x128x19200 FP16 44.3 / 47.4.
 __device__ __forceinline__ unsigned tile_of_block(unsigned block, unsigned tiles)
 {
     constexpr unsigned kXcds = 8;
@@ -561,7 +563,7 @@ __global__ __launch_bounds__(THREADS, 4) void distill_fused_kernel(DistillArgs k
     __shared__ double cosines[P];
 
     const unsigned lane = threadIdx.x % L, row = threadIdx.x / L, wave = threadIdx.x >> 6;
-    const unsigned tile = QUADS ? blockIdx.x : tile_of_block(blockIdx.x, k.tiles);
+    const unsigned tile = k.neighbours ? tile_of_block(blockIdx.x, k.tiles) : blockIdx.x;
     const unsigned n = tile / k.tiles_per_n, tn = tile - n * k.tiles_per_n;
     const long long tile_m = (long long)tn * P;
     long long m0 = tile_m + (long long)lane * V;
@@ -802,7 +804,7 @@ fq_status make_plan(const fq_distill *d, Plan &pl)
         // compute unit by itself, with nothing to stream while it reduces (15x256x19200 85 / 95, 8x250x5001 26.6 / 29;
         // 4x128x9601 15.1 / 14.4).
         // Not where the narrow ones are all resident at once and the wide ones need a second round (FP32 on the grid,
-        // 3x134x6588: 14.0 / 15.2; its registers let a compute unit hold 4, 3 or 2 narrow tiles, 2 or 1 wide ones).
+        // 3x134x6588: 14.6 / 14.9, 5x134x4800: 11.0 / 11.9; its registers let a compute unit hold 4, 3 or 2 narrow tiles, 2 or 1 wide ones).
         const bool many = narrow_tpn * d->n > (long long)kGatherTiles;
         const long long held_narrow = pl.fused_kch <= 2 ? 4 : pl.fused_kch <= 4 ? 3 : 2, held_wide = pl.fused_kch <= 2 ? 2 : 1;
         const bool second_round = pl.quads && narrow_tpn * d->n <= held_narrow * kComputeUnits &&
@@ -997,6 +999,7 @@ fq_status fq_distill_loss(const fq_distill *d, void *workspace, size_t ws_bytes,
     k.records = (unsigned long long *)workspace;
     k.nonce = pl.one_launch ? next_nonce() : 0ull;
     k.poll_rounds = kPollRounds;
+    k.neighbours = pl.fused_kch && (!pl.quads || d->inner * (d->dtype == FQ_F16 ? 2 : 4) % 128 != 0);
     if (pl.fused_kch) {
         k.coef = nullptr;
         return d->dtype == FQ_F16 ? launch_fused_width<_Float16>(k, pl, grad, st)
