@@ -442,10 +442,11 @@ constexpr int kStats = 3 * kFusedVec;            // per lane: a.b, a.a, b.b of f
 
 // The three results out of the tiles' sums, by one wavefront, in the kernel that makes them (at most
 // kGatherTiles tiles).  A tile's record is {cos, cos ^ N, sq, sq ^ N} with a number N of this call's own: the
-// workspace may hold anything, and a record that does not fit together with N has not arrived.
+// workspace may hold anything, and a pair of words that does not fit together with N has not arrived.
 // The protocol is that of the backward's sums (kPollRounds rounds, then a flag, here N, and the tile that
-// arrives last finishes; whoever claims the call puts ~N into the flag); records are invalid again
-// afterwards, because a graph replays N.
+// arrives last finishes; whoever claims the call puts ~N into the flag).  Afterwards all four words are zero,
+// which fits no N.  A graph replays N, and the words travel one by one: a pair left as it is would be taken
+// for the next replay's where that one's other pair is visible first.
 constexpr unsigned kGatherTiles = 256;
 constexpr unsigned kPollRounds = 32;
 
@@ -494,8 +495,9 @@ __device__ __forceinline__ void finish_gathered(const DistillArgs &k, double sc,
     const unsigned lane = threadIdx.x & 63;
     if (lane == kSumLane) write_results(k, sc, ss);
     for (unsigned tile = lane; tile < k.tiles; tile += 64) {
-        __hip_atomic_store(k.records + (size_t)tile * 4, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(k.records + (size_t)tile * 4 + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            __hip_atomic_store(k.records + (size_t)tile * 4 + j, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 

@@ -144,3 +144,44 @@ def test_distillation_step_in_a_graph():
         for a, b in zip(snapshot(), eager):
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), "replay %d differs" % rep
     assert torch.isfinite(out).all() and float(out[0]) > 0.0
+
+
+@pytest.mark.parametrize("shape, dtype, tiles", [
+    ((1, 5, 64), torch.float16, 1), ((2, 20, 1536), torch.float16, 48), ((3, 33, 131), torch.float32, 15),
+    ((1, 3, 16384), torch.float16, 256), ((2, 24, 16384), torch.float16, 256),        # narrow and wide tiles
+])
+@pytest.mark.parametrize("start", [0.0, float("nan")])
+def test_distillation_replays_carry_nothing_over(shape, dtype, tiles, start):
+    """One captured fq_distill_loss, replayed with new data and the workspace left alone: every replay brings
+    the same number for its tiles' records, so a replay may leave none that still fits it."""
+    H.say("graph capture: fq_distill_loss alone, shape %s %s, %d tiles, workspace starts as %r" % (shape, dtype, tiles, start))
+    gen = torch.Generator(device="cuda").manual_seed(shape[1] * 1000 + tiles)
+    draw = lambda: (torch.randn(shape, generator=gen, device="cuda") * 1.5).to(dtype)
+    a, b = draw(), draw()
+    out, want = (torch.zeros(3, dtype=torch.float64, device="cuda") for _ in range(2))
+    ga, want_ga = torch.zeros_like(a), torch.zeros_like(a)
+    d = fq.FqDistill.from_torch(*shape, a, b, out, ga, lam=0.5, upstream=256.0)
+    eager = fq.FqDistill.from_torch(*shape, a, b, want, want_ga, lam=0.5, upstream=256.0)
+    words = fq.fq_distill_workspace_bytes(d) // 8
+    assert words >= tiles * 4 + 1
+    ws, ws_eager = (torch.full((words,), start, dtype=torch.float64, device="cuda") for _ in range(2))
+    side = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            fq.fq_distill_loss(d, ws)
+    torch.cuda.synchronize()
+    for rep in range(6):
+        a.copy_(draw() * (1.0 + rep))
+        b.copy_(draw())
+        fq.fq_distill_loss(eager, ws_eager)
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and torch.equal(ga.view(torch.uint8), want_ga.view(torch.uint8)), rep
+        left = ws.view(torch.int64)
+        assert not bool(left[:tiles * 4].any()), "a record is left after replay %d" % rep
+        if start == 0.0:
+            assert not bool(left.any()), "the flag is left raised after replay %d" % rep
