@@ -54,11 +54,19 @@ class _FakeQuantize(torch.autograd.Function):
         x, theta = ctx.saved_tensors
         (outer, channels, inner), qmin, qmax, eps, s_min, s_max = ctx.meta
         gy = gy.contiguous()
+        th = theta.contiguous()
+        # The extents are the forward's, the tensors what came through torch's saved-tensor hooks.
+        if not x.is_contiguous():
+            raise ValueError("tensors must be contiguous")
         if gy.dtype != x.dtype:
             raise TypeError("expected %s, got %s" % (x.dtype, gy.dtype))
-        if gy.numel() != x.numel():
-            raise ValueError("tensor has %d elements, view says %d" % (gy.numel(), x.numel()))
-        th = theta.contiguous()
+        if th.dtype != torch.float32:
+            raise TypeError("expected %s, got %s" % (torch.float32, th.dtype))
+        for t in (x, gy):
+            if t.numel() != outer * channels * inner:
+                raise ValueError("tensor has %d elements, view says %d" % (t.numel(), outer * channels * inner))
+        if th.numel() != channels:
+            raise ValueError("per-channel tensor has %d elements, want %d" % (th.numel(), channels))
         gx = torch.empty_like(x) if want_gx else None
         gtheta = torch.empty_like(th)
         t = fq.FqTensor(outer, channels, inner, _DTYPES[x.dtype], qmin, qmax, eps, s_min, s_max,
