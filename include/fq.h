@@ -151,9 +151,9 @@ fq_status fq_layout(const fq_tensor *t, fq_layout_info *info);
  * call leaves the slots and the partial sums zero again, so the same tensor list (same shapes and
  * flags, any pointers) may follow without zeroing.  For fq_multi_tensor and fq_plan_create the
  * descriptor table stays where it was written, and where the sums and slots lie depends on the
- * list: before a workspace serves a list of other shapes, or after anything else has written to it
- * (fq_distill_loss, say), zero it again.  One workspace must not be used by two calls that can
- * overlap in time.
+ * list: before a workspace serves a list of other shapes, or after anything but this library has
+ * written to it, zero it again.  (fq_distill_loss leaves zero what it has written.)  One workspace
+ * must not be used by two calls that can overlap in time.
  */
 fq_status fq_workspace_init(void *workspace, size_t ws_bytes, void *hip_stream);
 
@@ -258,11 +258,11 @@ void fq_plan_destroy(fq_plan *plan);
  * gstudent = upstream * dloss/dstudent in the tensors' dtype (rounded once from binary64; a
  * clamped norm counts as a constant).  `upstream` is the factor in front of this pair's loss in
  * the total (Eq. (7) sums the pairs: 1, or the loss scale of an FP16 run).  student / teacher are
- * contiguous [n, channels, inner]; gstudent may be exactly student or teacher (in place).  One or
- * two launches; fixed summation order.  A tensor without elements needs no workspace and
+ * contiguous [n, channels, inner]; gstudent may be exactly student or teacher (in place).  One to
+ * three launches; fixed summation order.  A tensor without elements needs no workspace and
  * gives NaN for mse and loss (a mean of nothing); cosim is then NaN without positions and 0 with
- * positions but no channels.  The workspace need not be initialised and may be shared with other such calls
- * that do not overlap in time.
+ * positions but no channels.  The workspace need not be initialised and may be shared with other calls
+ * that do not overlap in time: whatever this one writes to it is zero again when it has completed.
  */
 typedef struct fq_distill {
     int64_t n, channels, inner;
