@@ -811,12 +811,18 @@ fq_status make_plan(const fq_distill *d, Plan &pl)
         // compute unit by itself, with nothing to stream while it reduces (15x256x19200 85 / 95, 8x250x5001 26.6 / 29;
         // 4x128x9601 15.1 / 14.4).
         // Not where the narrow ones are all resident at once and the wide ones need a second round (FP32 on the grid,
-        // 3x134x6588: 14.6 / 14.9, 5x134x4800: 11.0 / 11.9; its registers let a compute unit hold 4, 3 or 2 narrow tiles, 2 or 1 wide ones).
+        // 3x134x6588: 13.6 / 14.3, 5x134x4800: 11.7 / 12.9, without a gradient 10.0 / 10.4 and 9.3 / 9.7; its registers
+        // let a compute unit hold 4, 3 or 2 narrow tiles, 2 or 1 wide ones).
+        // Nor where the last wide tile of an image is half empty and images are short: on the grid if more than a
+        // sixteenth of the wide tiles' positions lie behind the image (400x128x96 15.3 / 17.2, 150x384x288 37.6 / 40.6,
+        // 400x128x224 27.7 / 28.9), off it, where wide rows share fewer lines (400x128x129 29.3 / 24.1), if they are
+        // as many as the narrow ones (1000x128x9 11.4 / 15.6; on the grid 4000x128x4 22.6 / 36.4, 3000x24x32 13.9 / 21.7).
         const bool many = narrow_tpn * d->n > (long long)kGatherTiles;
         const long long held_narrow = pl.fused_kch <= 2 ? 4 : pl.fused_kch <= 4 ? 3 : 2, held_wide = pl.fused_kch <= 2 ? 2 : 1;
         const bool second_round = pl.quads && narrow_tpn * d->n <= held_narrow * kComputeUnits &&
                                   wide_tpn * d->n > held_wide * kComputeUnits;
-        pl.wide = many && (wide_tpn * d->n <= (long long)kGatherTiles || (!half && !second_round));
+        const bool half_empty = pl.quads ? 16 * (2 * wide_tpn - narrow_tpn) > narrow_tpn : wide_tpn == narrow_tpn;
+        pl.wide = many && (wide_tpn * d->n <= (long long)kGatherTiles || (!half && !second_round && !half_empty));
         const long long tpn = pl.wide ? wide_tpn : narrow_tpn;
         pl.one_launch = tpn * d->n <= (long long)kGatherTiles;
         if (tpn * d->n > 0x3fffffffLL) return FQ_ERR_SHAPE;

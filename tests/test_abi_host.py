@@ -183,6 +183,18 @@ def test_distill_struct_and_workspace(fq):
     assert fq.fq_distill_workspace_bytes(_distill(fq, channels=0, student=None, teacher=None)) == 256
 
 
+@pytest.mark.parametrize("n, channels, inner, tiles", [
+    # FP32, more tiles than one launch adds up: tiles of 64 positions where they cover an image, else of 32
+    (400, 128, 128, 800), (400, 128, 96, 1200), (400, 128, 224, 2800), (150, 384, 288, 1350), (200, 128, 480, 3000),
+    (80, 128, 15 * 32, 80 * 15), (80, 128, 17 * 32 - 4, 80 * 9), (400, 128, 65, 800), (400, 128, 129, 1200),
+    (600, 128, 32, 600), (4, 256, 9600, 600),
+])
+def test_distill_tiles_follow_the_image(fq, n, channels, inner, tiles):
+    d = _distill(fq, n=n, channels=channels, inner=inner, dtype=fq.FQ_F32, student=1 << 40, teacher=2 << 40, gstudent=3 << 40)
+    got = fq.fq_distill_workspace_bytes(d)
+    assert tiles * 16 <= got < tiles * 16 + 256, (got // 16, tiles)
+
+
 @pytest.mark.parametrize("kw, status", [
     (dict(dtype=7), -2), (dict(n=-1), -3), (dict(inner=2 ** 31, n=2), -3), (dict(channels=2 ** 31), -3),
     (dict(student=None), -1), (dict(teacher=None), -1), (dict(out=None), -1),

@@ -28,6 +28,9 @@ pytestmark = pytest.mark.gpu
     *[(np.float32, (1, c, 8300)) for c in (128, 256, 384, 512)],
     # ends of images
     *[(d, (9, 5, m)) for d in (np.float16, np.float32) for m in (1, 2, 3, 5, 63, 65, 127, 129)],
+    # more than 256 images of one or a few tiles
+    *[(d, (n, 5, m)) for d in (np.float16, np.float32) for n, m in ((300, 9), (1100, 4), (300, 32), (129, 96), (130, 65))],
+    (np.float32, (300, 130, 16)), (np.float32, (65, 130, 160)), (np.float32, (600, 70, 64)),
 ])
 def test_tiles(oracle, dtype, shape):
     a, b = _pair(shape[1] * 7 + shape[2], shape, dtype)
