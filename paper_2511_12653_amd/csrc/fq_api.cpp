@@ -418,7 +418,12 @@ fq_status prepare(const fq_tensor *ts, int n, int mode, bool use_table, void *wo
     P.blocks = L.blocks;
     P.channels = L.channels;
     P.any_empty_with_channels = L.any_empty_with_channels;
-    for (int i = 0; i < n; ++i) P.emit_q = P.emit_q || ts[i].q != nullptr;
+    long long whole = 0;
+    for (int i = 0; i < n; ++i) {
+        P.emit_q = P.emit_q || ts[i].q != nullptr;
+        if (table[(size_t)i].rows == kChunkVecs / kBlock) whole += L.plans[(size_t)i].blocks;
+    }
+    P.args.whole = 2 * whole >= L.blocks ? 1u : 0u;
     P.two_pass = any_flag(ts, n, FQ_FLAG_TWO_PASS) || L.any_empty_with_channels;
     return FQ_OK;
 }

@@ -92,6 +92,7 @@ struct KArgs {
     const DevTensor *table;    // device array of n descriptors, and behind it of their n first blocks
                                // (multi-tensor launch)
     int n;
+    unsigned whole;            // forward of a table: most of the blocks have as many rows as a chunk can have
     AdamBias bias;             // backward of a table
 };
 

@@ -445,25 +445,25 @@ __device__ __forceinline__ void forward_chunk(const DevTensor &d, const Chunk &c
 }
 
 // what one tensor asks of the forward pass: y only, y and codes, or codes only
-template <typename T, int G>
+template <typename T, int G, bool EARLY>
 __device__ __forceinline__ void forward_variants(const DevTensor &d, unsigned unit)
 {
     const Chunk ck = locate_chunk(d, unit);
-    if (!d.q) forward_chunk<T, true, false, G, kMaxRows, true>(d, ck);
-    else if (d.y) forward_chunk<T, true, true, G, kMaxRows, true>(d, ck);
-    else forward_chunk<T, false, true, G, kMaxRows, true>(d, ck);
+    if (!d.q) forward_chunk<T, true, false, G, kMaxRows, EARLY>(d, ck);
+    else if (d.y) forward_chunk<T, true, true, G, kMaxRows, EARLY>(d, ck);
+    else forward_chunk<T, false, true, G, kMaxRows, EARLY>(d, ck);
 }
 
 // Tensors whose slabs are short (d.wave_units) give every wavefront a slab of its own: four
 // slabs to a block, no barrier.  Otherwise the block owns one chunk.
-template <typename T>
+template <typename T, bool EARLY>
 __device__ __forceinline__ void forward_dispatch(const DevTensor &d, unsigned local_block)
 {
     if (d.wave_units) {
         const unsigned unit = local_block * (kBlock / 64) + wave_index();
-        if (unit < d.slabs * d.cps) forward_variants<T, 64>(d, unit);
+        if (unit < d.slabs * d.cps) forward_variants<T, 64, EARLY>(d, unit);
     } else {
-        forward_variants<T, kBlock>(d, local_block);
+        forward_variants<T, kBlock, EARLY>(d, local_block);
     }
 }
 
@@ -1129,8 +1129,8 @@ __global__ void __launch_bounds__(kBlock) forward_multi_kernel(const DevTensor *
     const DevTensor d = fetch(table, find_by_block(table, n, blockIdx.x));
     const unsigned local = blockIdx.x - d.block_begin;
     if (ANY_Q) {
-        if (d.dtype == 0) forward_dispatch<_Float16>(d, local);
-        else forward_dispatch<float>(d, local);
+        if (d.dtype == 0) forward_dispatch<_Float16, EARLY>(d, local);
+        else forward_dispatch<float, EARLY>(d, local);
         return;
     }
     const unsigned unit = d.wave_units ? local * (kBlock / 64) + wave_index() : local;
@@ -1355,7 +1355,12 @@ int launch_forward(const KArgs &a, unsigned blocks, bool emit_q, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
     if (a.table) {
-        if (emit_q) launch(forward_multi_kernel<true, true>, blocks, st, a.table, a.n);
+        // Lists with codes run the code for kMaxRows rows whatever their chunks have, so that blocks of fewer rows wait
+        // for loads that they do not need: there theta in front of the rows pays for whole chunks only.  us, in front /
+        // behind: whole chunks 16x(2x128x9600) FP16 36.3 / 37.3, 6x(200x9600) 12.4 / 13.0, 8x(8x128x9600) FP32 120.1 /
+        // 122.2; others 12x(128x4800) FP16 11.4 / 10.5, 64x(64x4800) 27.9 / 26.2, 22x(64x576) FP32 5.3 / 4.8.
+        if (emit_q && a.whole && blocks > kResidentBlocks) launch(forward_multi_kernel<true, true>, blocks, st, a.table, a.n);
+        else if (emit_q) launch(forward_multi_kernel<true, false>, blocks, st, a.table, a.n);
         else if (blocks > kResidentBlocks) launch(forward_multi_kernel<false, true>, blocks, st, a.table, a.n);
         else launch(forward_multi_kernel<false, false>, blocks, st, a.table, a.n);
     } else if (a.one.dtype == 0) {

@@ -42,6 +42,22 @@ def test_every_block_finds_its_tensor(n):
             H.check_backward(d, ref[0], ref[1], "lookup[%d of %d]" % (i, n))
 
 
+@pytest.mark.parametrize("n, channels, inner, dtype", [
+    # theta in front of the rows or behind: up to 768 blocks, more of them with whole chunks, more with short ones
+    (3, 256, 5120, np.float32), (4, 200, 5120, np.float32), (4, 200, 10240, np.float16), (5, 200, 2400, np.float16),
+])
+def test_lists_with_codes(n, channels, inner, dtype):
+    rng = np.random.Generator(np.random.Philox(n * channels))
+    cases = [_case(rng, 1, channels, inner, dtype) for _ in range(n)] + [_case(rng, 2, 3, 77, dtype)]
+    H.say("list with codes: %d x (1, %d, %d) %s" % (n, channels, inner, np.dtype(dtype).name))
+    dcs = [H.DeviceCase(c, want_q=i % 2 == 0) for i, c in enumerate(cases)]
+    arr = fq.fq_tensor_array([d.desc for d in dcs])
+    fq.fq_multi_tensor(arr, fq.FQ_MODE_FORWARD, H.workspace_for(arr, fq.FQ_MODE_FORWARD))
+    torch.cuda.synchronize()
+    for i, (c, d) in enumerate(zip(cases, dcs)):
+        H.check_forward(d, H.oracle_forward(c), "codes[%d]" % i)
+
+
 @pytest.mark.parametrize("same", [True, False])
 def test_adam_steps_of_a_plan(same):
     rng = np.random.Generator(np.random.Philox(99))
