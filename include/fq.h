@@ -66,8 +66,8 @@ enum {
        of in the last block of each channel.  Same results bit for bit. */
     FQ_FLAG_TWO_PASS = 2u,
     /* Backward: the wavefronts that gather a channel's partial sums do not poll for those that
-       are still missing (a few tens of microseconds at most otherwise); the unit that comes last
-       finishes the channel.  Same results bit for bit. */
+       are still missing (otherwise a few tens of microseconds at most, beside the time that adding
+       the sums takes); the unit that comes last finishes the channel.  Same results bit for bit. */
     FQ_FLAG_NO_POLL = 4u
 };
 

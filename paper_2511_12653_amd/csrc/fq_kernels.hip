@@ -714,35 +714,43 @@ __device__ __forceinline__ unsigned long long bits_of(double v) { return __built
 __device__ __forceinline__ double published(double v) { return bits_of(v) == 0ull ? -0.0 : v; }
 
 // This thread's share of the partial sums of channel c, for a block: thread t adds the sums t, t+256,
-// t+512, ... in that order, eight loads in flight.  `present` becomes false where a sum is still zero,
-// that is, not published yet.  own >= 0: unit `own` is the caller's; its sum is `mine`, not in memory.
-__device__ __forceinline__ double add_partials_block(const DevTensor &d, unsigned c, unsigned own, double mine,
-                                                     bool &present)
+// t+512, ... in that order, eight loads in flight.  looks > 0: a sum that is still zero is not published yet;
+// the wavefront then looks at those eight rows again, and gives up (false) when it has looked in vain that
+// often in all.  own >= 0: unit `own` is the caller's; its sum is `mine`, not in memory.
+__device__ __forceinline__ bool add_partials_block(const DevTensor &d, unsigned c, unsigned own, double mine,
+                                                   unsigned looks, double &acc)
 {
     const unsigned bpc = d.outer * d.cps;
     constexpr unsigned kBatch = 8;
+    const bool wait = looks != 0u;
     double *const parts = partials_of(d, c);
-    double acc = 0.0;
-    present = true;
-    for (unsigned j0 = threadIdx.x; j0 < bpc; j0 += kBlock * kBatch) {
+    acc = 0.0;
+    for (unsigned first = wave_index() * 64u; first < bpc; first += kBlock * kBatch) {
+        const unsigned j0 = first + (threadIdx.x & 63);
         double part[kBatch];
+        for (;;) {
+            order_accesses();
+            bool here = true;
 #pragma unroll
-        for (unsigned i = 0; i < kBatch; ++i) {
-            const unsigned j = j0 + i * kBlock;
-            part[i] = mine;
-            if (j < bpc && j != own)
-                part[i] = __hip_atomic_load(&parts[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-#pragma unroll
-        for (unsigned i = 0; i < kBatch; ++i) {
-            const unsigned j = j0 + i * kBlock;
-            if (j < bpc) {
-                acc += part[i];
-                present = present && (j == own || bits_of(part[i]) != 0ull);
+            for (unsigned i = 0; i < kBatch; ++i) {
+                const unsigned j = j0 + i * kBlock;
+                part[i] = mine;
+                if (j < bpc && j != own)
+                    part[i] = __hip_atomic_load(&parts[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
+#pragma unroll
+            for (unsigned i = 0; i < kBatch; ++i) {
+                const unsigned j = j0 + i * kBlock;
+                if (j < bpc && j != own) here = here && bits_of(part[i]) != 0ull;
+            }
+            if (!wait || __builtin_amdgcn_ballot_w64(!here) == 0ull) break;
+            if (--looks == 0u) return false;
         }
+#pragma unroll
+        for (unsigned i = 0; i < kBatch; ++i)
+            if (j0 + i * kBlock < bpc) acc += part[i];
     }
-    return acc;
+    return true;
 }
 
 // Put the partial sums of channel c back to zero, for the next call.
@@ -760,8 +768,9 @@ __device__ __forceinline__ void clear_partials(const DevTensor &d, unsigned c)
 // Block-wide; lds holds kBlock/64 doubles.
 __device__ __forceinline__ void finalize_channel(const DevTensor &d, unsigned c, const BlockScale &bs, double *lds)
 {
-    bool present;
-    const double acc = wave_sum(add_partials_block(d, c, ~0u, 0.0, present));
+    double acc;
+    add_partials_block(d, c, ~0u, 0.0, 0u, acc);
+    acc = wave_sum(acc);
     clear_partials<kBlock>(d, c);
     if ((threadIdx.x & 63) == kSumLane) lds[threadIdx.x >> 6] = acc;
     __syncthreads();
@@ -784,29 +793,61 @@ __device__ __forceinline__ double read_lane(double v, int lane)
 
 // The same sum, bit for bit, by a single wavefront: the block-wide version gives thread t the sums
 // t, t+256, ... and adds wavefront 0's tree to wavefront 1's, 2's and 3's in that order; here the
-// one wavefront plays the four in turn.  `present` is uniform: all sums of the channel are there.
-__device__ __forceinline__ double add_partials_wave(const DevTensor &d, unsigned c, unsigned own, double mine,
-                                                    bool &present)
+// one wavefront plays the four, 256 sums in flight (4000x4x100 FP32, 4000 units per channel: 30.8 us with one
+// row of 64 at a time, 22.1 now).  looks (at least 1) as above.
+__device__ __forceinline__ bool add_partials_wave(const DevTensor &d, unsigned c, unsigned own, double mine,
+                                                  unsigned looks, double &total)
 {
+    constexpr unsigned kWaves = kBlock / 64;
     const unsigned bpc = d.outer * d.cps;
     const unsigned lane = threadIdx.x & 63;
     double *const parts = partials_of(d, c);
-    double total = 0.0;
-    bool here = true;
-    for (unsigned w = 0; w * 64 < bpc && w < kBlock / 64; ++w) {       // (an empty one would add +0.0)
-        double acc = 0.0;
-        for (unsigned j = w * 64 + lane; j < bpc; j += kBlock) {
-            double part = mine;
-            if (j != own) {
-                part = __hip_atomic_load(&parts[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                here = here && bits_of(part) != 0ull;
-            }
-            acc += part;
+    if (bpc <= 64u) {                              // the usual case, in less code (5x1500x72 FP16 7.5 us instead of 7.7)
+        double part = mine;
+        for (;;) {
+            order_accesses();
+            if (lane < bpc && lane != own)
+                part = __hip_atomic_load(&parts[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (__builtin_amdgcn_ballot_w64(lane < bpc && lane != own && bits_of(part) == 0ull) == 0ull) break;
+            if (--looks == 0u) return false;
         }
-        total += read_lane(wave_sum(acc), kSumLane);
+        double one = 0.0;
+        if (lane < bpc) one += part;
+        total = 0.0 + read_lane(wave_sum(one), kSumLane);
+        return true;
     }
-    present = __builtin_amdgcn_ballot_w64(!here) == 0ull;
-    return total;
+    double acc[kWaves];
+#pragma unroll
+    for (unsigned w = 0; w < kWaves; ++w) acc[w] = 0.0;
+    for (unsigned first = 0; first < bpc; first += kBlock) {
+        double part[kWaves];
+        for (;;) {
+            order_accesses();
+            bool here = true;
+#pragma unroll
+            for (unsigned w = 0; w < kWaves; ++w) {
+                const unsigned j = first + w * 64 + lane;
+                part[w] = mine;
+                if (first + w * 64 < bpc && j < bpc && j != own)
+                    part[w] = __hip_atomic_load(&parts[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (unsigned w = 0; w < kWaves; ++w) {
+                const unsigned j = first + w * 64 + lane;
+                if (j < bpc && j != own) here = here && bits_of(part[w]) != 0ull;
+            }
+            if (__builtin_amdgcn_ballot_w64(!here) == 0ull) break;
+            if (--looks == 0u) return false;
+        }
+#pragma unroll
+        for (unsigned w = 0; w < kWaves; ++w)
+            if (first + w * 64 + lane < bpc) acc[w] += part[w];
+    }
+    total = 0.0;
+#pragma unroll
+    for (unsigned w = 0; w < kWaves; ++w)
+        if (w * 64 < bpc) total += read_lane(wave_sum(acc[w]), kSumLane);      // (an empty one would add +0.0)
+    return true;
 }
 
 // How the units (blocks, or wavefronts of short-slab tensors) of a channel combine their sums
@@ -872,16 +913,16 @@ __device__ __forceinline__ void combine(const DevTensor &d, const Chunk &ck, dou
 // dependent trips to memory behind the last unit's sum, about 0.5 us each: with arrival tickets there
 // were four (store acknowledged, first-level ticket, top ticket, sums re-read).  Here there are two: the
 // unit's sum reaches memory, and the collector, which is polling the channel's sums (eight per thread and
-// trip), sees it.  A sum announces itself: its place was zero and a published sum never is.  A channel's
+// trip, in order: what it has added it does not read again), sees it.  A sum announces itself: its place was zero and a published sum never is.  A channel's
 // sums lie next to each other, so a trip is one or two cache lines.  Measured against the tickets (graph
 // of back-to-back launches): one scale, 153600 FP32 elements in 150 units 6.0 -> 4.7 us; 2457600 FP16 in
 // 240 units 7.9 -> 6.4; 39321600 FP16 in 3840 units 44.4 -> 43.0; 15x128x19200 FP16, 30 units per channel
 // 40.1 -> 39.8; 15x384x1200 FP16, 15 wavefront units 11.9 -> 11.5.  Waiting between the rounds (s_sleep
 // 4, 20) is no faster (4.7, 4.7 and 6.7, 6.9 us on the first two).
 //
-// No wait is without end and nothing rests on the order in which blocks are dispatched: the collector
-// polls at most kPollRounds times (a few tens of microseconds; normally one to three).  If a sum is still
-// missing then, it publishes its own, raises the channel's slot to kGivenUp, and looks once more after the
+// No wait is without end and nothing rests on the order in which blocks are dispatched: beside the one pass
+// that the adding takes anyhow, the collector looks at most kPollRounds times in vain (a few tens of
+// microseconds, whatever the number of units; normally one to three).  If a sum is still missing then, it publishes its own, raises the channel's slot to kGivenUp, and looks once more after the
 // flag has been acknowledged.  Every unit reads the flag after its own sum has been acknowledged, so
 // either the collector's last look sees that sum or the unit sees the flag; a unit that sees the flag
 // looks at all sums itself, and the last one to arrive finds them complete.  Whoever finds them complete
@@ -894,9 +935,8 @@ constexpr unsigned kPollRounds = 32;
 // channel if they are complete and no other unit has claimed it.
 __device__ __forceinline__ void finish_if_complete(const DevTensor &d, unsigned c, const BlockScale &bs)
 {
-    bool present;
-    const double total = add_partials_wave(d, c, ~0u, 0.0, present);
-    if (!present) return;
+    double total;
+    if (!add_partials_wave(d, c, ~0u, 0.0, 1u, total)) return;
     unsigned won = 0u;
     if ((threadIdx.x & 63) == 0) {
         unsigned long long expected = kGivenUp;
@@ -970,19 +1010,13 @@ __device__ __forceinline__ void combine_block(const DevTensor &d, const Chunk &c
         publish(d, ck, total, bs);
         return;
     }
-    // Poll: every thread until the sums it adds are all there.
-    const unsigned rounds = d.flags & 4u ? 0u : kPollRounds;      // FQ_FLAG_NO_POLL
-    bool present = false;
     double acc = 0.0;
-    for (unsigned round = 0; round < rounds && !present; ++round) {
-        order_accesses();
-        acc = add_partials_block(d, ck.channel, bpc - 1u, total, present);
-    }
+    const bool present = !(d.flags & 4u) &&                       // FQ_FLAG_NO_POLL
+                         add_partials_block(d, ck.channel, bpc - 1u, total, kPollRounds, acc);
     acc = wave_sum(acc);
-    const bool wave_missing = __builtin_amdgcn_ballot_w64(!present) != 0ull;
     if ((threadIdx.x & 63) == kSumLane) {
         fin_part[threadIdx.x >> 6] = acc;
-        missing[threadIdx.x >> 6] = wave_missing ? 1u : 0u;
+        missing[threadIdx.x >> 6] = present ? 0u : 1u;
     }
     __syncthreads();
     unsigned any_missing = 0u;
@@ -1014,13 +1048,9 @@ __device__ __forceinline__ void combine_wave(const DevTensor &d, const Chunk &ck
         publish(d, ck, total, bs);
         return;
     }
-    const unsigned rounds = d.flags & 4u ? 0u : kPollRounds;      // FQ_FLAG_NO_POLL
-    bool present = false;
     double all = 0.0;
-    for (unsigned round = 0; round < rounds && !present; ++round) {
-        order_accesses();
-        all = add_partials_wave(d, ck.channel, bpc - 1u, total, present);
-    }
+    const bool present = !(d.flags & 4u) &&                       // FQ_FLAG_NO_POLL
+                         add_partials_wave(d, ck.channel, bpc - 1u, total, kPollRounds, all);
     if (__builtin_expect(!present, 0)) {
         give_up(d, ck, total, bs);
         return;

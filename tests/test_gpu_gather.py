@@ -31,6 +31,7 @@ CHUNK = {np.float16: 10240, np.float32: 5120}     # largest chunk of a block, in
     (np.float16, 5, 1500, 72, 1),                   # a wavefront per unit
     (np.float32, 65, 70, 30, 1),                    # its second round of lanes
     (np.float16, 257, 17, 9, 1),
+    (np.float16, 2100, 2, 9, 1),                    # many rows of a wavefront's lanes
 ])
 def test_gathered_sums(dtype, outer, channels, inner, waves):
     rng = np.random.Generator(np.random.Philox(outer * 1000 + channels))
