@@ -34,8 +34,8 @@
 // itself up to 256 tiles (gather_tiles), in a kernel of its own (distill_finish_kernel) or in the
 // gradient kernel otherwise.
 // What a call has written to its workspace is zero again when it has completed: the backward's partial sums may
-// lie in the same memory, and one that is not zero reads as a unit that has arrived.  After the two reads a fill
-// does that, 1.7 to 2.4 us: every wavefront of the gradient kernel reads the coefficients, so none can clear them.
+// lie in the same memory, and one that is not zero reads as a unit that has arrived.  That costs the summing kernel
+// 0.2 to 0.4 us (15x128x19200 FP16 44.2 -> 44.6).  After the two reads a fill does it, 1.7 to 2.4 us: every wavefront of the gradient kernel reads the coefficients, so none can clear them.
 // (1x600x4800 FP16 18.5 -> 20.1, 4x768x4800 FP16 33.8 -> 36.1; a kernel that also adds the sums is no faster.)
 // All arithmetic is binary64 (two conversions and five fused multiply-adds per element pair, well
 // under the memory time), so results do not depend on how the channels were grouped beyond
@@ -318,10 +318,10 @@ __global__ __launch_bounds__(1024) void distill_finish_kernel(DistillArgs k)
             if (i0 + 1024 * j < k.tiles) {
                 sc += v[j][0];
                 ss += v[j][1];
-                st_global((double2v *)k.blocksum + (i0 + 1024 * j), double2v{0.0, 0.0});
             }
         }
     }
+    for (unsigned i = threadIdx.x; i < k.tiles; i += 1024) st_global((double2v *)k.blocksum + i, double2v{0.0, 0.0});
     sc = wave_sum(sc);
     ss = wave_sum(ss);
     if ((threadIdx.x & 63) == kSumLane) {
@@ -499,11 +499,10 @@ __device__ __forceinline__ void finish_gathered(const DistillArgs &k, double sc,
 {
     const unsigned lane = threadIdx.x & 63;
     if (lane == kSumLane) write_results(k, sc, ss);
-    for (unsigned tile = lane; tile < k.tiles; tile += 64) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            __hip_atomic_store(k.records + (size_t)tile * 4 + j, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    // (Plain stores, 16 bytes each: nobody else needs to see them within this launch, and written through to the
+    // level that all XCDs share, one word each, they add 0.2 to 0.5 us: 2x128x4819 FP32 7.46 / 7.14, 1x128x16384
+    // FP16 6.41 / 5.88.)
+    for (unsigned i = lane; i < k.tiles * 2; i += 64) st_global((double2v *)k.records + i, double2v{0.0, 0.0});
 }
 
 __device__ __forceinline__ void finish_if_complete(const DistillArgs &k, unsigned long long *flag)
