@@ -281,6 +281,12 @@ size_t fq_distill_workspace_bytes(const fq_distill *d);   /* 0 if d does not val
    has no elements.  Pure host function. */
 int fq_distill_reads_of_pair(const fq_distill *d);
 fq_status fq_distill_loss(const fq_distill *d, void *workspace, size_t ws_bytes, void *hip_stream);
+/*
+ * Testing aid: the same call, but the wavefront that gathers the tiles' sums does not poll for those
+ * that are still missing (what FQ_FLAG_NO_POLL is to the backward); the tile that comes last finishes
+ * the loss.  Same results bit for bit, of use to nobody but a test of that way.
+ */
+fq_status fq_distill_loss_no_poll(const fq_distill *d, void *workspace, size_t ws_bytes, void *hip_stream);
 
 /*
  * Measurement aid, not part of the operation: a streaming kernel without arithmetic in the launch

@@ -176,6 +176,8 @@ _lib.fq_distill_workspace_bytes.argtypes = [ctypes.POINTER(FqDistill)]
 _lib.fq_distill_workspace_bytes.restype = ctypes.c_size_t
 _lib.fq_distill_loss.argtypes = [ctypes.POINTER(FqDistill), ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
 _lib.fq_distill_loss.restype = ctypes.c_int
+_lib.fq_distill_loss_no_poll.argtypes = [ctypes.POINTER(FqDistill), ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+_lib.fq_distill_loss_no_poll.restype = ctypes.c_int
 _lib.fq_distill_reads_of_pair.argtypes = [ctypes.POINTER(FqDistill)]
 _lib.fq_distill_reads_of_pair.restype = ctypes.c_int
 _lib.fq_layout.argtypes = [ctypes.POINTER(FqTensor), ctypes.POINTER(FqLayoutInfo)]
@@ -317,6 +319,11 @@ def fq_distill_reads_of_pair(d: FqDistill) -> int:
 def fq_distill_loss(d: FqDistill, workspace, stream=None):
     p, nbytes = _ws(workspace)
     _check(_lib.fq_distill_loss(ctypes.byref(d), p, nbytes, _stream(stream)))
+
+
+def fq_distill_loss_no_poll(d: FqDistill, workspace, stream=None):
+    p, nbytes = _ws(workspace)
+    _check(_lib.fq_distill_loss_no_poll(ctypes.byref(d), p, nbytes, _stream(stream)))
 
 
 def fq_probe_stream(inputs, a, b, out, nbytes, stream=None):

@@ -972,7 +972,7 @@ size_t fq_distill_workspace_bytes(const fq_distill *d)
     return fq::make_plan(d, pl) == FQ_OK ? pl.bytes : 0;
 }
 
-fq_status fq_distill_loss(const fq_distill *d, void *workspace, size_t ws_bytes, void *hip_stream)
+static fq_status distill_loss(const fq_distill *d, void *workspace, size_t ws_bytes, void *hip_stream, unsigned poll_rounds)
 {
     using namespace fq;
     Plan pl;
@@ -1011,7 +1011,7 @@ fq_status fq_distill_loss(const fq_distill *d, void *workspace, size_t ws_bytes,
     const bool grad = d->gstudent != nullptr;
     k.records = (unsigned long long *)workspace;
     k.nonce = pl.one_launch ? next_nonce() : 0ull;
-    k.poll_rounds = kPollRounds;
+    k.poll_rounds = poll_rounds;
     k.neighbours = pl.fused_kch && (!pl.quads || d->inner * (d->dtype == FQ_F16 ? 2 : 4) % 128 != 0);
     if (pl.fused_kch) {
         k.coef = nullptr;
@@ -1030,6 +1030,16 @@ fq_status fq_distill_loss(const fq_distill *d, void *workspace, size_t ws_bytes,
     case 2: return launch<float, 2>(k, pl, grad, st);
     default: return launch<float, 1>(k, pl, grad, st);
     }
+}
+
+fq_status fq_distill_loss(const fq_distill *d, void *workspace, size_t ws_bytes, void *hip_stream)
+{
+    return distill_loss(d, workspace, ws_bytes, hip_stream, fq::kPollRounds);
+}
+
+fq_status fq_distill_loss_no_poll(const fq_distill *d, void *workspace, size_t ws_bytes, void *hip_stream)
+{
+    return distill_loss(d, workspace, ws_bytes, hip_stream, 0u);
 }
 
 }  // extern "C"

@@ -63,3 +63,40 @@ def test_workspace_shared_by_calls_of_different_shapes(oracle):
             got = out.cpu().numpy()
             assert np.all(np.abs(got - np.array(ref[:3])) <= 1e-12 * np.maximum(1.0, np.abs(ref[:3]))), rep
             assert H.ulp_distance(ga.cpu().numpy(), ref[3]).max() <= 1
+
+
+@pytest.mark.parametrize("tiles", [1, 2, 63, 65, 256])
+@pytest.mark.parametrize("start", [0.0, float("nan")])
+def test_tiles_that_come_late(tiles, start):
+    """The gathering wavefront gives up at once, so the tiles behind it finish the loss: the flag, the claim and
+    the records' way back to zero, eager and replayed, against the call that polls."""
+    H.say("distill without polling: %d tiles, workspace starts as %r" % (tiles, start))
+    shape = (1, 5, 64 * tiles)
+    gen = torch.Generator(device="cuda").manual_seed(tiles)
+    a, b = ((torch.randn(shape, generator=gen, device="cuda") * 1.5).half() for _ in range(2))
+    out, want = (torch.zeros(3, dtype=torch.float64, device="cuda") for _ in range(2))
+    ga, want_ga = torch.zeros_like(a), torch.zeros_like(a)
+    d = fq.FqDistill.from_torch(*shape, a, b, out, ga, lam=0.5)
+    polls = fq.FqDistill.from_torch(*shape, a, b, want, want_ga, lam=0.5)
+    words = fq.fq_distill_workspace_bytes(d) // 8
+    ws, ws_polls = (torch.full((words,), start, dtype=torch.float64, device="cuda") for _ in range(2))
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            fq.fq_distill_loss_no_poll(d, ws)
+    torch.cuda.synchronize()
+    for rep in range(8):
+        a.mul_(1.0 - 0.03 * rep)
+        out.fill_(float("nan"))
+        ga.zero_()
+        fq.fq_distill_loss(polls, ws_polls)
+        torch.cuda.synchronize()
+        if rep % 2:
+            graph.replay()
+        else:
+            fq.fq_distill_loss_no_poll(d, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and torch.equal(ga.view(torch.int16), want_ga.view(torch.int16)), rep
+        left = ws.view(torch.int64)
+        assert not bool(left[:tiles * 4 + 1].any()), "a record or the flag is left after pass %d" % rep
