@@ -349,7 +349,7 @@ __device__ __forceinline__ void forward_elem(T x, T *y, int8_t *q, int i, const 
 
 // WRITE_Y: write the dequantized tensor y.  EMIT_Q: write the int8 codes, N per lane packed into
 // one 64-bit (FP16 input) or 32-bit (FP32 input) store.  At least one of the two.
-// G: lanes that share the chunk, 0: `group`, known at run time only.
+// G: lanes that share the chunk.
 // EARLY: theta is requested in front of the rows, and all rows have to be there when the scale is.  That is
 // for launches of more blocks than are resident at once, whose blocks then read while others write.
 // Measured on buffers that no cache holds, us, without / with: 512x19200 FP16 (1024 blocks) 8.7 / 8.1, 8x64x19200 FP16
@@ -357,7 +357,7 @@ __device__ __forceinline__ void forward_elem(T x, T *y, int8_t *q, int i, const 
 // 1 GiB forward + backward 930 / 918; but 384x19200 FP16 (768) 6.4 / 6.7, one scale 2457600 FP16 (240) 3.7 / 4.2, and
 // wavefront units 15x384x1200 FP16 6.99 / 7.07.  (The backward gains nothing by it: 384x19200 FP16 9.1 / 9.8.)
 template <typename T, bool WRITE_Y, bool EMIT_Q, int G, int ROWS, bool EARLY>
-__device__ __forceinline__ void forward_chunk(const DevTensor &d, const Chunk &ck, const int group = G)
+__device__ __forceinline__ void forward_chunk(const DevTensor &d, const Chunk &ck)
 {
     typedef typename VecOf<T>::type VT;
     constexpr int N = VecOf<T>::N;
@@ -365,7 +365,7 @@ __device__ __forceinline__ void forward_chunk(const DevTensor &d, const Chunk &c
     const T *x = (const T *)d.x + ck.first;
     T *y = WRITE_Y ? (T *)d.y + ck.first : nullptr;
     int8_t *q = EMIT_Q ? d.q + ck.first : nullptr;
-    const int tid = threadIdx.x & (group - 1);
+    const int tid = threadIdx.x & (G - 1);
     const float theta = EARLY ? ld_early(d.theta + ck.channel) : ld_uniform(d.theta + ck.channel);
 
     const bool vector_ok = !WRITE_Y || (((uintptr_t)x ^ (uintptr_t)y) & (kVecBytes - 1)) == 0;
@@ -383,7 +383,7 @@ __device__ __forceinline__ void forward_chunk(const DevTensor &d, const Chunk &c
         const int last = nvec - 1;
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) {
-            int v = u * group + tid;
+            int v = u * G + tid;
             r[u] = ld_stream(xv + (v < last ? v : last));
         }
     }
@@ -391,12 +391,12 @@ __device__ __forceinline__ void forward_chunk(const DevTensor &d, const Chunk &c
     if (tid < edges.count) ex = ld_bits(x + edges.at(tid, head));
 
     BlockScale bs;
-    const QParams p = block_params<false, G>(d, theta, bs, group);
+    const QParams p = block_params<false, G>(d, theta, bs);
     if (d.s && ck.first == (long long)ck.channel * d.inner && tid == 0) st_global(d.s + ck.channel, p.s);
 
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
-        const int v = u * group + tid;
+        const int v = u * G + tid;
         if (v < nvec) {
             float quot[N];
 #pragma unroll
@@ -440,7 +440,7 @@ __device__ __forceinline__ void forward_chunk(const DevTensor &d, const Chunk &c
     pin_here(ex);
     if (tid < edges.count) forward_elem<T, WRITE_Y, EMIT_Q>(from_bits<T>(ex), y, q, edges.at(tid, head), p);
     if (!vector_ok) {               // x and y are misaligned relative to each other
-        for (int i = tid; i < ck.n; i += group) forward_elem<T, WRITE_Y, EMIT_Q>(ld_global(x + i), y, q, i, p);
+        for (int i = tid; i < ck.n; i += G) forward_elem<T, WRITE_Y, EMIT_Q>(ld_global(x + i), y, q, i, p);
     }
 }
 
@@ -482,7 +482,8 @@ __device__ __forceinline__ double backward_elem(T x, T g, T *gx, int i, const QP
 }
 
 // Per-thread sum of gy*t over this thread's elements of the chunk (binary64).  GX: whether gx is
-// written, kGxAsked: as the tensor's flags say.  G as in forward_chunk.
+// written, kGxAsked: as the tensor's flags say.  G: lanes that share the chunk, 0: `group`, known at run
+// time only.
 enum { kGxNo = 0, kGxYes = 1, kGxAsked = 2 };
 
 template <typename T, int GX, int G, int ROWS>
@@ -1142,9 +1143,11 @@ __global__ void __launch_bounds__(kBlock) forward_kernel(const DevTensor d)
 }
 
 // The code of the multi-tensor kernels is kept short: blocks of one launch run through different parts of
-// it, and two compute units share 64 KB of instruction cache.  So the lanes that share a chunk (a block's or a
-// wavefront's) and whether gx is written are told at run time, and the number of rows is rounded up
-// to 1, 2 or kMaxRows (the backward kernel: 72 KB -> 45 KB).
+// it, and two compute units share 64 KB of instruction cache.  So the number of rows is rounded up to 1, 2 or
+// kMaxRows, and the backward is told at run time which lanes share a chunk (a block's or a wavefront's) and
+// whether gx is written (72 KB -> 45 KB).  The forward, which is shorter, loses by the former (us, told at run
+// time / compiled in: lists of 16 mixed tensors and 20 M elements 28.2 / 27.7, 40 and 60 M 66.2 / 65.0, 4x(128x9600)
+// FP16 5.72 / 5.64).
 template <typename F> __device__ __forceinline__ void for_rows(int rows, F f)
 {
     if (rows == 1) f(std::integral_constant<int, 1>());
@@ -1166,11 +1169,15 @@ __global__ void __launch_bounds__(kBlock) forward_multi_kernel(const DevTensor *
     const unsigned unit = d.wave_units ? local * (kBlock / 64) + wave_index() : local;
     if (unit >= d.slabs * d.cps) return;
     const Chunk ck = locate_chunk(d, unit);
-    const int group = d.wave_units ? 64 : kBlock;
-    for_rows(d.rows, [&](auto rows) {
-        if (d.dtype == 0) forward_chunk<_Float16, true, false, 0, decltype(rows)::value, EARLY>(d, ck, group);
-        else forward_chunk<float, true, false, 0, decltype(rows)::value, EARLY>(d, ck, group);
-    });
+    if (d.wave_units) {
+        if (d.dtype == 0) forward_chunk<_Float16, true, false, 64, kMaxRows, EARLY>(d, ck);
+        else forward_chunk<float, true, false, 64, kMaxRows, EARLY>(d, ck);
+    } else {
+        for_rows(d.rows, [&](auto rows) {
+            if (d.dtype == 0) forward_chunk<_Float16, true, false, kBlock, decltype(rows)::value, EARLY>(d, ck);
+            else forward_chunk<float, true, false, kBlock, decltype(rows)::value, EARLY>(d, ck);
+        });
+    }
 }
 
 // SHAPE: 0 = one chunk per block; 1 = one slab per wavefront (short slabs); 2 = one chunk per block
