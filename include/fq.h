@@ -273,12 +273,13 @@ typedef struct fq_distill {
     double *out;                      /* out: 3 doubles, 8-byte aligned */
 } fq_distill;
 size_t fq_distill_workspace_bytes(const fq_distill *d);   /* 0 if d does not validate; host only */
-/* How often at most fq_distill_loss reads a line of the pair from memory for this descriptor: 1 (one
-   fused kernel holds a tile of the pair in registers from the statistics to the gradient: up to 512
-   channels, inner a multiple of 4, pointers aligned to 4 elements; also when no gradient is asked
-   for) or 2 (the fused kernel on rows off that grid, whose tiles share the lines at their ends, or,
-   with more channels, a statistics kernel and then a gradient kernel); 0 if d does not validate or
-   has no elements.  Pure host function. */
+/* Passes over the pair that fq_distill_loss makes at most for this descriptor: 1 if its rows lie on the 4-element
+   grid (inner a multiple of 4, pointers aligned to 4 elements) and there are at most 512 channels, where one fused
+   kernel holds a tile of the pair in registers from the statistics to the gradient, and wherever no gradient is asked
+   for; else 2.  (With more channels those are a statistics kernel and a gradient kernel.  Off the grid the fused kernel
+   makes one pass; the bound is what callers have planned with.)  Where rows are no whole number of 128-byte lines,
+   neighbouring tiles share the lines at their ends, which no figure here counts.  0 if d does not validate or has
+   no elements.  Pure host function. */
 int fq_distill_reads_of_pair(const fq_distill *d);
 fq_status fq_distill_loss(const fq_distill *d, void *workspace, size_t ws_bytes, void *hip_stream);
 /*

@@ -11,7 +11,8 @@ constexpr int kVecBytes = 16;        // one 128-bit global load/store per lane
 constexpr int kChunkVecs = 1280;     // at most this many 128-bit vectors per block (20 KiB)
 constexpr int kWaveChunkVecs = kChunkVecs / (kBlock / 64);   // what one wavefront covers: 320 vectors
 constexpr int kComputeUnits = 256;   // MI355X; used by the host to balance blocks over the chip
-// Up to this many blocks a launch has all of them resident at once (three per compute unit).
+// Three blocks per compute unit: up to here every launch has all its blocks resident at once, whatever its kernel's
+// registers (forward: eight would be; backward: four to eight), and as many on one compute unit as on another.
 constexpr unsigned kResidentBlocks = 3 * kComputeUnits;
 // Backward launches of at most that many blocks take the schedule made for one burst from here on
 // (launch_backward_shaped has the figures): enough blocks and enough of data.

@@ -351,11 +351,14 @@ __device__ __forceinline__ void forward_elem(T x, T *y, int8_t *q, int i, const 
 // one 64-bit (FP16 input) or 32-bit (FP32 input) store.  At least one of the two.
 // G: lanes that share the chunk.
 // EARLY: theta is requested in front of the rows, and all rows have to be there when the scale is.  That is
-// for launches of more blocks than are resident at once, whose blocks then read while others write.
-// Measured on buffers that no cache holds, us, without / with: 512x19200 FP16 (1024 blocks) 8.7 / 8.1, 8x64x19200 FP16
-// (1024) 8.4 / 7.7, 15x128x19200 FP16 (3840) 26.35 / 25.9, 2x384x19200 FP32 (3072) 21.1 / 20.8, 64 mixed tensors of
-// 1 GiB forward + backward 930 / 918; but 384x19200 FP16 (768) 6.4 / 6.7, one scale 2457600 FP16 (240) 3.7 / 4.2, and
-// wavefront units 15x384x1200 FP16 6.99 / 7.07.  (The backward gains nothing by it: 384x19200 FP16 9.1 / 9.8.)
+// for launches of more than three blocks per compute unit, where some compute units get more blocks than others and
+// blocks read while others write.  (Registers would let eight of these blocks reside on a compute unit: what
+// counts is how evenly a launch fills the chip, not whether it has to wait for room.)  Measured on buffers that no cache
+// holds, us, without / with: 780x10240 FP16 (780 blocks) 7.8 / 7.6, 850x9600 (850) 8.0 / 7.7, 512x19200 FP16 (1024) 8.7 /
+// 8.1, 8x64x19200 FP16 (1024) 8.4 / 7.7, 15x128x19200 FP16 (3840) 26.35 / 25.9, 2x384x19200 FP32 (3072) 21.1 / 20.8, 64
+// mixed tensors of 1 GiB forward + backward 930 / 918; but 384x19200 FP16 (768 blocks) 6.4 / 6.7, one scale 2457600 FP16
+// (240) 3.7 / 4.2, and wavefront units 15x384x1200 FP16 6.99 / 7.07.  (The backward gains nothing by it: 384x19200 FP16
+// 9.1 / 9.8.)
 template <typename T, bool WRITE_Y, bool EMIT_Q, int G, int ROWS, bool EARLY>
 __device__ __forceinline__ void forward_chunk(const DevTensor &d, const Chunk &ck)
 {
@@ -563,17 +566,17 @@ __device__ __forceinline__ double backward_chunk(const DevTensor &d, const Chunk
     return sum;
 }
 
-// The same sum with the schedule for launches whose blocks are all resident at once (at most three
-// per compute unit: the 1x384x120x160 FP16 tensor).  Such a launch is one burst: every wavefront asks
+// The same sum with the schedule for launches of at most three blocks per compute unit, all resident at
+// once (the 1x384x120x160 FP16 tensor).  Such a launch is one burst: every wavefront asks
 // for its whole chunk at the start, the data trickles in over the next microseconds, and whatever a
 // wavefront still has to compute after its last row has landed is added to the kernel's duration,
 // with nothing left to hide it.  So all x rows are requested before all gy rows; what depends on x
 // alone (quotient, clip, round, t, the mask: two thirds of the arithmetic) is done as the x rows
 // arrive, while the gy rows are still on their way; only the products and the selects wait for the
 // last row; and gx is stored at the very end, in one run, so that no store sits between the loads
-// in the memory pipeline.  The price is registers (every row's t is kept: 134 VGPRs instead of 71,
-// three wavefronts per SIMD), which costs a large launch more than the schedule gains (a
-// 15x128x120x160 FP16 tensor: 44.5 us instead of 40.7), so larger launches interleave as before.
+// in the memory pipeline.  The price is registers (every row's t is kept: 123 VGPRs instead of 64 for five
+// FP16 rows, four wavefronts per SIMD; 95 and five for FP32), which costs a large launch more than the schedule
+// gains (a 15x128x120x160 FP16 tensor: 44.5 us instead of 40.7), so larger launches interleave as before.
 // The arithmetic and its order are the same in both schedules; so are the bits.
 template <typename T, int GX, int G, int ROWS>
 __device__ __forceinline__ double backward_chunk_short(const DevTensor &d, const Chunk &ck, BlockScale &bs, const int group = G)
@@ -1422,9 +1425,11 @@ static void launch_backward_typed(const DevTensor &d, unsigned blocks, bool fuse
     });
 }
 
-// The burst schedule (backward_chunk_short) pays in launches that are resident at once (at most three
-// blocks per compute unit) and move much data: its arithmetic lies in front of the last loads, but it is
-// more arithmetic and more registers.  Measured against the interleaved schedule, us, burst / interleaved:
+// The burst schedule (backward_chunk_short) pays in launches that are resident at once and move much data: its
+// arithmetic lies in front of the last loads, but it is more arithmetic and more registers.  The line stands at three
+// blocks per compute unit; four FP16 blocks would still be resident, and there it still gains (1024 blocks x 1200
+// vectors 13.3 / 12.9 interleaved / burst, 800 x 1200 11.8 / 11.2), with more than four it loses (1200 x 1200 14.7 / 16.4;
+// FP32 1024 x 1200 no change).  Measured against the interleaved schedule, us, burst / interleaved:
 //   FP16  768 blocks x 1200 vectors 9.2 / 9.65   768 x 1000 7.8 / 8.2   700 x 1200 9.2 / 9.2
 //         600 x 1200 8.7 / 8.3   768 x 800 7.2 / 7.1   768 x 600 6.2 / 5.7   400 x 1200 7.1 / 6.3
 //   FP32  768 x 1200 8.5 / 8.9   512 x 1200 6.2 / 6.5   400 x 1200 5.4 / 5.9   768 x 600 4.95 / 5.3

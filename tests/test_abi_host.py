@@ -108,14 +108,14 @@ def test_workspace_bytes(fq):
     fwd = fq.fq_workspace_bytes(t, 1)
     bwd = fq.fq_workspace_bytes(t, 2)
     assert fwd % 256 == 0 and bwd % 256 == 0 and fwd >= 256
-    # 30 blocks per channel: more than 16, so each channel has 16 first-level ticket slots beside its own
+    # 30 blocks per channel: more than 16, so each channel has 16 reserved slots beside its own
     assert bwd >= fwd + 3840 * 8 + 128 * 17 * 8
     assert bwd <= fwd + 3840 * 8 + 128 * 17 * 8 + 3 * 256
     # one scale for 7 372 800 FP16 elements = 921 600 vectors: 720 blocks of 1280 vectors share the
-    # channel, more than 64, so it gets 32 first-level ticket slots beside its own: 33 slots
+    # channel, more than 64, so it gets 32 reserved slots beside its own: 33 slots
     pt = _desc(fq, outer=1, channels=1, inner=7372800, x=1 << 32, y=2 << 32, gy=3 << 32, gx=4 << 32)
     assert fq.fq_workspace_bytes(pt, 2) == fq.fq_workspace_bytes(pt, 1) + (720 * 8 + 128) + 512
-    # 16 blocks per channel still share one slot; 18 get 16 first-level slots each
+    # 16 blocks per channel have their one slot; 18 get 16 reserved ones each
     few = _desc(fq, outer=8, channels=384, inner=19200, x=1 << 32, y=2 << 32, gy=3 << 32, gx=4 << 32)
     assert fq.fq_workspace_bytes(few, 2) == fq.fq_workspace_bytes(few, 1) + 8 * 384 * 2 * 8 + 384 * 8
     more = _desc(fq, outer=9, channels=384, inner=19200, x=1 << 32, y=2 << 32, gy=3 << 32, gx=4 << 32)
@@ -154,16 +154,17 @@ def _distill(fq, **kw):
 def test_distill_struct_and_workspace(fq):
     assert ctypes.sizeof(fq.FqDistill) == 3 * 8 + 4 * 4 + 4 * 8
     # 384 channels, inner a multiple of 4, aligned: the fused kernel reads the pair once and needs
-    # only per-tile sums (2 doubles per tile of 64 FP16 positions: 300 tiles per image)
+    # only per-tile sums (one launch: 150 tiles of 128 positions, four words each and a flag; the batch: 2
+    # doubles per tile of 64, 300 to an image)
     assert fq.fq_distill_reads_of_pair(_distill(fq)) == 1
     got = fq.fq_distill_workspace_bytes(_distill(fq))
     assert got % 256 == 0 and 300 * 16 <= got < 300 * 16 + 256
     got = fq.fq_distill_workspace_bytes(_distill(fq, n=15))
     assert 15 * 300 * 16 <= got < 15 * 300 * 16 + 256
     assert fq.fq_distill_reads_of_pair(_distill(fq, gstudent=None)) == 1
-    # more channels than a lane's registers hold (or inner not in whole quads, or pointers off the
-    # quad's alignment): statistics kernel + gradient kernel, coefficients (2 doubles per position)
-    # + per-tile sums (2 doubles per tile of 64 x 2 positions: 150 tiles of 128 positions)
+    # more channels than a lane's registers hold: statistics kernel + gradient kernel, coefficients (2
+    # doubles per position) + per-tile sums (2 doubles per tile of 64 x 2 positions: 150 tiles of 128
+    # positions); inner not in whole quads, or pointers off the quad's alignment: the same bound
     for kw in (dict(channels=520), dict(inner=19202), dict(student=0x10000002)):
         assert fq.fq_distill_reads_of_pair(_distill(fq, **kw)) == 2
         assert fq.fq_distill_reads_of_pair(_distill(fq, gstudent=None, **kw)) == 1
@@ -238,10 +239,10 @@ def test_layout_info(fq):
     # a 188 x 120 map: four blocks per channel, the exchange tree with its two pair slots
     i = fq.fq_layout(_desc(fq, outer=1, channels=384, inner=22560, **big))
     assert (i.units_per_channel, i.wave_units, i.extra_slots) == (4, 0, 2)
-    # 15 frames: 30 blocks per channel, two-level tickets with 16 first-level slots
+    # 15 frames: 30 blocks per channel, gathered, with 16 reserved slots
     i = fq.fq_layout(_desc(fq, outer=15, channels=128, inner=19200, **big))
     assert (i.blocks, i.units_per_channel, i.extra_slots) == (3840, 30, 16)
-    # one scale for everything: 720 blocks, 32 first-level slots
+    # one scale for everything: 720 blocks, 32 reserved slots
     i = fq.fq_layout(_desc(fq, outer=1, channels=1, inner=7372800, **big))
     assert (i.blocks, i.units_per_channel, i.extra_slots) == (720, 720, 32)
     # short slabs: a wavefront per slab (30 x 40 FP16 = 150 vectors), units per channel = outer

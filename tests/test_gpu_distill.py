@@ -60,8 +60,8 @@ def _run(a, b, lam, oracle, eps=1e-8, upstream=1.0, want_grad=True, inplace=None
     need = fq.fq_distill_workspace_bytes(d)
     assert need >= 256 and need % 256 == 0
     if a.size:
-        # which way the library takes is a function of shape and alignment: one fused kernel that
-        # reads the pair once, or a statistics kernel followed by a gradient kernel
+        # the bound on the passes is a function of shape and alignment: 1 on the 4-element grid where the
+        # fused kernel holds the channels
         rows = 32 if a.dtype == np.float16 else 64
         fused = (m % 4 == 0 and (misalign * a.itemsize) % (4 * a.itemsize) == 0 and
                  -(-c // rows) <= (16 if a.dtype == np.float16 else 8))

@@ -261,7 +261,7 @@ def test_empty_tensors():
 
 def test_backward_is_bitwise_reproducible():
     """Same inputs, same workspace, repeated calls: identical bits every time (no float atomics;
-    the ticket counters must come back to zero or the second call would not finish its sums)."""
+    partial sums and slots must come back to zero or the second call would take them for its own)."""
     case = workloads.train_batch_fp16(shape=(3, 16, 120, 160))[0]
     H.say("run-twice determinism, fused and two-pass")
     first = None

@@ -1,5 +1,5 @@
 """Repeat the backward pass many times on one workspace: the cross-block combination (atomic
-exchange for two blocks per channel, tickets for more) must hand every channel's finisher the
+exchange for two to four blocks per channel, sums gathered by the last for more) must hand every channel's finisher the
 other blocks' sums of THIS launch.  Two cases of the same shape but different upstream gradients
 take turns on the workspace, so a partial sum left over from the launch before belongs to the
 other case and would change bits; outputs are poisoned before every launch and compared on the
@@ -61,7 +61,7 @@ def test_two_blocks_per_channel_exchange():
 
 def test_many_blocks_per_channel_tickets():
     case = workloads.train_batch_fp16(shape=(6, 64, 120, 160))[0]   # 64 channels x 12 blocks
-    _repeat(case, "stress/tickets", 200)
+    _repeat(case, "stress/gathered", 200)
 
 
 def test_one_channel_many_blocks():
@@ -110,7 +110,7 @@ def _protocol_case(dtype, outer, channels, inner, units, waves, extra, iters=3):
                                           (40, 16), (66, 16), (130, 16), (256, 16), (257, 32), (300, 32)])
 def test_wavefront_units_every_protocol(outer, extra):
     """Short slabs (40 FP16 elements) and thousands of them: one wavefront per slab, so a channel
-    has exactly `outer` units: direct write, exchange, exchange tree, tickets, two-level tickets."""
+    has exactly `outer` units: direct write, exchange, exchange tree, gathered sums (from 17 units on with reserved slots)."""
     _protocol_case(np.float16, outer, 4100, 40, outer, 1, extra, iters=2)
 
 
@@ -118,9 +118,9 @@ def test_wavefront_units_every_protocol(outer, extra):
     (np.float16, 1, 19200, 2, 0),        # the headline layout: exchange
     (np.float16, 1, 28800, 3, 2),        # exchange tree, three blocks
     (np.float16, 1, 22560, 4, 2),        # exchange tree, four blocks
-    (np.float32, 1, 9600 * 3, 6, 0),     # tickets on one slot
-    (np.float16, 8, 19200, 16, 0),       # the last count that shares one slot
-    (np.float16, 9, 19200, 18, 16),      # two-level tickets
+    (np.float32, 1, 9600 * 3, 6, 0),     # gathered
+    (np.float16, 8, 19200, 16, 0),       # the last count without reserved slots
+    (np.float16, 9, 19200, 18, 16),      # the first with them
 ])
 def test_block_units_every_protocol(dtype, outer, inner, units, extra):
     _protocol_case(dtype, outer, 384, inner, units, 0, extra, iters=2)
@@ -150,8 +150,8 @@ def test_one_workspace_serves_lists_of_other_shapes_after_zeroing():
         theta = workloads.theta_for_scale(rng.uniform(0.02, 0.05, channels))
         return workloads.TensorCase("reuse", x.shape, outer, channels, inner, -128, 127, x, theta, gy)
 
-    # tickets on many partial sums, then an exchange layout whose slots lie where those sums were,
-    # then two-level tickets, then the first one again
+    # many gathered sums, then an exchange layout whose slots lie where those sums were, then one channel
+    # with many gathered sums, then the first one again
     cases = [case(6, 48, 19200, np.float16), case(1, 384, 19200, np.float16), case(1, 1, 97 * 5120 + 13, np.float32)]
     cases.append(cases[0])
     dcs = [H.DeviceCase(c, want_q=False) for c in cases]
@@ -169,9 +169,9 @@ def test_one_workspace_serves_lists_of_other_shapes_after_zeroing():
 
 def test_calls_on_two_streams_with_a_workspace_each():
     """Two streams, each with its own tensors and workspace, launching at the same time: calls
-    that do not share a workspace do not disturb each other (forward and backward, tickets on one
-    stream, exchange on the other)."""
-    a = workloads.train_batch_fp16(shape=(4, 32, 120, 160))[0]      # 8 blocks per channel: tickets
+    that do not share a workspace do not disturb each other (forward and backward, gathered
+    sums on one stream, exchange on the other)."""
+    a = workloads.train_batch_fp16(shape=(4, 32, 120, 160))[0]      # 8 blocks per channel: gathered
     b = workloads.make("feature_fp16_per_channel")[0]               # 2 blocks per channel: exchange
     want = []
     for c in (a, b):

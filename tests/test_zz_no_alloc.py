@@ -1,7 +1,7 @@
 """fq_backward_static (the backward whose partial sums and slots live in the library's built-in
 scratch array, for callers that cannot allocate) against fq_backward with a caller's workspace:
 same bits in gx, gs, gtheta and s, on calls in a row that share the one array -- a large tensor
-first (tickets in two levels), then smaller ones with other protocols (exchange, exchange tree,
+first (gathered sums), then smaller ones with other protocols (exchange, exchange tree,
 one unit per channel, two launches), then the large one again."""
 import numpy as np
 import pytest
@@ -44,7 +44,7 @@ def _both(case, label, flags=0):
 
 
 def test_static_backward_equals_workspace_backward_on_calls_in_a_row():
-    big = _case(np.float16, 9, 96, 19200, 41)          # 18 units per channel: two-level tickets
+    big = _case(np.float16, 9, 96, 19200, 41)          # 18 units per channel: gathered
     ref, info = _both(big, "first, large")
     assert info.units_per_channel == 18 and info.extra_slots == 16
     s, active, _, _ = H.oracle_forward(big)
@@ -52,7 +52,7 @@ def test_static_backward_equals_workspace_backward_on_calls_in_a_row():
     small = _case(np.float16, 1, 384, 19200, 42)       # 2 units per channel: exchange
     _, info = _both(small, "second, smaller")
     assert info.units_per_channel == 2
-    _, info = _both(_case(np.float32, 1, 384, 28800, 43), "tickets on one slot")
+    _, info = _both(_case(np.float32, 1, 384, 28800, 43), "gathered, no reserved slots")
     assert info.units_per_channel == 6 and info.extra_slots == 0
     _, info = _both(_case(np.float16, 1, 384, 28800, 44), "exchange tree")
     assert info.units_per_channel == 3 and info.extra_slots == 2
