@@ -813,8 +813,8 @@ fq_status make_plan(const fq_distill *d, Plan &pl)
         // 3x134x6588: 13.6 / 14.3, 5x134x4800: 11.7 / 12.9, without a gradient 10.0 / 10.4 and 9.3 / 9.7; its registers
         // let a compute unit hold 4, 3 or 2 narrow tiles, 2 or 1 wide ones).
         // (Known loss: such launches with a gradient and 150 to 400 channels, 2x200x9600 13.5 -> 14.3, 1x160x23040 13.8 ->
-        // 14.7, 150x384x96 15.5 -> 16.6 since the rows are added by lane exchanges.  The faster sum lets the first tiles'
-        // stores fall among the others' loads: without a gradient the same pairs went 11.5 -> 10.6, and waiting in front
+        // 14.7, 150x384x96 15.5 -> 16.6 since the rows are added by lane exchanges.  It looks as if the faster sum let the
+        // first tiles' stores fall among the others' loads: without a gradient the same pairs went 11.5 -> 10.6, and waiting in front
         // of the stores, or storing without the non-temporal hint, gains 7 % on some of them and loses as much on others.)
         // Nor where the last wide tile of an image is half empty and images are short: on the grid if more than a
         // sixteenth of the wide tiles' positions lie behind the image (400x128x96 15.3 / 17.2, 150x384x288 37.6 / 40.6,
