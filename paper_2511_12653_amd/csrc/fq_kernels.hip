@@ -489,8 +489,30 @@ __device__ __forceinline__ double backward_elem(T x, T g, T *gx, int i, const QP
 // time only.
 enum { kGxNo = 0, kGxYes = 1, kGxAsked = 2 };
 
-template <typename T, int GX, int G, int ROWS>
-__device__ __forceinline__ double backward_chunk(const DevTensor &d, const Chunk &ck, BlockScale &bs, const int group = G)
+// The vectors of gx that a lane has worked out and not stored yet (bit patterns of either type).
+template <int ROWS> struct GxRows {
+    typedef unsigned Bits __attribute__((ext_vector_type(4)));
+    Bits v[ROWS];
+    Bits *to;                  // nullptr: gx is not written
+    int nvec, first, step;     // vector u of this lane is the chunk's (u * step + first)-th, if below nvec
+
+    __device__ __forceinline__ void store() const
+    {
+        if (!to) return;
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            const int i = u * step + first;
+            if (i < nvec) st_stream(to + i, v[u]);
+        }
+    }
+};
+template <> struct GxRows<0> {         // gx is stored row by row, where it is worked out
+    typedef unsigned Bits __attribute__((ext_vector_type(4)));
+};
+
+template <typename T, int GX, int G, int ROWS, int HELD>
+__device__ __forceinline__ double backward_chunk(const DevTensor &d, const Chunk &ck, BlockScale &bs, GxRows<HELD> &out,
+                                                 const int group = G)
 {
     typedef typename VecOf<T>::type VT;
     constexpr int N = VecOf<T>::N;
@@ -549,8 +571,15 @@ __device__ __forceinline__ double backward_chunk(const DevTensor &d, const Chunk
                 any_nan |= is_nan;
             }
             if (any_nan) acc[u] = __builtin_nan("");   // a NaN quotient poisons its channel
-            if (WRITE_GX) st_stream(ov + v, o);
+            if constexpr (HELD != 0) out.v[u] = __builtin_bit_cast(typename GxRows<HELD>::Bits, o);
+            else if (WRITE_GX) st_stream(ov + v, o);
         }
+    }
+    if constexpr (HELD != 0) {
+        out.to = (typename GxRows<HELD>::Bits *)ov;
+        out.nvec = nvec;
+        out.first = tid;
+        out.step = group;
     }
 
     double sum = 0.0;
@@ -573,13 +602,12 @@ __device__ __forceinline__ double backward_chunk(const DevTensor &d, const Chunk
 // with nothing left to hide it.  So all x rows are requested before all gy rows; what depends on x
 // alone (quotient, clip, round, t, the mask: two thirds of the arithmetic) is done as the x rows
 // arrive, while the gy rows are still on their way; only the products and the selects wait for the
-// last row; and gx is stored at the very end, in one run, so that no store sits between the loads
-// in the memory pipeline.  The price is registers (every row's t is kept: 123 VGPRs instead of 64 for five
-// FP16 rows, four wavefronts per SIMD; 95 and five for FP32), which costs a large launch more than the schedule
-// gains (a 15x128x120x160 FP16 tensor: 44.5 us instead of 40.7), so larger launches interleave as before.
+// last row.  The price is registers (every row's t is kept: 124 VGPRs instead of 67 for five
+// FP16 rows, four wavefronts per SIMD; 86 and five for FP32), so larger launches interleave.
 // The arithmetic and its order are the same in both schedules; so are the bits.
 template <typename T, int GX, int G, int ROWS>
-__device__ __forceinline__ double backward_chunk_short(const DevTensor &d, const Chunk &ck, BlockScale &bs, const int group = G)
+__device__ __forceinline__ double backward_chunk_short(const DevTensor &d, const Chunk &ck, BlockScale &bs, GxRows<ROWS> &out,
+                                                       const int group = G)
 {
     constexpr bool WRITE_GX = GX == kGxYes;
     typedef typename VecOf<T>::type VT;
@@ -655,17 +683,14 @@ __device__ __forceinline__ double backward_chunk_short(const DevTensor &d, const
                     acc[u] = __builtin_fma((double)(float)rg[u][e], (double)t[u][e], acc[u]);
                 }
                 if (nan_row[u]) acc[u] = __builtin_nan("");   // a NaN quotient poisons its channel
-                rg[u] = o;
-            }
-        }
-        if (WRITE_GX) {
-#pragma unroll
-            for (int u = 0; u < ROWS; ++u) {
-                const int v = u * group + tid;
-                if (v < nvec) st_stream(ov + v, rg[u]);
+                out.v[u] = __builtin_bit_cast(typename GxRows<ROWS>::Bits, o);
             }
         }
     }
+    out.to = (typename GxRows<ROWS>::Bits *)ov;
+    out.nvec = nvec;
+    out.first = tid;
+    out.step = group;
 
     double sum = 0.0;
 #pragma unroll
@@ -717,10 +742,16 @@ __device__ __forceinline__ unsigned long long bits_of(double v) { return __built
 // A published sum differs from an empty (all zero) place: +0.0 travels as -0.0, which adds the same.
 __device__ __forceinline__ double published(double v) { return bits_of(v) == 0ull ? -0.0 : v; }
 
-// This thread's share of the partial sums of channel c, for a block: thread t adds the sums t, t+256,
-// t+512, ... in that order, eight loads in flight.  looks > 0: a sum that is still zero is not published yet;
-// the wavefront then looks at those eight rows again, and gives up (false) when it has looked in vain that
-// often in all.  own >= 0: unit `own` is the caller's; its sum is `mine`, not in memory.
+// Up to this many units a channel's sums are added by one wavefront, lane l taking the sums l, l + 64, ... (at
+// most four) in that order and wave_sum adding the lanes; beyond it by a block, thread t taking t, t + 256, ....
+// A block that polls 150 to 240 sums with all its wavefronts and meets at a barrier afterwards is slower by 0.2 to
+// 0.4 us (8x64x19200 FP16, 16 units: 12.65 / 12.25; 3x134x6588 FP32, 6 units: 8.93 / 8.50).
+constexpr unsigned kWaveGather = 256;
+
+// This thread's share of the partial sums of channel c, for a block (more than kWaveGather units): thread t adds the
+// sums t, t+256, t+512, ... in that order, eight loads in flight.  looks > 0: a sum that is still zero is not
+// published yet; the wavefront then looks at those eight rows again, and gives up (false) when it has looked in vain
+// that often in all.  own >= 0: unit `own` is the caller's; its sum is `mine`, not in memory.
 __device__ __forceinline__ bool add_partials_block(const DevTensor &d, unsigned c, unsigned own, double mine,
                                                    unsigned looks, double &acc)
 {
@@ -767,25 +798,6 @@ __device__ __forceinline__ void clear_partials(const DevTensor &d, unsigned c)
         __hip_atomic_store(&parts[j], 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Second launch of the two-launch mode: the sum of all partial sums of channel c (thread-strided
-// binary64 sums, fixed tree), the channel's gradients, and the partial sums back to zero.
-// Block-wide; lds holds kBlock/64 doubles.
-__device__ __forceinline__ void finalize_channel(const DevTensor &d, unsigned c, const BlockScale &bs, double *lds)
-{
-    double acc;
-    add_partials_block(d, c, ~0u, 0.0, 0u, acc);
-    acc = wave_sum(acc);
-    clear_partials<kBlock>(d, c);
-    if ((threadIdx.x & 63) == kSumLane) lds[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double total = 0.0;
-#pragma unroll
-        for (int w = 0; w < kBlock / 64; ++w) total += lds[w];
-        write_channel_grads(d, c, total, bs);
-    }
-}
-
 // value of v in the given lane, as a wavefront-uniform scalar
 __device__ __forceinline__ double read_lane(double v, int lane)
 {
@@ -795,16 +807,19 @@ __device__ __forceinline__ double read_lane(double v, int lane)
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
-// The same sum, bit for bit, by a single wavefront: the block-wide version gives thread t the sums
-// t, t+256, ... and adds wavefront 0's tree to wavefront 1's, 2's and 3's in that order; here the
-// one wavefront plays the four, 256 sums in flight (4000x4x100 FP32, 4000 units per channel: 30.8 us with one
-// row of 64 at a time, 22.1 now).  looks (at least 1) as above.
+// The sum of channel c's partial sums by a single wavefront: the way of up to kWaveGather units, and beyond
+// that the block's, bit for bit: the block-wide version gives thread t the sums t, t+256, ... and adds wavefront 0's
+// tree to wavefront 1's, 2's and 3's in that order; here the one wavefront plays the four, 256 sums in flight
+// (4000x4x100 FP32, 4000 units per channel: 30.8 us with one row of 64 at a time, 22.1 now).  looks and own as above.
+// clear: put the sums back to zero as soon as they are all here (up to kWaveGather units; `own' was never there).
 __device__ __forceinline__ bool add_partials_wave(const DevTensor &d, unsigned c, unsigned own, double mine,
-                                                  unsigned looks, double &total)
+                                                  unsigned looks, bool clear, double &total)
 {
     constexpr unsigned kWaves = kBlock / 64;
+    static_assert(kWaveGather == kWaves * 64, "one batch of four loads per lane");
     const unsigned bpc = d.outer * d.cps;
     const unsigned lane = threadIdx.x & 63;
+    const bool wait = looks != 0u;
     double *const parts = partials_of(d, c);
     if (bpc <= 64u) {                              // the usual case, in less code (5x1500x72 FP16 7.5 us instead of 7.7)
         double part = mine;
@@ -812,9 +827,10 @@ __device__ __forceinline__ bool add_partials_wave(const DevTensor &d, unsigned c
             order_accesses();
             if (lane < bpc && lane != own)
                 part = __hip_atomic_load(&parts[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (__builtin_amdgcn_ballot_w64(lane < bpc && lane != own && bits_of(part) == 0ull) == 0ull) break;
+            if (!wait || __builtin_amdgcn_ballot_w64(lane < bpc && lane != own && bits_of(part) == 0ull) == 0ull) break;
             if (--looks == 0u) return false;
         }
+        if (clear && lane < bpc) st_global(&parts[lane], 0.0);
         double one = 0.0;
         if (lane < bpc) one += part;
         total = 0.0 + read_lane(wave_sum(one), kSumLane);
@@ -840,8 +856,19 @@ __device__ __forceinline__ bool add_partials_wave(const DevTensor &d, unsigned c
                 const unsigned j = first + w * 64 + lane;
                 if (j < bpc && j != own) here = here && bits_of(part[w]) != 0ull;
             }
-            if (__builtin_amdgcn_ballot_w64(!here) == 0ull) break;
+            if (!wait || __builtin_amdgcn_ballot_w64(!here) == 0ull) break;
             if (--looks == 0u) return false;
+        }
+        if (bpc <= kWaveGather) {
+            double one = 0.0;
+#pragma unroll
+            for (unsigned w = 0; w < kWaves; ++w) {
+                const unsigned j = w * 64 + lane;
+                if (clear && j < bpc) st_global(&parts[j], 0.0);
+                if (j < bpc) one += part[w];
+            }
+            total = 0.0 + read_lane(wave_sum(one), kSumLane);
+            return true;
         }
 #pragma unroll
         for (unsigned w = 0; w < kWaves; ++w)
@@ -849,9 +876,29 @@ __device__ __forceinline__ bool add_partials_wave(const DevTensor &d, unsigned c
     }
     total = 0.0;
 #pragma unroll
-    for (unsigned w = 0; w < kWaves; ++w)
-        if (w * 64 < bpc) total += read_lane(wave_sum(acc[w]), kSumLane);      // (an empty one would add +0.0)
+    for (unsigned w = 0; w < kWaves; ++w) total += read_lane(wave_sum(acc[w]), kSumLane);
     return true;
+}
+
+// Second launch of the two-launch mode: the sum of all partial sums of channel c, the channel's gradients, and the
+// partial sums back to zero.  Block-wide; lds holds kBlock/64 doubles.
+__device__ __forceinline__ void finalize_channel(const DevTensor &d, unsigned c, const BlockScale &bs, double *lds)
+{
+    double total = 0.0;
+    if (d.outer * d.cps <= kWaveGather) {
+        if (threadIdx.x >= 64) return;
+        add_partials_wave(d, c, ~0u, 0.0, 0u, true, total);
+    } else {
+        double acc;
+        add_partials_block(d, c, ~0u, 0.0, 0u, acc);
+        acc = wave_sum(acc);
+        clear_partials<kBlock>(d, c);
+        if ((threadIdx.x & 63) == kSumLane) lds[threadIdx.x >> 6] = acc;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) total += lds[w];
+    }
+    if (threadIdx.x == 0) write_channel_grads(d, c, total, bs);
 }
 
 // How the units (blocks, or wavefronts of short-slab tensors) of a channel combine their sums
@@ -866,19 +913,25 @@ __device__ __forceinline__ bool add_partials_wave(const DevTensor &d, unsigned c
 // Slots and partial sums are zero between calls.
 // Without FUSED the sums are only stored and finalize_kernel adds them in a second launch.
 //
-// Called by one lane per unit with the unit's total, for up to kTreeBlocks units per channel and
-// without FUSED.
-template <bool FUSED>
-__device__ __forceinline__ void combine(const DevTensor &d, const Chunk &ck, double total, const BlockScale &bs)
+// Called by one wavefront per unit with the unit's total, for up to kTreeBlocks units per channel and
+// without FUSED; its first lane does the work.  store_gx: what the wavefront still has to store, behind the exchange.
+template <bool FUSED, typename F>
+__device__ __forceinline__ void combine(const DevTensor &d, const Chunk &ck, double total, const BlockScale &bs, F store_gx)
 {
     const unsigned bpc = d.outer * d.cps;
-    if (!FUSED) {
-        __hip_atomic_store(&partials_of(d, ck.channel)[ck.j], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else if (bpc == 1u) {
-        write_channel_grads(d, ck.channel, total, bs);
+    const bool first_lane = (threadIdx.x & 63) == 0;
+    if (!FUSED || bpc == 1u) {
+        if (first_lane) {
+            if (FUSED) write_channel_grads(d, ck.channel, total, bs);
+            else __hip_atomic_store(&partials_of(d, ck.channel)[ck.j], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        store_gx();
     } else if (bpc == 2u) {
-        const unsigned long long theirs = __hip_atomic_exchange(&d.slot[ck.channel], bits_of(published(total)),
-                                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        unsigned long long theirs = 0ull;
+        if (first_lane)
+            theirs = __hip_atomic_exchange(&d.slot[ck.channel], bits_of(published(total)), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+        store_gx();
         if (theirs != 0ull) {
             __hip_atomic_store(&d.slot[ck.channel], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const double both = (__builtin_bit_cast(double, theirs) + total) + 0.0;
@@ -889,24 +942,23 @@ __device__ __forceinline__ void combine(const DevTensor &d, const Chunk &ck, dou
         // associates its sums, (p0 + p1) + (p2 + p3) with an absent p3 counting as +0.0, so the
         // bits equal those of the two-launch mode.
         const unsigned j = ck.j;
-        double pair_sum = total + 0.0;                 // unit 2 of 3 has no partner
-        bool carry_on = true;
-        if (!(bpc == 3u && j == 2u)) {
-            unsigned long long *pair = d.slot + d.channels + (size_t)ck.channel * 2u + (j >> 1);
-            const unsigned long long theirs = __hip_atomic_exchange(pair, bits_of(published(total)), __ATOMIC_RELAXED,
-                                                                    __HIP_MEMORY_SCOPE_AGENT);
-            carry_on = theirs != 0ull;
-            if (carry_on) {
-                __hip_atomic_store(pair, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                pair_sum = __builtin_bit_cast(double, theirs) + total;
-            }
+        const bool paired = !(bpc == 3u && j == 2u);   // unit 2 of 3 has no partner
+        unsigned long long *pair = d.slot + d.channels + (size_t)ck.channel * 2u + (j >> 1);
+        unsigned long long theirs = 0ull;
+        if (first_lane && paired)
+            theirs = __hip_atomic_exchange(pair, bits_of(published(total)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        store_gx();
+        double pair_sum = total + 0.0;
+        if (theirs != 0ull) {
+            __hip_atomic_store(pair, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            pair_sum = __builtin_bit_cast(double, theirs) + total;
         }
-        if (carry_on) {
-            const unsigned long long theirs = __hip_atomic_exchange(&d.slot[ck.channel], bits_of(published(pair_sum)),
+        if (first_lane && (theirs != 0ull || !paired)) {
+            const unsigned long long others = __hip_atomic_exchange(&d.slot[ck.channel], bits_of(published(pair_sum)),
                                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (theirs != 0ull) {
+            if (others != 0ull) {
                 __hip_atomic_store(&d.slot[ck.channel], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const double all = (__builtin_bit_cast(double, theirs) + pair_sum) + 0.0;
+                const double all = (__builtin_bit_cast(double, others) + pair_sum) + 0.0;
                 write_channel_grads(d, ck.channel, all, bs);
             }
         }
@@ -916,13 +968,15 @@ __device__ __forceinline__ void combine(const DevTensor &d, const Chunk &ck, dou
 // More than kTreeBlocks units per channel.  What bounds the end of such a launch is the number of
 // dependent trips to memory behind the last unit's sum, about 0.5 us each: with arrival tickets there
 // were four (store acknowledged, first-level ticket, top ticket, sums re-read).  Here there are two: the
-// unit's sum reaches memory, and the collector, which is polling the channel's sums (eight per thread and
-// trip, in order: what it has added it does not read again), sees it.  A sum announces itself: its place was zero and a published sum never is.  A channel's
-// sums lie next to each other, so a trip is one or two cache lines.  Measured against the tickets (graph
-// of back-to-back launches): one scale, 153600 FP32 elements in 150 units 6.0 -> 4.7 us; 2457600 FP16 in
-// 240 units 7.9 -> 6.4; 39321600 FP16 in 3840 units 44.4 -> 43.0; 15x128x19200 FP16, 30 units per channel
-// 40.1 -> 39.8; 15x384x1200 FP16, 15 wavefront units 11.9 -> 11.5.  Waiting between the rounds (s_sleep
-// 4, 20) is no faster (4.7, 4.7 and 6.7, 6.9 us on the first two).
+// unit's sum reaches memory, and the collector, which is polling the channel's sums (up to four per lane of one
+// wavefront, beyond kWaveGather units eight per thread of the block, where what has been added is not read again),
+// sees it.  A sum announces itself: its place was zero and a published sum never is.  A channel's sums lie next to
+// each other, so a trip is one or two cache lines.  What it takes (stamps of the clock in the blocks, one scale, 921600
+// FP16 in 225 units, us): loads requested 0.1, scale there 0.6, last row done 1.4, last sum published 1.6, seen by the
+// collector 2.3, added 2.4 (2.75 while four wavefronts' trees were added apart), gradients in memory 3.
+// Measured, back to back, with tickets / polled by the whole block with gx in front / now: one scale, 153600 FP32 in
+// 150 units 6.0 / 4.4 / 3.8; 2457600 FP16 in 240 units 7.9 / 6.2 / 5.5; 39321600 FP16 in 3840 units 44.4 / 42.8 / 40.7;
+// 15x128x19200 FP16, 30 units per channel 40.1 / 39.9 / 37.6; 15x384x1200 FP16, 15 wavefront units 11.9 / 11.3 / 9.8.
 //
 // No wait is without end and nothing rests on the order in which blocks are dispatched: beside the one pass
 // that the adding takes anyhow, the collector looks at most kPollRounds times in vain (a few tens of
@@ -935,12 +989,16 @@ __device__ __forceinline__ void combine(const DevTensor &d, const Chunk &ck, dou
 constexpr unsigned long long kGivenUp = 1ull, kClaimed = 2ull;
 constexpr unsigned kPollRounds = 32;
 
+// (Tried and slower, one scale, 921600 FP16 in 225 units, 5.1 us at the time: looks in flight side by side, two 6.6,
+// four 8.0, because they hold up the sums that are on their way to the same lines; reading again only what was
+// missing 5.2; a sum per cache line 5.0 to 5.25, but 6.6 instead of 6.2 for 2457600; sums of one XCD next to each other 5.3.)
+
 // The flag is up: one wavefront looks at all sums (`own`: none, all are in memory) and finishes the
 // channel if they are complete and no other unit has claimed it.
 __device__ __forceinline__ void finish_if_complete(const DevTensor &d, unsigned c, const BlockScale &bs)
 {
     double total;
-    if (!add_partials_wave(d, c, ~0u, 0.0, 1u, total)) return;
+    if (!add_partials_wave(d, c, ~0u, 0.0, 1u, false, total)) return;
     unsigned won = 0u;
     if ((threadIdx.x & 63) == 0) {
         unsigned long long expected = kGivenUp;
@@ -961,11 +1019,14 @@ __device__ __forceinline__ void finish_if_complete(const DevTensor &d, unsigned 
 // Stores count in vmcnt on this target and an agent-scope store is acknowledged only once it has reached
 // that level, so after s_waitcnt vmcnt(0) the sum is visible to every XCD, and the flag is read after
 // that.  A release fence at agent scope would give the same order but also write back the whole L2.
-__device__ __forceinline__ void publish(const DevTensor &d, const Chunk &ck, double total, const BlockScale &bs)
+template <typename F>
+__device__ __forceinline__ void publish(const DevTensor &d, const Chunk &ck, double total, const BlockScale &bs, F store_gx)
 {
     if ((threadIdx.x & 63) == 0)
         __hip_atomic_store(&partials_of(d, ck.channel)[ck.j], published(total), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
+    order_accesses();
+    store_gx();
     wait_stores_acknowledged();
     const unsigned long long flag = __hip_atomic_load(&d.slot[ck.channel], __ATOMIC_RELAXED,
                                                       __HIP_MEMORY_SCOPE_AGENT);
@@ -986,10 +1047,17 @@ __device__ __forceinline__ void give_up(const DevTensor &d, const Chunk &ck, dou
     finish_if_complete(d, ck.channel, bs);
 }
 
-// What follows the chunk of a block: the block's sum, and its combination with the channel's others.
-// FEW: the launch has no channel whose sums are gathered.
-template <bool FUSED, bool FEW>
-__device__ __forceinline__ void combine_block(const DevTensor &d, const Chunk &ck, double sum, const BlockScale &bs)
+// What follows the chunk of a block: the block's sum, its combination with the channel's others, and gx.
+// FEW: the launch has no channel whose sums are gathered.  store_gx stores this thread's rows of gx.
+//
+// The sum goes out in front of gx, whose stores would otherwise lie ahead of it in the memory pipeline; the
+// exchange or the gathering then runs while they drain.  Measured with gx in front of the sum / behind it, us:
+// 15x128x19200 FP16 39.9 / 38.05, 1x384x19200 FP16 9.3 / 8.95, 8x64x19200 FP16 13.7 / 12.8, 15x384x1200 FP16 (wavefront
+// units) 11.35 / 10.25, 3x131x4819 FP16 5.9 / 5.5, 1x1x4915200 FP16 9.0 / 8.2, 384x3456 FP32 5.2 / 4.8.  The collector
+// stores its own gx in front of the first look, which would come too early otherwise (one scale, 921600 FP16:
+// 4.8 / 4.5), and which leaves the registers to the sums.
+template <bool FUSED, bool FEW, typename F>
+__device__ __forceinline__ void combine_block(const DevTensor &d, const Chunk &ck, double sum, const BlockScale &bs, F store_gx)
 {
     __shared__ double wave_part[kBlock / 64];
     __shared__ double fin_part[kBlock / 64];
@@ -1002,21 +1070,38 @@ __device__ __forceinline__ void combine_block(const DevTensor &d, const Chunk &c
     const bool gathered = FUSED && !FEW && bpc > kTreeBlocks;
     // the channel's last unit in index order: normally dispatched after the others
     const bool collector = gathered && ck.j + 1u == bpc;
-    if (!collector && threadIdx.x >= (gathered ? 64u : 1u)) return;
+    if (threadIdx.x >= 64 && !(collector && bpc > kWaveGather)) {
+        store_gx();
+        return;
+    }
     double total = 0.0;
 #pragma unroll
     for (int w = 0; w < kBlock / 64; ++w) total += wave_part[w];
     if (!gathered) {
-        combine<FUSED>(d, ck, total, bs);
+        combine<FUSED>(d, ck, total, bs, store_gx);
         return;
     }
     if (!collector) {
-        publish(d, ck, total, bs);
+        publish(d, ck, total, bs, store_gx);
+        return;
+    }
+    store_gx();
+    const unsigned looks = d.flags & 4u ? 0u : kPollRounds;       // FQ_FLAG_NO_POLL
+    if (bpc <= kWaveGather) {
+        double all = 0.0;
+        // A look costs about 0.5 us, and one that comes too early costs that for nothing.  Many units of one channel
+        // end together, so the first look waits 0.2 us for their sums (us, without / with: 921600 FP16, 225 units, 4.45 /
+        // 4.18, 2457600 FP16, 240 units, 5.98 / 5.60); few units of many channels don't (3x134x6588 FP32, 6 units, 8.2 / 8.4).
+        if (bpc > 64u) __builtin_amdgcn_s_sleep(8);
+        if (looks && add_partials_wave(d, ck.channel, bpc - 1u, total, looks, true, all)) {
+            if (threadIdx.x == 0) write_channel_grads(d, ck.channel, all, bs);
+        } else {
+            give_up(d, ck, total, bs);
+        }
         return;
     }
     double acc = 0.0;
-    const bool present = !(d.flags & 4u) &&                       // FQ_FLAG_NO_POLL
-                         add_partials_block(d, ck.channel, bpc - 1u, total, kPollRounds, acc);
+    const bool present = looks && add_partials_block(d, ck.channel, bpc - 1u, total, looks, acc);
     acc = wave_sum(acc);
     if ((threadIdx.x & 63) == kSumLane) {
         fin_part[threadIdx.x >> 6] = acc;
@@ -1039,28 +1124,29 @@ __device__ __forceinline__ void combine_block(const DevTensor &d, const Chunk &c
 }
 
 // The same for a unit that is a wavefront: the block never meets at a barrier.
-template <bool FUSED>
-__device__ __forceinline__ void combine_wave(const DevTensor &d, const Chunk &ck, double sum, const BlockScale &bs)
+template <bool FUSED, typename F>
+__device__ __forceinline__ void combine_wave(const DevTensor &d, const Chunk &ck, double sum, const BlockScale &bs, F store_gx)
 {
     const double total = read_lane(wave_sum(sum), kSumLane);
     const unsigned bpc = d.outer * d.cps;
     if (!FUSED || bpc <= kTreeBlocks) {
-        if ((threadIdx.x & 63) == 0) combine<FUSED>(d, ck, total, bs);
+        combine<FUSED>(d, ck, total, bs, store_gx);
         return;
     }
     if (ck.j + 1u != bpc) {
-        publish(d, ck, total, bs);
+        publish(d, ck, total, bs, store_gx);
         return;
     }
+    store_gx();
     double all = 0.0;
     const bool present = !(d.flags & 4u) &&                       // FQ_FLAG_NO_POLL
-                         add_partials_wave(d, ck.channel, bpc - 1u, total, kPollRounds, all);
+                         add_partials_wave(d, ck.channel, bpc - 1u, total, kPollRounds, true, all);
     if (__builtin_expect(!present, 0)) {
         give_up(d, ck, total, bs);
         return;
     }
     if ((threadIdx.x & 63) == 0) write_channel_grads(d, ck.channel, all, bs);
-    clear_partials<64>(d, ck.channel);
+    if (bpc > kWaveGather) clear_partials<64>(d, ck.channel);
 }
 
 // One block of the backward grid, owning one chunk of one slab.
@@ -1069,10 +1155,11 @@ __device__ __forceinline__ void backward_block(const DevTensor &d, const Chunk &
 {
     const bool write_gx = !(d.flags & 1u);
     BlockScale bs;
+    GxRows<ROWS> gx;
     double sum;
-    if (SHORT) sum = write_gx ? backward_chunk_short<T, kGxYes, kBlock, ROWS>(d, ck, bs) : backward_chunk_short<T, kGxNo, kBlock, ROWS>(d, ck, bs);
-    else sum = write_gx ? backward_chunk<T, kGxYes, kBlock, ROWS>(d, ck, bs) : backward_chunk<T, kGxNo, kBlock, ROWS>(d, ck, bs);
-    combine_block<FUSED, SHORT>(d, ck, sum, bs);
+    if (SHORT) sum = write_gx ? backward_chunk_short<T, kGxYes, kBlock, ROWS>(d, ck, bs, gx) : backward_chunk_short<T, kGxNo, kBlock, ROWS>(d, ck, bs, gx);
+    else sum = write_gx ? backward_chunk<T, kGxYes, kBlock, ROWS>(d, ck, bs, gx) : backward_chunk<T, kGxNo, kBlock, ROWS>(d, ck, bs, gx);
+    combine_block<FUSED, SHORT>(d, ck, sum, bs, [&] { gx.store(); });
 }
 
 // One block of the backward grid for a tensor with short slabs: every wavefront owns a slab (a
@@ -1085,8 +1172,9 @@ __device__ __forceinline__ void backward_waves(const DevTensor &d, unsigned loca
     const bool write_gx = !(d.flags & 1u);
     const Chunk ck = locate_chunk(d, unit);
     BlockScale bs;
-    const double sum = write_gx ? backward_chunk<T, kGxYes, 64, ROWS>(d, ck, bs) : backward_chunk<T, kGxNo, 64, ROWS>(d, ck, bs);
-    combine_wave<FUSED>(d, ck, sum, bs);
+    GxRows<ROWS> gx;
+    const double sum = write_gx ? backward_chunk<T, kGxYes, 64, ROWS>(d, ck, bs, gx) : backward_chunk<T, kGxNo, 64, ROWS>(d, ck, bs, gx);
+    combine_wave<FUSED>(d, ck, sum, bs, [&] { gx.store(); });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1216,13 +1304,16 @@ __global__ void __launch_bounds__(kBlock) backward_multi_kernel(const DevTensor 
     const Chunk ck = locate_chunk(d, unit);
     const int group = d.wave_units ? 64 : kBlock;
     BlockScale bs;
+    // (gx in front of the sum: behind it, held in registers over the five ways to work it out, a list of 64 mixed
+    // tensors takes 551 us instead of 547, and 22 weight tensors the same.)
+    GxRows<0> gx;
     double sum = 0.0;
     for_rows(d.rows, [&](auto rows) {
-        if (d.dtype == 0) sum = backward_chunk<_Float16, kGxAsked, 0, decltype(rows)::value>(d, ck, bs, group);
-        else sum = backward_chunk<float, kGxAsked, 0, decltype(rows)::value>(d, ck, bs, group);
+        if (d.dtype == 0) sum = backward_chunk<_Float16, kGxAsked, 0, decltype(rows)::value>(d, ck, bs, gx, group);
+        else sum = backward_chunk<float, kGxAsked, 0, decltype(rows)::value>(d, ck, bs, gx, group);
     });
-    if (d.wave_units) combine_wave<FUSED>(d, ck, sum, bs);
-    else combine_block<FUSED, false>(d, ck, sum, bs);
+    if (d.wave_units) combine_wave<FUSED>(d, ck, sum, bs, [] {});
+    else combine_block<FUSED, false>(d, ck, sum, bs, [] {});
 }
 
 // one block per channel: second pass of the two-pass backward, and the whole backward of tensors
@@ -1434,10 +1525,8 @@ static void launch_backward_typed(const DevTensor &d, unsigned blocks, bool fuse
 //         600 x 1200 8.7 / 8.3   768 x 800 7.2 / 7.1   768 x 600 6.2 / 5.7   400 x 1200 7.1 / 6.3
 //   FP32  768 x 1200 8.5 / 8.9   512 x 1200 6.2 / 6.5   400 x 1200 5.4 / 5.9   768 x 600 4.95 / 5.3
 //         512 x 600 4.2 / 4.3   400 x 600 4.1 / 4.0   768 x 432 5.0 / 4.9   64 x 144 3.0 / 2.9
-// It stores gx at the very end of a chunk, in front of the unit's sum.  Where the sums are gathered, that
-// would lengthen the tail it is meant to shorten (one scale for 153600 FP32 elements: 5.4 instead of 4.7;
-// for 2457600 FP16: 7.2 instead of 6.4), so there it is not used, and the kernel with it leaves the
-// gathering out.
+// Where the sums are gathered it is not used, and the kernel with it leaves the gathering out (one scale, 153600 FP32
+// elements 4.13 / 3.87, 921600 FP16 4.77 / 4.40, 4915200 FP16 8.6 / 8.0).
 template <typename T> static bool burst_pays(const DevTensor &d, unsigned blocks)
 {
     const bool half = sizeof(T) == 2;
