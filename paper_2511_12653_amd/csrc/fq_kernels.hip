@@ -297,7 +297,7 @@ template <typename T> __device__ __forceinline__ T from_bits(unsigned b)
     return __builtin_bit_cast(T, (U)b);
 }
 
-// Scale of this group's channel (G = 256: the block; G = 64: one wavefront).  Callers issue their
+// Scale of this group's channel (G = 256 or 512: the block; G = 64: one wavefront).  Callers issue their
 // first global loads before this, so the evaluation sits in the shadow of the memory latency.
 // A block lets one wavefront (rotating with the block index, so the work spreads over the four
 // SIMDs of a compute unit) evaluate Eq. (3)-(4), about a hundred binary64 instructions, and the
@@ -315,7 +315,7 @@ __device__ __forceinline__ QParams block_params(const DevTensor &d, float theta,
     } else {
         __shared__ BlockScale shared_scale;
         // (the sum of the indices, not the linear index: that takes the grid's extents, one more load)
-        if ((threadIdx.x >> 6) == ((blockIdx.x + blockIdx.y + blockIdx.z) & (kBlock / 64 - 1))) {
+        if ((threadIdx.x >> 6) == ((blockIdx.x + blockIdx.y + blockIdx.z) & ((G ? G : kBlock) / 64 - 1))) {
             const Scale sc = compute_scale<NEED_SIGMOID>(theta, d.eps, d.s_min, d.s_max);
             if ((threadIdx.x & 63) == 0) {
                 shared_scale.s = sc.s;
@@ -1220,16 +1220,16 @@ __device__ __forceinline__ DevTensor fetch(const DevTensor *table, int i)
 }
 
 // Single tensor: descriptor in the kernel arguments (SGPRs), dtype fixed at compile time.
-// WAVES: the tensor's slabs are short and every wavefront owns one (chosen by the launcher).  ROWS: the
-// vectors per lane that a whole chunk of this tensor has.
-template <typename T, bool WRITE_Y, bool EMIT_Q, bool WAVES, int ROWS, bool EARLY>
-__global__ void __launch_bounds__(kBlock) forward_kernel(const DevTensor d)
+// G: lanes that share a chunk: 64 (the tensor's slabs are short and every wavefront owns one), or the block's
+// threads, kBlock or kWideBlock (chosen by the launcher).  ROWS: the vectors per lane that a whole chunk has, at most.
+template <typename T, bool WRITE_Y, bool EMIT_Q, int G, int ROWS, bool EARLY>
+__global__ void __launch_bounds__(G == 64 ? kBlock : G) forward_kernel(const DevTensor d)
 {
-    if (WAVES) {
+    if (G == 64) {
         const unsigned unit = blockIdx.x * (kBlock / 64) + wave_index();
         if (unit < d.slabs * d.cps) forward_chunk<T, WRITE_Y, EMIT_Q, 64, ROWS, EARLY>(d, locate_chunk(d, unit));
     } else {
-        forward_chunk<T, WRITE_Y, EMIT_Q, kBlock, ROWS, EARLY>(d, own_chunk(d));
+        forward_chunk<T, WRITE_Y, EMIT_Q, G, ROWS, EARLY>(d, own_chunk(d));
     }
 }
 
@@ -1439,10 +1439,10 @@ static void launch(K kernel, unsigned blocks, hipStream_t st, Args... args)
 
 // Single-tensor launch: grid (chunks per slab, channels, outer) where d.grid3 says so.
 template <typename K>
-static void launch_tensor(K kernel, unsigned blocks, hipStream_t st, const DevTensor &d)
+static void launch_tensor(K kernel, unsigned blocks, hipStream_t st, const DevTensor &d, unsigned threads = kBlock)
 {
     const dim3 grid = d.grid3 ? dim3(d.cps, d.channels, d.outer) : dim3(blocks);
-    hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, st, d);
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, d);
 }
 
 // Vectors in a whole chunk.
@@ -1464,22 +1464,55 @@ template <typename F> static void with_rows(int rows, F f)
 // Forward, us before -> with exactly one or two rows: 153600 FP32 elements 2.47 -> 2.31; 64x147 FP32 3.05 ->
 // 2.65; 384x3456 FP32 3.31 -> 3.19.  With three rows exactness loses (3x128x4800 FP16: 3.42 -> 3.48), and
 // so it does for wavefront units (15x384x1200 FP16: 6.70 -> 6.94), so those take kMaxRows.
-template <typename T, bool WAVES, bool EARLY>
+template <typename T, int G, bool EARLY>
 static void launch_forward_full(const DevTensor &d, unsigned blocks, hipStream_t st)
 {
-    if (!d.q) launch_tensor(forward_kernel<T, true, false, WAVES, kMaxRows, EARLY>, blocks, st, d);
-    else if (d.y) launch_tensor(forward_kernel<T, true, true, WAVES, kMaxRows, EARLY>, blocks, st, d);
-    else launch_tensor(forward_kernel<T, false, true, WAVES, kMaxRows, EARLY>, blocks, st, d);
+    constexpr int rows = G == 64 ? kMaxRows : (kChunkVecs + G - 1) / G;
+    constexpr unsigned threads = G == 64 ? kBlock : G;
+    if (!d.q) launch_tensor(forward_kernel<T, true, false, G, rows, EARLY>, blocks, st, d, threads);
+    else if (d.y) launch_tensor(forward_kernel<T, true, true, G, rows, EARLY>, blocks, st, d, threads);
+    else launch_tensor(forward_kernel<T, false, true, G, rows, EARLY>, blocks, st, d, threads);
+}
+
+// Whether a chunk is shared by kWideBlock threads.  The chunk is the same; its rows are requested, worked out and
+// stored by twice the wavefronts, so what a wavefront still has to do when its last row has landed is shorter.  That
+// pays in small launches, whose compute units have one or two blocks and would run one or two wavefronts per SIMD, and
+// in those of many rounds; in between, where every compute unit holds four or five blocks, the smaller blocks end more
+// evenly.  Buffers that no cache holds, us, kBlock / kWideBlock threads, blocks x vectors:
+//   FP16  225 x 512 2.86 / 2.68   240 x 1280 3.72 / 3.52   256 x 603 3.33 / 3.12   384 x 1200 4.90 / 4.73
+//         480 x 1280 5.49 / 5.20   540 x 1200 6.09 / 5.63   600 x 1200 6.29 / 6.05   660 x 1200 6.39 / 6.29
+//         880 x 1200 7.90 / 8.12   960 7.62 / 8.40   1024 7.65 / 8.35   1280 9.75 / 10.87   1536 11.8 / 12.3
+//         1800 x 1200 14.12 / 13.83   2560 18.5 / 18.2   3840 25.9 / 25.2   2000 x 600 9.07 / 8.35
+//         3000 x 512 10.58 / 9.80   3000 x 375 8.58 / 8.68   4000 x 313 9.71 / 10.54 (three of eight wavefronts idle)
+//   FP32  512 x 576 3.30 / 3.28   512 x 1200 5.03 / 4.95   804 x 824 6.12 / 5.81   1024 x 1200 7.7 / 8.6
+//         1800 x 1200 13.6 / 13.4   3000 x 640 12.35 / 11.95;   768 x 432 3.42 / 3.73 (one row each instead of two)
+//   codes alone, FP16  128 x 603 3.22 / 3.08   240 x 1280 3.68 / 3.43   400 x 1200 4.53 / 4.21   768 x 1200 5.90 / 6.14
+//         2000 x 600 7.58 / 8.21   3840 x 1200 20.2 / 20.9
+// With more than kEarlyBlocks blocks theta goes in front of the rows there too (768 x 1200 FP16 6.68 / 6.73 without it and
+// 6.44 with it, FP32 6.39 / 6.75 / 6.05; but 540 x 1200 5.63 without and 5.96 with it).
+constexpr int kWideBlock = 2 * kBlock, kWideRows = (kChunkVecs + kWideBlock - 1) / kWideBlock;
+constexpr unsigned kEarlyBlocks = 640, kWideFewBlocks = 512, kWideManyBlocks = 1800;
+static bool wide_pays(unsigned blocks, unsigned vecs, bool codes)
+{
+    if (blocks <= kWideFewBlocks) return vecs > (unsigned)kBlock;
+    if (codes) return false;
+    return blocks <= kResidentBlocks ? vecs > 2u * kWideBlock : blocks >= kWideManyBlocks && vecs > kWideBlock * 7u / 8u;
 }
 
 template <typename T>
 static void launch_forward_single(const DevTensor &d, unsigned blocks, hipStream_t st)
 {
-    if (d.wave_units) launch_forward_full<T, true, false>(d, blocks, st);
-    else if (!d.q && d.rows == 1) launch_tensor(forward_kernel<T, true, false, false, 1, false>, blocks, st, d);
-    else if (!d.q && d.rows == 2) launch_tensor(forward_kernel<T, true, false, false, 2, false>, blocks, st, d);
-    else if (blocks > kResidentBlocks) launch_forward_full<T, false, true>(d, blocks, st);
-    else launch_forward_full<T, false, false>(d, blocks, st);
+    const unsigned vecs = chunk_vecs<T>(d);
+    if (d.wave_units) launch_forward_full<T, 64, false>(d, blocks, st);
+    else if (wide_pays(blocks, vecs, d.q != nullptr)) {
+        if (!d.q && vecs <= (unsigned)kWideBlock) launch_tensor(forward_kernel<T, true, false, kWideBlock, 1, false>, blocks, st, d, kWideBlock);
+        else if (!d.q && vecs <= 2u * kWideBlock) launch_tensor(forward_kernel<T, true, false, kWideBlock, 2, false>, blocks, st, d, kWideBlock);
+        else if (blocks > kEarlyBlocks) launch_tensor(forward_kernel<T, true, false, kWideBlock, kWideRows, true>, blocks, st, d, kWideBlock);
+        else launch_forward_full<T, kWideBlock, false>(d, blocks, st);
+    } else if (!d.q && d.rows == 1) launch_tensor(forward_kernel<T, true, false, kBlock, 1, false>, blocks, st, d);
+    else if (!d.q && d.rows == 2) launch_tensor(forward_kernel<T, true, false, kBlock, 2, false>, blocks, st, d);
+    else if (blocks > kResidentBlocks) launch_forward_full<T, kBlock, true>(d, blocks, st);
+    else launch_forward_full<T, kBlock, false>(d, blocks, st);
 }
 
 int launch_forward(const KArgs &a, unsigned blocks, bool emit_q, void *stream)
