@@ -2,7 +2,8 @@
 
 hipcc cross-compiles for gfx950 without a GPU.  Flags: IEEE arithmetic only (no fast-math, no
 implicit FMA contraction -- the kernels call fma explicitly where they want one) and no packed
-FP32 instructions.
+FP32 instructions.  The first 14 dwords of a kernel's scalar arguments (all that fit beside the address of the
+rest) come in registers with the launch instead of being loaded by every wavefront.
 """
 import os
 import subprocess
@@ -17,7 +18,7 @@ HEADERS = [os.path.join(CSRC, "fq_internal.h"), os.path.join(CSRC, "fq_device.h"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off",
          "-fno-fast-math", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-         "-Wall", "-Wextra", "-Wno-unused-command-line-argument"]
+         "-mllvm", "-amdgpu-kernarg-preload-count=14", "-Wall", "-Wextra", "-Wno-unused-command-line-argument"]
 
 
 def stale() -> bool:

@@ -229,17 +229,6 @@ struct Cursor {
     long long block = 0, chan = 0, slot = 0, unit = 0;
 };
 
-Divisor divisor(unsigned d)
-{
-    Divisor r = {0u, 0, 0};
-    if (d == 0) return r;                         // an empty tensor: never divided by
-    const unsigned s = d > 1 ? 32u - (unsigned)__builtin_clz(d - 1) : 0u;
-    r.multiplier = (unsigned)((((1ull << s) - d) << 32) / d + 1ull);
-    r.shift1 = (unsigned short)(s < 1 ? s : 1);
-    r.shift2 = (unsigned short)(s > 0 ? s - 1 : 0);
-    return r;
-}
-
 // Device descriptor of one tensor; `partials` / `slots` are the launch's arrays of partial sums and
 // of 64-bit slots (nullptr: forward, nothing is reduced).
 DevTensor describe(const fq_tensor &t, const Plan &p, int mode, double *partials, unsigned long long *slots,

@@ -76,7 +76,6 @@ struct DistillArgs {
     double *out;        // mse, cosim, loss
     long long M, P;     // positions per image, positions in total
     unsigned C, groups, per_group, tiles_per_n, tiles, poll_rounds;
-    unsigned neighbours;           // see tile_of_block
     double k1u, k2u, eps, lambda, inv_ncm, inv_nm;
 };
 
@@ -555,9 +554,20 @@ __device__ __forceinline__ unsigned tile_of_block(unsigned block, unsigned tiles
     return xcd * each + (xcd < more ? xcd : more) + block / kXcds;
 }
 
+// The leading arguments, which are what the first loads' addresses are made of, come in registers with the launch (see
+// forward_kernel in the other file).  neighbours: 0, or the number of tiles (see tile_of_block).
 template <typename T, int THREADS, int KCH, bool QUADS, bool WANT_GRAD>
-__global__ __launch_bounds__(THREADS, 4) void distill_fused_kernel(DistillArgs k)
+__global__ __launch_bounds__(THREADS, 4)
+void distill_fused_kernel(const void *student, const void *teacher, long long M, unsigned C, unsigned tiles_per_n,
+                          unsigned by_multiplier, unsigned by_shifts, unsigned neighbours, const DistillArgs rest)
 {
+    DistillArgs k = rest;
+    k.a = student;
+    k.b = teacher;
+    k.M = M;
+    k.C = C;
+    k.tiles_per_n = tiles_per_n;
+    const Divisor by_tiles_per_n = {by_multiplier, (unsigned short)by_shifts, (unsigned short)(by_shifts >> 16)};
     typedef FusedShape<T, THREADS> Shape;
     constexpr int V = kFusedVec, L = Shape::L, P = Shape::P, R = Shape::R, W = THREADS / 64, S = 64 / L;
     constexpr int HELD = S >= 4 ? kStats / 4 : kStats / 2;      // sums a lane is left with
@@ -569,8 +579,8 @@ __global__ __launch_bounds__(THREADS, 4) void distill_fused_kernel(DistillArgs k
     __shared__ double cosines[P];
 
     const unsigned lane = threadIdx.x % L, row = threadIdx.x / L, wave = threadIdx.x >> 6;
-    const unsigned tile = k.neighbours ? tile_of_block(blockIdx.x, k.tiles) : blockIdx.x;
-    const unsigned n = tile / k.tiles_per_n, tn = tile - n * k.tiles_per_n;
+    const unsigned tile = neighbours ? tile_of_block(blockIdx.x, neighbours) : blockIdx.x;
+    const unsigned n = divide(tile, by_tiles_per_n), tn = tile - n * k.tiles_per_n;
     const long long tile_m = (long long)tn * P;
     long long m0 = tile_m + (long long)lane * V;
     // positions of this lane that exist; QUADS: four or none (none: re-read the last quad, results dropped)
@@ -736,6 +746,7 @@ struct Plan {
     int vec;                 // elements per lane
     int fused_kch;           // > 0: the fused kernel with this many channels per lane; 0: two kernels
     bool quads, wide;        // fused: see Quad; wide tiles
+    bool neighbours;         // fused: see tile_of_block
     bool one_launch;         // fused: the kernel adds its tiles' sums itself
     unsigned tiles_per_n, tiles, groups, per_group, grad_groups, grad_per_group;
     size_t stats_lds, off_blocksum, bytes;
@@ -906,15 +917,24 @@ fq_status launch(const DistillArgs &k, const Plan &pl, bool want_grad, hipStream
     return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_LAUNCH;
 }
 
+template <typename T, int THREADS, int KCH, bool QUADS, bool WANT_GRAD>
+void launch_fused_kernel(const DistillArgs &k, const Plan &pl, hipStream_t st)
+{
+    const Divisor by = divisor(pl.tiles_per_n);
+    distill_fused_kernel<T, THREADS, KCH, QUADS, WANT_GRAD><<<pl.tiles, THREADS, 0, st>>>(
+        k.a, k.b, k.M, k.C, k.tiles_per_n, by.multiplier, by.shift1 | (unsigned)by.shift2 << 16,
+        pl.neighbours ? pl.tiles : 0u, k);
+}
+
 template <typename T, int KCH, bool QUADS>
 fq_status launch_fused(const DistillArgs &k, const Plan &pl, bool want_grad, hipStream_t st)
 {
     if (pl.wide) {
-        if (want_grad) distill_fused_kernel<T, kWideThreads, KCH, QUADS, true><<<pl.tiles, kWideThreads, 0, st>>>(k);
-        else distill_fused_kernel<T, kWideThreads, KCH, QUADS, false><<<pl.tiles, kWideThreads, 0, st>>>(k);
+        if (want_grad) launch_fused_kernel<T, kWideThreads, KCH, QUADS, true>(k, pl, st);
+        else launch_fused_kernel<T, kWideThreads, KCH, QUADS, false>(k, pl, st);
     } else {
-        if (want_grad) distill_fused_kernel<T, kNarrowThreads, KCH, QUADS, true><<<pl.tiles, kNarrowThreads, 0, st>>>(k);
-        else distill_fused_kernel<T, kNarrowThreads, KCH, QUADS, false><<<pl.tiles, kNarrowThreads, 0, st>>>(k);
+        if (want_grad) launch_fused_kernel<T, kNarrowThreads, KCH, QUADS, true>(k, pl, st);
+        else launch_fused_kernel<T, kNarrowThreads, KCH, QUADS, false>(k, pl, st);
     }
     if (!pl.one_launch) distill_finish_kernel<<<1, 1024, 0, st>>>(k);
     return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_LAUNCH;
@@ -1016,7 +1036,7 @@ static fq_status distill_loss(const fq_distill *d, void *workspace, size_t ws_by
     k.records = (unsigned long long *)workspace;
     k.nonce = pl.one_launch ? next_nonce() : 0ull;
     k.poll_rounds = poll_rounds;
-    k.neighbours = pl.fused_kch && (!pl.quads || d->inner * (d->dtype == FQ_F16 ? 2 : 4) % 128 != 0);
+    pl.neighbours = pl.fused_kch && (!pl.quads || d->inner * (d->dtype == FQ_F16 ? 2 : 4) % 128 != 0);
     if (pl.fused_kch) {
         k.coef = nullptr;
         return d->dtype == FQ_F16 ? launch_fused_width<_Float16>(k, pl, grad, st)

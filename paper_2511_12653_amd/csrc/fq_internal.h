@@ -39,6 +39,17 @@ struct Divisor {
     unsigned short shift1, shift2;
 };
 
+inline Divisor divisor(unsigned d)
+{
+    Divisor r = {0u, 0, 0};
+    if (d == 0) return r;                         // an empty tensor: never divided by
+    const unsigned s = d > 1 ? 32u - (unsigned)__builtin_clz(d - 1) : 0u;
+    r.multiplier = (unsigned)((((1ull << s) - d) << 32) / d + 1ull);
+    r.shift1 = (unsigned short)(s < 1 ? s : 1);
+    r.shift2 = (unsigned short)(s > 0 ? s - 1 : 0);
+    return r;
+}
+
 // Bias corrections 1 - beta^t of an Adam step that a launch brings with it (set != 0).
 struct AdamBias {
     float bc1, bc2;

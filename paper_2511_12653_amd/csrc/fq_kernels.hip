@@ -227,14 +227,6 @@ struct Chunk {
     int n;             // elements in the chunk
 };
 
-// n / d with the numbers that the host has worked out for d (see Divisor): five scalar instructions in
-// front of a block's first load instead of the two dozen of an integer division.
-__device__ __forceinline__ unsigned divide(unsigned n, const Divisor &by)
-{
-    const unsigned t = __umulhi(n, by.multiplier);
-    return (t + ((n - t) >> by.shift1)) >> by.shift2;
-}
-
 __device__ __forceinline__ Chunk locate_chunk(const DevTensor &d, unsigned local_block)
 {
     Chunk c;
@@ -1153,7 +1145,7 @@ __device__ __forceinline__ void combine_wave(const DevTensor &d, const Chunk &ck
 template <typename T, bool FUSED, int ROWS, bool SHORT>
 __device__ __forceinline__ void backward_block(const DevTensor &d, const Chunk &ck)
 {
-    const bool write_gx = !(d.flags & 1u);
+    const bool write_gx = d.gx != nullptr;
     BlockScale bs;
     GxRows<ROWS> gx;
     double sum;
@@ -1169,7 +1161,7 @@ __device__ __forceinline__ void backward_waves(const DevTensor &d, unsigned loca
 {
     const unsigned unit = local_block * (kBlock / 64) + wave_index();
     if (unit >= d.slabs * d.cps) return;
-    const bool write_gx = !(d.flags & 1u);
+    const bool write_gx = d.gx != nullptr;
     const Chunk ck = locate_chunk(d, unit);
     BlockScale bs;
     GxRows<ROWS> gx;
@@ -1220,11 +1212,26 @@ __device__ __forceinline__ DevTensor fetch(const DevTensor *table, int i)
 }
 
 // Single tensor: descriptor in the kernel arguments (SGPRs), dtype fixed at compile time.
+// What the first loads' addresses are made of stands in front of the descriptor as arguments of its own: the build has
+// the leading 14 dwords of arguments put into registers with the launch (build.py), so that no wavefront waits for the
+// descriptor, one trip to memory, before it requests its rows.  channels is 0 where the grid is linear.  us, before / with:
+// forward of 153600 FP32 2.34 / 2.22, 64x576 FP32 2.25 / 2.16, 2457600 FP16 3.46 / 3.35, 384x19200 FP16 6.49 / 6.36, backward
+// 3.62 / 3.49, 2.91 / 2.80, 5.80 / 5.69, 3x131x4819 FP16 5.77 / 5.55, 15x128x19200 FP16 38.8 / 38.4; list of 22 FP32 weight tensors
+// forward 4.72 / 4.55 (the table's address and length); distillation of 1x128x1200 FP16 5.30 / 5.17.
 // G: lanes that share a chunk: 64 (the tensor's slabs are short and every wavefront owns one), or the block's
 // threads, kBlock or kWideBlock (chosen by the launcher).  ROWS: the vectors per lane that a whole chunk has, at most.
 template <typename T, bool WRITE_Y, bool EMIT_Q, int G, int ROWS, bool EARLY>
-__global__ void __launch_bounds__(G == 64 ? kBlock : G) forward_kernel(const DevTensor d)
+__global__ void __launch_bounds__(G == 64 ? kBlock : G)
+forward_kernel(const void *x, void *y, const float *theta, long long inner, unsigned chunk, unsigned channels, const DevTensor rest)
 {
+    DevTensor d = rest;
+    d.x = x;
+    d.y = y;
+    d.theta = theta;
+    d.inner = inner;
+    d.chunk = chunk;
+    d.grid3 = channels != 0u;
+    if (d.grid3) d.channels = channels;
     if (G == 64) {
         const unsigned unit = blockIdx.x * (kBlock / 64) + wave_index();
         if (unit < d.slabs * d.cps) forward_chunk<T, WRITE_Y, EMIT_Q, 64, ROWS, EARLY>(d, locate_chunk(d, unit));
@@ -1271,11 +1278,24 @@ __global__ void __launch_bounds__(kBlock) forward_multi_kernel(const DevTensor *
     }
 }
 
+// gx: nullptr where the gradient of x is not asked for.
 // SHAPE: 0 = one chunk per block; 1 = one slab per wavefront (short slabs); 2 = one chunk per block
 // with the burst schedule (see backward_chunk_short and launch_backward_shaped).
 template <typename T, bool FUSED, int SHAPE, int ROWS>
-__global__ void __launch_bounds__(kBlock) backward_kernel(const DevTensor d)
+__global__ void __launch_bounds__(kBlock)
+backward_kernel(const void *x, const void *gy, void *gx, const float *theta, long long inner, unsigned chunk, unsigned cps,
+                unsigned channels, const DevTensor rest)
 {
+    DevTensor d = rest;
+    d.x = x;
+    d.gy = gy;
+    d.gx = gx;
+    d.theta = theta;
+    d.inner = inner;
+    d.chunk = chunk;
+    d.cps = cps;
+    d.grid3 = channels != 0u;
+    if (d.grid3) d.channels = channels;
     if (SHAPE == 1) {
         backward_waves<T, FUSED, ROWS>(d, blockIdx.x);
     } else {
@@ -1438,11 +1458,21 @@ static void launch(K kernel, unsigned blocks, hipStream_t st, Args... args)
 }
 
 // Single-tensor launch: grid (chunks per slab, channels, outer) where d.grid3 says so.
-template <typename K>
-static void launch_tensor(K kernel, unsigned blocks, hipStream_t st, const DevTensor &d, unsigned threads = kBlock)
+typedef void (*ForwardKernel)(const void *, void *, const float *, long long, unsigned, unsigned, const DevTensor);
+typedef void (*BackwardKernel)(const void *, const void *, void *, const float *, long long, unsigned, unsigned, unsigned,
+                               const DevTensor);
+
+static void launch_tensor(ForwardKernel kernel, unsigned blocks, hipStream_t st, const DevTensor &d, unsigned threads = kBlock)
 {
     const dim3 grid = d.grid3 ? dim3(d.cps, d.channels, d.outer) : dim3(blocks);
-    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, d);
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, d.x, d.y, d.theta, d.inner, d.chunk, d.grid3 ? d.channels : 0u, d);
+}
+
+static void launch_tensor(BackwardKernel kernel, unsigned blocks, hipStream_t st, const DevTensor &d)
+{
+    const dim3 grid = d.grid3 ? dim3(d.cps, d.channels, d.outer) : dim3(blocks);
+    hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, st, d.x, d.gy, d.flags & 1u ? nullptr : d.gx, d.theta, d.inner, d.chunk, d.cps,
+                       d.grid3 ? d.channels : 0u, d);
 }
 
 // Vectors in a whole chunk.
