@@ -8,7 +8,7 @@
 // without atomics.  Two ways, chosen on the host:
 //
 // One pass (fused kernel; channel counts up to 512): a block owns a tile of all channels x one run of
-// positions, 128 bytes of each channel (64 FP16 or 32 FP32 positions; 512 threads) or 256 bytes (1024
+// positions, 128 bytes of each channel (64 FP16 or 32 FP32 positions; 512 threads) or 256 bytes (1024, 512 or 256
 // threads); a lane holds 4 consecutive positions of up to 16 channels IN REGISTERS, adds its three sums
 // (a.b, a.a, b.b) per position and its one sum of (a-b)^2, the wavefront adds its rows by lane exchanges,
 // the block adds the wavefronts through LDS in a fixed order, forms cos and the two gradient coefficients
@@ -20,7 +20,8 @@
 //   passes of 32 dependent additions, and a second launch added the tiles), 1x128x1200 7.1 -> 5.0,
 //   15x128x19200 45.3 -> 43.7, 1x384x19200 FP32 25.9 -> 22.3, 4x128x19200 FP32 29.9 -> 25.5; off the grid,
 //   where two kernels used to read the pair: 2x128x4819 FP32 13.1 -> 6.6, 4x256x9601 FP32 55.9 -> 35.3,
-//   8x250x5001 FP16 39.7 -> 21.9.
+//   8x250x5001 FP16 39.7 -> 21.9.  With rows of 256 bytes by smaller blocks in launches of many tiles: 15x128x19200 FP16
+//   44.2 -> 42.0, 15x64x19200 28.6 -> 25.5, 16x32x19200 23.0 -> 16.2, 15x64x9600 FP32 25.9 -> 23.0, 16x16x4800 11.9 -> 7.3.
 //
 // Two reads (more than 512 channels): a wavefront owns 64 lanes x V consecutive positions (one coalesced
 // row per channel) and walks over a group of channels, every lane keeping the four sums of its V positions
@@ -403,14 +404,18 @@ __global__ __launch_bounds__(kThreads) void distill_grad_kernel(DistillArgs k, u
 // positions 4l .. 4l+3 of the tile for channels r, r + R, r + 2R, ... (KCH of them at most).
 constexpr int kFusedVec = 4;                     // positions per lane
 constexpr int kFusedMaxKch = 16;                 // channels per lane the registers hold (FP16; half for FP32)
-constexpr int kNarrowThreads = 512, kWideThreads = 1024;
-// A narrow tile's rows are 128 bytes of each channel, a whole cache line, a wide tile's two lines.
-// (Rows of 64 bytes would cut a 1x384x120x160 pair into 600 tiles and spread them more evenly over the
+// The shapes of a tile: threads of its block and bytes of each channel in it.  Which one is taken, and why, stands at
+// make_plan.  (Rows of 64 bytes would cut a 1x384x120x160 pair into 600 tiles and spread them more evenly over the
 // 256 compute units, but half-line accesses cost more than the balance gains: 24.4 us against 16.9.)
-template <typename T, int THREADS> struct FusedShape {
-    static constexpr int L = THREADS / 4 / (kFusedVec * (int)sizeof(T));   // lanes per row
-    static constexpr int P = kFusedVec * L;                                // positions per tile
-    static constexpr int R = THREADS / L;                                  // channel rows: 32 (FP16), 64 (FP32)
+enum TileShape { kNarrow, kWide, kLong, kSmall };
+constexpr int kTileThreads[] = {512, 1024, 512, 256};
+constexpr int kTileRowBytes[] = {128, 256, 256, 256};
+template <typename T, int SHAPE> struct FusedShape {
+    static constexpr int THREADS = kTileThreads[SHAPE];
+    static constexpr int L = kTileRowBytes[SHAPE] / (kFusedVec * (int)sizeof(T));   // lanes per row
+    static constexpr int P = kFusedVec * L;                                         // positions per tile
+    static constexpr int R = THREADS / L;                                           // channel rows
+    static constexpr bool GATHERS = SHAPE == kNarrow || SHAPE == kWide;             // may be launched without a second kernel
 };
 
 // Four positions of one channel.  QUADS: rows lie on the 4-element grid.  Otherwise a row starts at
@@ -556,8 +561,8 @@ __device__ __forceinline__ unsigned tile_of_block(unsigned block, unsigned tiles
 
 // The leading arguments, which are what the first loads' addresses are made of, come in registers with the launch (see
 // forward_kernel in the other file).  neighbours: 0, or the number of tiles (see tile_of_block).
-template <typename T, int THREADS, int KCH, bool QUADS, bool WANT_GRAD>
-__global__ __launch_bounds__(THREADS, 4)
+template <typename T, int SHAPE, int KCH, bool QUADS, bool WANT_GRAD>
+__global__ __launch_bounds__(kTileThreads[SHAPE], 4)
 void distill_fused_kernel(const void *student, const void *teacher, long long M, unsigned C, unsigned tiles_per_n,
                           unsigned by_multiplier, unsigned by_shifts, unsigned neighbours, const DistillArgs rest)
 {
@@ -568,7 +573,8 @@ void distill_fused_kernel(const void *student, const void *teacher, long long M,
     k.C = C;
     k.tiles_per_n = tiles_per_n;
     const Divisor by_tiles_per_n = {by_multiplier, (unsigned short)by_shifts, (unsigned short)(by_shifts >> 16)};
-    typedef FusedShape<T, THREADS> Shape;
+    typedef FusedShape<T, SHAPE> Shape;
+    constexpr int THREADS = Shape::THREADS;
     constexpr int V = kFusedVec, L = Shape::L, P = Shape::P, R = Shape::R, W = THREADS / 64, S = 64 / L;
     constexpr int HELD = S >= 4 ? kStats / 4 : kStats / 2;      // sums a lane is left with
     typedef Quad<T, QUADS> Q;
@@ -690,7 +696,7 @@ void distill_fused_kernel(const void *student, const void *teacher, long long M,
         cos_sum = wave_sum(cos_sum);
         sq_sum = wave_sum(sq_sum);
         if (threadIdx.x == kSumLane) {
-            if (k.nonce) {
+            if (Shape::GATHERS && k.nonce) {
                 unsigned long long *r = k.records + (size_t)tile * 4;
                 const unsigned long long w[4] = {bits_of(cos_sum), bits_of(cos_sum) ^ k.nonce, bits_of(sq_sum),
                                                  bits_of(sq_sum) ^ k.nonce};
@@ -737,7 +743,7 @@ void distill_fused_kernel(const void *student, const void *teacher, long long M,
             }
         }
     }
-    if (k.nonce && wave == 0) gather_or_leave(k);
+    if (Shape::GATHERS && k.nonce && wave == 0) gather_or_leave(k);
 }
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -745,20 +751,33 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 struct Plan {
     int vec;                 // elements per lane
     int fused_kch;           // > 0: the fused kernel with this many channels per lane; 0: two kernels
-    bool quads, wide;        // fused: see Quad; wide tiles
+    bool quads;              // fused: see Quad
+    TileShape shape;         // fused
     bool neighbours;         // fused: see tile_of_block
     bool one_launch;         // fused: the kernel adds its tiles' sums itself
     unsigned tiles_per_n, tiles, groups, per_group, grad_groups, grad_per_group;
     size_t stats_lds, off_blocksum, bytes;
 };
 
-// Channels per lane the fused kernel would need for this pair, rounded up to a width it is built
-// for; 0 if there are more channels than a lane's registers hold.
-int fused_channels_per_lane(const fq_distill *d)
+template <typename T> constexpr int positions_of(int shape) { return kTileRowBytes[shape] / (int)sizeof(T); }
+template <typename T> constexpr int rows_of(int shape) { return kTileThreads[shape] * kFusedVec * (int)sizeof(T) / kTileRowBytes[shape]; }
+
+// Channels per lane that a tile's shape is built for, at most.
+template <typename T> constexpr int most_channels_per_lane(int shape)
 {
-    const long long rows = d->dtype == FQ_F16 ? FusedShape<_Float16, kNarrowThreads>::R : FusedShape<float, kNarrowThreads>::R;
+    return shape == kSmall ? 4 : sizeof(T) == 2 ? kFusedMaxKch : kFusedMaxKch / 2;
+}
+
+long long tile_positions(const fq_distill *d, TileShape s) { return d->dtype == FQ_F16 ? positions_of<_Float16>(s) : positions_of<float>(s); }
+
+// Channels per lane the fused kernel needs for this pair with tiles of this shape, rounded up to a width it is
+// built for; 0 if there are more channels than a lane's registers hold.
+int fused_channels_per_lane(const fq_distill *d, TileShape s)
+{
+    const bool half = d->dtype == FQ_F16;
+    const long long rows = half ? rows_of<_Float16>(s) : rows_of<float>(s);
     const long long need = (d->channels + rows - 1) / rows;
-    const long long cap = d->dtype == FQ_F16 ? kFusedMaxKch : kFusedMaxKch / 2;
+    const long long cap = half ? most_channels_per_lane<_Float16>(s) : most_channels_per_lane<float>(s);
     if (need > cap) return 0;
     for (int kch : {2, 4, 6, 8, 12, 16})
         if (kch >= need) return kch;
@@ -771,6 +790,59 @@ bool on_quads(const fq_distill *d)
     const size_t esz = d->dtype == FQ_F16 ? 2 : 4;
     const uintptr_t addr_bits = (uintptr_t)d->student | (uintptr_t)d->teacher | (uintptr_t)d->gstudent;
     return d->inner % kFusedVec == 0 && addr_bits % (kFusedVec * esz) == 0;
+}
+
+// The shape of the tiles in launches of more than kGatherTiles of them, which a second kernel follows.  Rows of 256
+// bytes: longer runs in memory and half the tiles, for as many positions behind the last tile of an image.
+//
+// Long tiles, 512 threads: a compute unit holds two to four of them, so that some read while others reduce or write.
+// Measured, us, before (narrow for FP16, narrow or wide for FP32) / long:
+//   FP16  15x128x19200 44.2 / 42.0   8x128x19200 27.2 / 26.0   15x64x19200 28.6 / 25.5   3x256x19200 22.1 / 20.7   60x128x1000
+//         16.2 / 14.4   30x64x4800 16.9 / 15.4   20x30x4819 12.4 / 9.4
+//   FP32  4x128x19200 26.2 / 25.6   15x64x9600 25.9 / 23.7   16x32x9600 20.7 / 15.8   3x134x6588 13.5 / 12.7   8x256x4800
+//         26.7 / 25.0   4x256x9601 35.8 / 32.8
+// FP16 loses where the tiles are few and uneven over the compute units (tiles of the launch: 300, 2x128x19200 10.8 / 12.0;
+// 304, 8x256x4800 16.5 / 19.6; 600, 4x128x19200 15.8 / 16.5; but 450, 3x128x19200 13.25 / 13.0 and 480, 60x128x1000), less so with
+// few channels (608, 16x64x4800 11.1 / 11.0; 600, 4x32x19200 9.3 / 8.4).  Both lose where the last tile of an image is half
+// empty and images are short (400x128x129 FP16 20.6 / 26.7, 400x128x96 FP32 15.2 / 16.7), with few channels from shorter images on
+// (200x16x400 FP16 9.4 / 7.9, 200x32x200 FP32 10.3 / 8.5).  FP32 off the grid with 65 to 128 channels, whose wide
+// tiles go two to a compute unit, stays with those (12x100x4819 20.6 / 22.7), and so do few tiles of the most channels
+// (450, 3x256x9600 19.9 / 20.2).
+bool long_pays(const fq_distill *d, bool quads, long long narrow_tpn, long long wide_tpn)
+{
+    const int kch = fused_channels_per_lane(d, kLong);
+    if (!kch || (2 * wide_tpn - narrow_tpn) * (kch <= 2 ? 4 : 16) > narrow_tpn) return false;
+    const long long tiles = wide_tpn * d->n, rounds = (tiles + kComputeUnits - 1) / kComputeUnits;
+    if (d->dtype == FQ_F32) return (quads || kch != 4) && (kch < 8 || tiles >= 2 * kComputeUnits);
+    return 8 * tiles >= 7 * rounds * kComputeUnits || tiles >= (kch <= 4 ? 2 : kch <= 8 ? 4 : 7) * kComputeUnits;
+}
+
+// Where long tiles pay: with few channels the same rows by 256 threads, twice the channels per lane.  us, long / small:
+//   FP16  16x32x9600 11.1 / 10.7   60x24x2000 9.3 / 8.9   30x16x19200 22.6 / 18.5   64 channels: no difference
+//   FP32  16x16x4800 8.45 / 7.3   60x48x1200 13.5 / 12.8   15x64x9600 23.7 / 23.0
+// Off the grid, and in smaller launches, with the fewest channels only (10x64x4819 FP32 11.9 / 12.2, 20x30x4819 FP16 9.4 /
+// 10.0, 8x64x4800 FP32 9.5 / 9.9; but 30x30x2411 FP32 11.3 / 10.5).
+bool small_pays(const fq_distill *d, bool quads, long long tiles)
+{
+    const int kch = fused_channels_per_lane(d, kSmall);
+    return kch && (kch <= 2 || (quads && tiles >= 2 * kComputeUnits));
+}
+
+// Where they don't: wide tiles, 1024 threads, for FP32 (us, narrow / wide: 3x384x19200 61 / 55, 12x100x4819 25.8 /
+// 20.6; a wide FP16 tile fills a compute unit by itself, with nothing to stream while it reduces: 15x256x19200 85 / 95).
+// Not where the narrow ones are all resident at once and the wide ones need a second round (on the grid; its registers
+// let a compute unit hold 4, 3 or 2 narrow tiles, 2 or 1 wide ones; 150x384x96 15.5 / 17.2).
+// Nor where the last wide tile of an image is half empty and images are short: on the grid if more than a
+// sixteenth of the wide tiles' positions lie behind the image (400x128x96 15.3 / 17.2, 150x384x288 37.6 / 40.6,
+// 400x128x224 27.7 / 28.9), off it, where wide rows share fewer lines (400x128x129 29.3 / 24.1), if they are
+// as many as the narrow ones (1000x128x9 11.4 / 15.6; on the grid 4000x128x4 22.6 / 36.4, 3000x24x32 13.9 / 21.7).
+bool wide_pays(const fq_distill *d, bool quads, long long narrow_tpn, long long wide_tpn, int kch)
+{
+    const long long held_narrow = kch <= 2 ? 4 : kch <= 4 ? 3 : 2, held_wide = kch <= 2 ? 2 : 1;
+    const bool second_round = quads && narrow_tpn * d->n <= held_narrow * kComputeUnits &&
+                              wide_tpn * d->n > held_wide * kComputeUnits;
+    const bool half_empty = quads ? 16 * (2 * wide_tpn - narrow_tpn) > narrow_tpn : wide_tpn == narrow_tpn;
+    return d->dtype == FQ_F32 && !second_round && !half_empty;
 }
 
 fq_status make_plan(const fq_distill *d, Plan &pl)
@@ -809,35 +881,20 @@ fq_status make_plan(const fq_distill *d, Plan &pl)
         pl.bytes = 256;
         return FQ_OK;
     }
-    pl.fused_kch = fused_channels_per_lane(d);
+    pl.fused_kch = fused_channels_per_lane(d, kNarrow);
     if (pl.fused_kch) {
         pl.quads = on_quads(d);
-        const bool half = d->dtype == FQ_F16;
-        const long long narrow = half ? FusedShape<_Float16, kNarrowThreads>::P : FusedShape<float, kNarrowThreads>::P;
+        const long long narrow = tile_positions(d, kNarrow);
         const long long narrow_tpn = (d->inner + narrow - 1) / narrow, wide_tpn = (d->inner + 2 * narrow - 1) / (2 * narrow);
-        // Wide tiles where that leaves few enough of them for one launch (1x384x19200 FP16: 15.9 -> 12.6 us),
-        // and for FP32, whose wide rows are worth more than the finer grain (us, narrow / wide: 4x128x19200 28.3 /
-        // 25.2, 3x384x19200 61 / 55, 4x256x9601 53 / 40; 8x256x4800 23.9 / 25.7).  A wide FP16 tile fills a
-        // compute unit by itself, with nothing to stream while it reduces (15x256x19200 85 / 95, 8x250x5001 26.6 / 29;
-        // 4x128x9601 15.1 / 14.4).
-        // Not where the narrow ones are all resident at once and the wide ones need a second round (FP32 on the grid,
-        // 3x134x6588: 13.6 / 14.3, 5x134x4800: 11.7 / 12.9, without a gradient 10.0 / 10.4 and 9.3 / 9.7; its registers
-        // let a compute unit hold 4, 3 or 2 narrow tiles, 2 or 1 wide ones).
-        // (Known loss: such launches with a gradient and 150 to 400 channels, 2x200x9600 13.5 -> 14.3, 1x160x23040 13.8 ->
-        // 14.7, 150x384x96 15.5 -> 16.6 since the rows are added by lane exchanges.  It looks as if the faster sum let the
-        // first tiles' stores fall among the others' loads: without a gradient the same pairs went 11.5 -> 10.6, and waiting in front
-        // of the stores, or storing without the non-temporal hint, gains 7 % on some of them and loses as much on others.)
-        // Nor where the last wide tile of an image is half empty and images are short: on the grid if more than a
-        // sixteenth of the wide tiles' positions lie behind the image (400x128x96 15.3 / 17.2, 150x384x288 37.6 / 40.6,
-        // 400x128x224 27.7 / 28.9), off it, where wide rows share fewer lines (400x128x129 29.3 / 24.1), if they are
-        // as many as the narrow ones (1000x128x9 11.4 / 15.6; on the grid 4000x128x4 22.6 / 36.4, 3000x24x32 13.9 / 21.7).
-        const bool many = narrow_tpn * d->n > (long long)kGatherTiles;
-        const long long held_narrow = pl.fused_kch <= 2 ? 4 : pl.fused_kch <= 4 ? 3 : 2, held_wide = pl.fused_kch <= 2 ? 2 : 1;
-        const bool second_round = pl.quads && narrow_tpn * d->n <= held_narrow * kComputeUnits &&
-                                  wide_tpn * d->n > held_wide * kComputeUnits;
-        const bool half_empty = pl.quads ? 16 * (2 * wide_tpn - narrow_tpn) > narrow_tpn : wide_tpn == narrow_tpn;
-        pl.wide = many && (wide_tpn * d->n <= (long long)kGatherTiles || (!half && !second_round && !half_empty));
-        const long long tpn = pl.wide ? wide_tpn : narrow_tpn;
+        const long long wide_tiles = wide_tpn * d->n;
+        pl.shape = kNarrow;
+        if (narrow_tpn * d->n > (long long)kGatherTiles) {
+            if (wide_tiles <= (long long)kGatherTiles) pl.shape = kWide;     // one launch (1x384x19200 FP16: 15.9 -> 12.6 us)
+            else if (long_pays(d, pl.quads, narrow_tpn, wide_tpn)) pl.shape = small_pays(d, pl.quads, wide_tiles) ? kSmall : kLong;
+            else if (wide_pays(d, pl.quads, narrow_tpn, wide_tpn, pl.fused_kch)) pl.shape = kWide;
+        }
+        if (pl.shape != kNarrow) pl.fused_kch = fused_channels_per_lane(d, pl.shape);
+        const long long tpn = pl.shape != kNarrow ? wide_tpn : narrow_tpn;
         pl.one_launch = tpn * d->n <= (long long)kGatherTiles;
         if (tpn * d->n > 0x3fffffffLL) return FQ_ERR_SHAPE;
         pl.vec = kFusedVec;
@@ -917,48 +974,47 @@ fq_status launch(const DistillArgs &k, const Plan &pl, bool want_grad, hipStream
     return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_LAUNCH;
 }
 
-template <typename T, int THREADS, int KCH, bool QUADS, bool WANT_GRAD>
-void launch_fused_kernel(const DistillArgs &k, const Plan &pl, hipStream_t st)
-{
-    const Divisor by = divisor(pl.tiles_per_n);
-    distill_fused_kernel<T, THREADS, KCH, QUADS, WANT_GRAD><<<pl.tiles, THREADS, 0, st>>>(
-        k.a, k.b, k.M, k.C, k.tiles_per_n, by.multiplier, by.shift1 | (unsigned)by.shift2 << 16,
-        pl.neighbours ? pl.tiles : 0u, k);
-}
-
-template <typename T, int KCH, bool QUADS>
+template <typename T, int SHAPE, int KCH, bool QUADS>
 fq_status launch_fused(const DistillArgs &k, const Plan &pl, bool want_grad, hipStream_t st)
 {
-    if (pl.wide) {
-        if (want_grad) launch_fused_kernel<T, kWideThreads, KCH, QUADS, true>(k, pl, st);
-        else launch_fused_kernel<T, kWideThreads, KCH, QUADS, false>(k, pl, st);
-    } else {
-        if (want_grad) launch_fused_kernel<T, kNarrowThreads, KCH, QUADS, true>(k, pl, st);
-        else launch_fused_kernel<T, kNarrowThreads, KCH, QUADS, false>(k, pl, st);
-    }
+    const Divisor by = divisor(pl.tiles_per_n);
+    const auto kernel = want_grad ? distill_fused_kernel<T, SHAPE, KCH, QUADS, true> : distill_fused_kernel<T, SHAPE, KCH, QUADS, false>;
+    kernel<<<pl.tiles, kTileThreads[SHAPE], 0, st>>>(k.a, k.b, k.M, k.C, k.tiles_per_n, by.multiplier,
+                                                     by.shift1 | (unsigned)by.shift2 << 16, pl.neighbours ? pl.tiles : 0u, k);
     if (!pl.one_launch) distill_finish_kernel<<<1, 1024, 0, st>>>(k);
     return hipGetLastError() == hipSuccess ? FQ_OK : FQ_ERR_LAUNCH;
 }
 
-template <typename T, int KCH>
+template <typename T, int SHAPE, int KCH>
 fq_status launch_fused(const DistillArgs &k, const Plan &pl, bool want_grad, hipStream_t st)
 {
-    return pl.quads ? launch_fused<T, KCH, true>(k, pl, want_grad, st) : launch_fused<T, KCH, false>(k, pl, want_grad, st);
+    return pl.quads ? launch_fused<T, SHAPE, KCH, true>(k, pl, want_grad, st) : launch_fused<T, SHAPE, KCH, false>(k, pl, want_grad, st);
+}
+
+template <typename T, int SHAPE>
+fq_status launch_fused(const DistillArgs &k, const Plan &pl, bool want_grad, hipStream_t st)
+{
+    constexpr int most = most_channels_per_lane<T>(SHAPE);
+    switch (pl.fused_kch) {
+    case 2: return launch_fused<T, SHAPE, 2>(k, pl, want_grad, st);
+    case 4: return launch_fused<T, SHAPE, 4>(k, pl, want_grad, st);
+    case 6: if constexpr (most >= 6) return launch_fused<T, SHAPE, 6>(k, pl, want_grad, st); else break;
+    case 8: if constexpr (most >= 8) return launch_fused<T, SHAPE, 8>(k, pl, want_grad, st); else break;
+    case 12: if constexpr (most >= 12) return launch_fused<T, SHAPE, 12>(k, pl, want_grad, st); else break;
+    case 16: if constexpr (most >= 16) return launch_fused<T, SHAPE, 16>(k, pl, want_grad, st); else break;
+    }
+    return FQ_ERR_SHAPE;                           // not reached: make_plan offers only the widths above
 }
 
 template <typename T>
-fq_status launch_fused_width(const DistillArgs &k, const Plan &pl, bool want_grad, hipStream_t st)
+fq_status launch_fused(const DistillArgs &k, const Plan &pl, bool want_grad, hipStream_t st)
 {
-    switch (pl.fused_kch) {
-    case 2: return launch_fused<T, 2>(k, pl, want_grad, st);
-    case 4: return launch_fused<T, 4>(k, pl, want_grad, st);
-    case 6: return launch_fused<T, 6>(k, pl, want_grad, st);
-    case 8: return launch_fused<T, 8>(k, pl, want_grad, st);
-    default: break;
+    switch (pl.shape) {
+    case kWide: return launch_fused<T, kWide>(k, pl, want_grad, st);
+    case kLong: return launch_fused<T, kLong>(k, pl, want_grad, st);
+    case kSmall: return launch_fused<T, kSmall>(k, pl, want_grad, st);
+    default: return launch_fused<T, kNarrow>(k, pl, want_grad, st);
     }
-    if (sizeof(T) == 2 && pl.fused_kch == 12) return launch_fused<_Float16, 12>(k, pl, want_grad, st);
-    if (sizeof(T) == 2 && pl.fused_kch == 16) return launch_fused<_Float16, 16>(k, pl, want_grad, st);
-    return FQ_ERR_SHAPE;                           // not reached: make_plan offers only the widths above
 }
 
 // A number that no other call of this process has, and that memory does not hold by chance: a counter from
@@ -1039,8 +1095,7 @@ static fq_status distill_loss(const fq_distill *d, void *workspace, size_t ws_by
     pl.neighbours = pl.fused_kch && (!pl.quads || d->inner * (d->dtype == FQ_F16 ? 2 : 4) % 128 != 0);
     if (pl.fused_kch) {
         k.coef = nullptr;
-        return d->dtype == FQ_F16 ? launch_fused_width<_Float16>(k, pl, grad, st)
-                                  : launch_fused_width<float>(k, pl, grad, st);
+        return d->dtype == FQ_F16 ? launch_fused<_Float16>(k, pl, grad, st) : launch_fused<float>(k, pl, grad, st);
     }
     if (d->dtype == FQ_F16) {
         switch (pl.vec) {
