@@ -4,15 +4,21 @@ hipcc cross-compiles for gfx950 without a GPU.  Flags: IEEE arithmetic only (no 
 implicit FMA contraction -- the kernels call fma explicitly where they want one) and no packed
 FP32 instructions.  The first 14 dwords of a kernel's scalar arguments (all that fit beside the address of the
 rest) come in registers with the launch instead of being loaded by every wavefront.
+
+The binding's native calls (csrc/fq_call.c) go into a CPython extension next to the library, by the host's C compiler.
 """
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfq.so")
 SOURCES = [os.path.join(CSRC, f) for f in ("fq_kernels.hip", "fq_distill.hip", "fq_api.cpp")]
+CALL_SOURCE = os.path.join(CSRC, "fq_call.c")
+CALL = os.path.join(HERE, "_fqcall" + sysconfig.get_config_var("EXT_SUFFIX"))
+CC = os.environ.get("CC", "gcc")
 HEADERS = [os.path.join(CSRC, "fq_internal.h"), os.path.join(CSRC, "fq_device.h"),
            os.path.join(HERE, "..", "include", "fq.h")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -22,10 +28,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(CALL):
         return True
-    t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(p) > t for p in SOURCES + HEADERS)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(CALL))
+    return any(os.path.getmtime(p) > t for p in SOURCES + HEADERS + [CALL_SOURCE])
 
 
 def build(force: bool = True, extra=()) -> str:
@@ -46,12 +52,23 @@ def build(force: bool = True, extra=()) -> str:
     if p.returncode != 0:
         raise subprocess.CalledProcessError(p.returncode, cmd)
     os.replace(tmp, LIB)
+    build_call()
     return LIB
+
+
+def build_call() -> str:
+    """The extension; it finds the library in its own folder."""
+    tmp = CALL + ".tmp.%d" % os.getpid()
+    subprocess.run([CC, "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-missing-field-initializers",
+                    "-I", sysconfig.get_paths()["include"], CALL_SOURCE, "-L", HERE, "-l:libfq.so", "-Wl,-rpath,$ORIGIN",
+                    "-o", tmp], check=True)
+    os.replace(tmp, CALL)
+    return CALL
 
 
 def ensure_built() -> str:
     """Build only if no library is there (tests, smoke and bench load what is built)."""
-    return LIB if os.path.exists(LIB) else build(force=True)
+    return LIB if os.path.exists(LIB) and os.path.exists(CALL) else build(force=True)
 
 
 if __name__ == "__main__":

@@ -170,13 +170,33 @@ fq_status validate_one(const fq_tensor &t, int mode, Plan &p)
     return FQ_OK;
 }
 
+// Where the parts of a workspace lie: [descriptor table][partial sums][slots].
+struct WorkspaceShape {
+    size_t table_bytes, partial_off, counter_off, total;
+};
+
+WorkspaceShape workspace_shape(long long n, int mode, long long partials, long long slots)
+{
+    WorkspaceShape w;
+    w.table_bytes = round_up((size_t)n * kTableEntryBytes, kAlign);
+    w.partial_off = w.table_bytes;
+    w.counter_off = w.partial_off;
+    w.total = w.table_bytes;
+    if (mode == FQ_MODE_BACKWARD) {
+        w.counter_off = w.partial_off + round_up((size_t)partials * sizeof(double), kAlign);
+        w.total = w.counter_off + round_up((size_t)slots * sizeof(unsigned long long), kAlign);
+    }
+    if (w.total < kAlign) w.total = kAlign;
+    return w;
+}
+
 struct Layout {
     std::vector<Plan> plans;
     long long blocks = 0;        // grid of the main kernel
     long long channels = 0;      // grid of the finalize kernel
     long long slots = 0;         // 64-bit slots (backward)
     long long partials = 0;      // doubles
-    size_t table_bytes = 0, partial_off = 0, counter_off = 0, total = 0;
+    WorkspaceShape at = {0, 0, 0, 0};
     bool any_empty_with_channels = false;
 };
 
@@ -211,15 +231,7 @@ fq_status make_layout(const fq_tensor *ts, int n, int mode, Layout &L)
             L.slots += ts[i].channels * (1 + (long long)p.sub);
         }
     }
-    L.table_bytes = round_up((size_t)n * kTableEntryBytes, kAlign);
-    L.partial_off = L.table_bytes;
-    L.counter_off = L.partial_off;
-    L.total = L.table_bytes;
-    if (mode == FQ_MODE_BACKWARD) {
-        L.counter_off = L.partial_off + round_up((size_t)L.partials * sizeof(double), kAlign);
-        L.total = L.counter_off + round_up((size_t)L.slots * sizeof(unsigned long long), kAlign);
-    }
-    if (L.total < kAlign) L.total = kAlign;
+    L.at = workspace_shape(n, mode, L.partials, L.slots);
     return FQ_OK;
 }
 
@@ -291,8 +303,8 @@ void build_table(const fq_tensor *ts, int n, int mode, const Layout &L, char *wo
                  std::vector<DevTensor> &out)
 {
     out.resize((size_t)n);
-    double *partials = workspace ? (double *)(workspace + L.partial_off) : nullptr;
-    unsigned long long *slots = workspace ? (unsigned long long *)(workspace + L.counter_off) : nullptr;
+    double *partials = workspace ? (double *)(workspace + L.at.partial_off) : nullptr;
+    unsigned long long *slots = workspace ? (unsigned long long *)(workspace + L.at.counter_off) : nullptr;
     Cursor at;
     for (int i = 0; i < n; ++i) {
         const fq_tensor &t = ts[i];
@@ -372,10 +384,9 @@ struct Prepared {
     std::vector<DevTensor> table;     // host copy of the device descriptors
 };
 
-// Validate, plan, build the device descriptors and (for table launches) copy them to the head of
-// the workspace.  Nothing is launched.
-fq_status prepare(const fq_tensor *ts, int n, int mode, bool use_table, void *workspace, size_t ws_bytes,
-                  void *stream, Prepared &P)
+// Validate, plan, build the device descriptors of a list and copy them to the head of the workspace.  Nothing is
+// launched.
+fq_status prepare(const fq_tensor *ts, int n, int mode, void *workspace, size_t ws_bytes, void *stream, Prepared &P)
 {
     Layout L;
     fq_status st = make_layout(ts, n, mode, L);
@@ -384,26 +395,18 @@ fq_status prepare(const fq_tensor *ts, int n, int mode, bool use_table, void *wo
     P.args.n = n;
     P.mode = mode;
     if (n == 0) return FQ_OK;
-    const bool need_ws = use_table || mode == FQ_MODE_BACKWARD;
-    if (need_ws) {
-        if (!workspace || ws_bytes < L.total) return FQ_ERR_WORKSPACE;
-        if (!aligned(workspace, kAlign)) return FQ_ERR_ALIGN;
-    }
+    if (!workspace || ws_bytes < L.at.total) return FQ_ERR_WORKSPACE;
+    if (!aligned(workspace, kAlign)) return FQ_ERR_ALIGN;
     std::vector<DevTensor> &table = P.table;
     build_table(ts, n, mode, L, (char *)workspace, table);
-    if (use_table) {
-        P.args.table = (const DevTensor *)workspace;
-        // the descriptors, and behind them their first blocks packed
-        std::vector<char> image((size_t)n * kTableEntryBytes);
-        std::memcpy(image.data(), table.data(), (size_t)n * sizeof(DevTensor));
-        for (int i = 0; i < n; ++i)
-            std::memcpy(image.data() + (size_t)n * sizeof(DevTensor) + (size_t)i * sizeof(unsigned),
-                        &table[(size_t)i].block_begin, sizeof(unsigned));
-        if (copy_table_async(workspace, image.data(), image.size(), stream) != 0) return FQ_ERR_LAUNCH;
-    } else {
-        P.args.one = table[0];
-        set_grid_shape(P.args.one);
-    }
+    P.args.table = (const DevTensor *)workspace;
+    // the descriptors, and behind them their first blocks packed
+    std::vector<char> image((size_t)n * kTableEntryBytes);
+    std::memcpy(image.data(), table.data(), (size_t)n * sizeof(DevTensor));
+    for (int i = 0; i < n; ++i)
+        std::memcpy(image.data() + (size_t)n * sizeof(DevTensor) + (size_t)i * sizeof(unsigned),
+                    &table[(size_t)i].block_begin, sizeof(unsigned));
+    if (copy_table_async(workspace, image.data(), image.size(), stream) != 0) return FQ_ERR_LAUNCH;
     P.blocks = L.blocks;
     P.channels = L.channels;
     P.any_empty_with_channels = L.any_empty_with_channels;
@@ -439,11 +442,10 @@ fq_status launch_prepared(const Prepared &P, void *stream, const AdamBias *bias 
     return FQ_OK;
 }
 
-fq_status run(const fq_tensor *ts, int n, int mode, bool use_table, void *workspace, size_t ws_bytes,
-              void *stream)
+fq_status run_list(const fq_tensor *ts, int n, int mode, void *workspace, size_t ws_bytes, void *stream)
 {
     Prepared P;
-    fq_status st = prepare(ts, n, mode, use_table, workspace, ws_bytes, stream, P);
+    fq_status st = prepare(ts, n, mode, workspace, ws_bytes, stream, P);
     if (st != FQ_OK) return st;
     return launch_prepared(P, stream);
 }
@@ -459,8 +461,38 @@ fq_status plan_single(const fq_tensor &t, int mode, Plan &p)
     return FQ_OK;
 }
 
-// fq_backward with the partial sums and slots in the library's built-in scratch array.  Touches
-// no allocator, host or device: one descriptor on the stack, passed by value to the kernel.
+// One tensor's launch with its partial sums and slots where the caller says (nullptr: forward).  Touches no
+// allocator, host or device: one descriptor on the stack, passed by value to the kernel.
+fq_status launch_single(const fq_tensor &t, const Plan &p, int mode, double *partials, unsigned long long *slots, void *stream)
+{
+    Prepared P;                               // its table (a vector) stays empty: nothing is allocated
+    std::memset(&P.args, 0, sizeof P.args);
+    P.args.n = 1;
+    P.args.one = describe(t, p, mode, partials, slots, Cursor());
+    set_grid_shape(P.args.one);
+    P.mode = mode;
+    P.blocks = p.blocks;
+    P.channels = t.channels;
+    P.any_empty_with_channels = p.numel == 0 && t.channels > 0;
+    P.two_pass = (t.flags & FQ_FLAG_TWO_PASS) != 0 || P.any_empty_with_channels;
+    return launch_prepared(P, stream);
+}
+
+// fq_forward and fq_backward: the launch of a list of one tensor, and its workspace, without the list.
+fq_status run_single(const fq_tensor &t, int mode, void *workspace, size_t ws_bytes, void *stream)
+{
+    Plan p;
+    fq_status st = plan_single(t, mode, p);
+    if (st != FQ_OK) return st;
+    if (mode == FQ_MODE_FORWARD) return launch_single(t, p, mode, nullptr, nullptr, stream);
+    const WorkspaceShape w = workspace_shape(1, mode, p.units, t.channels * (1 + (long long)p.sub));
+    if (!workspace || ws_bytes < w.total) return FQ_ERR_WORKSPACE;
+    if (!aligned(workspace, kAlign)) return FQ_ERR_ALIGN;
+    return launch_single(t, p, mode, (double *)((char *)workspace + w.partial_off),
+                         (unsigned long long *)((char *)workspace + w.counter_off), stream);
+}
+
+// fq_backward with the partial sums and slots in the library's built-in scratch array.
 fq_status run_static(const fq_tensor &t, void *stream)
 {
     Plan p;
@@ -472,18 +504,8 @@ fq_status run_static(const fq_tensor &t, void *stream)
         return FQ_ERR_WORKSPACE;
     void *base = nullptr;
     if (static_scratch(&base, stream) != 0) return FQ_ERR_LAUNCH;
-    Prepared P;                               // its table (a vector) stays empty: nothing is allocated
-    std::memset(&P.args, 0, sizeof P.args);
-    P.args.n = 1;
-    P.args.one = describe(t, p, FQ_MODE_BACKWARD, (double *)((char *)base + kStaticSlotBytes),
-                          (unsigned long long *)base, Cursor());
-    set_grid_shape(P.args.one);
-    P.mode = FQ_MODE_BACKWARD;
-    P.blocks = p.blocks;
-    P.channels = t.channels;
-    P.any_empty_with_channels = p.numel == 0 && t.channels > 0;
-    P.two_pass = (t.flags & FQ_FLAG_TWO_PASS) != 0 || P.any_empty_with_channels;
-    return launch_prepared(P, stream);
+    return launch_single(t, p, FQ_MODE_BACKWARD, (double *)((char *)base + kStaticSlotBytes), (unsigned long long *)base,
+                         stream);
 }
 
 }  // namespace
@@ -510,7 +532,7 @@ size_t fq_workspace_bytes(const fq_tensor *ts, int n, int mode)
     try {
         fq::Layout L;
         if (fq::make_layout(ts, n, mode, L) != FQ_OK) return 0;
-        return L.total;
+        return L.at.total;
     } catch (...) {
         return 0;
     }
@@ -551,13 +573,13 @@ fq_status fq_workspace_init(void *workspace, size_t ws_bytes, void *hip_stream)
 fq_status fq_forward(const fq_tensor *t, void *hip_stream)
 {
     if (!t) return FQ_ERR_NULL;
-    FQ_GUARDED(fq::run(t, 1, FQ_MODE_FORWARD, false, nullptr, 0, hip_stream), FQ_ERR_LAUNCH)
+    FQ_GUARDED(fq::run_single(*t, FQ_MODE_FORWARD, nullptr, 0, hip_stream), FQ_ERR_LAUNCH)
 }
 
 fq_status fq_backward(const fq_tensor *t, void *workspace, size_t ws_bytes, void *hip_stream)
 {
     if (!t) return FQ_ERR_NULL;
-    FQ_GUARDED(fq::run(t, 1, FQ_MODE_BACKWARD, false, workspace, ws_bytes, hip_stream), FQ_ERR_LAUNCH)
+    FQ_GUARDED(fq::run_single(*t, FQ_MODE_BACKWARD, workspace, ws_bytes, hip_stream), FQ_ERR_LAUNCH)
 }
 
 fq_status fq_backward_static(const fq_tensor *t, void *hip_stream)
@@ -569,7 +591,7 @@ fq_status fq_backward_static(const fq_tensor *t, void *hip_stream)
 fq_status fq_multi_tensor(const fq_tensor *ts, int n, int mode, void *workspace, size_t ws_bytes,
                           void *hip_stream)
 {
-    FQ_GUARDED(fq::run(ts, n, mode, true, workspace, ws_bytes, hip_stream), FQ_ERR_LAUNCH)
+    FQ_GUARDED(fq::run_list(ts, n, mode, workspace, ws_bytes, hip_stream), FQ_ERR_LAUNCH)
 }
 
 fq_status fq_probe_stream(int inputs, const void *a, const void *b, void *out, size_t bytes, void *hip_stream)
@@ -593,7 +615,7 @@ struct fq_plan {
 static fq_status fill_plan(fq_plan *p, const fq_tensor *ts, int n, int mode, void *workspace, size_t ws_bytes,
                            void *hip_stream)
 {
-    fq_status st = fq::prepare(ts, n, mode, true, workspace, ws_bytes, hip_stream, p->prepared);
+    fq_status st = fq::prepare(ts, n, mode, workspace, ws_bytes, hip_stream, p->prepared);
     if (st != FQ_OK) return st;
     p->workspace = workspace;
     p->beta1.resize((size_t)n); p->beta2.resize((size_t)n); p->has_adam.resize((size_t)n);
