@@ -14,9 +14,10 @@ constexpr int kComputeUnits = 256;   // MI355X; used by the host to balance bloc
 // Three blocks per compute unit: up to here every launch has all its blocks resident at once, whatever its kernel's
 // registers (forward: eight would be; backward: four to eight), and as many on one compute unit as on another.
 constexpr unsigned kResidentBlocks = 3 * kComputeUnits;
-// Backward launches of at most that many blocks take the schedule made for one burst from here on
-// (launch_backward_shaped has the figures): enough blocks and enough of data.
-constexpr unsigned kBurstLeastBlocksF16 = 640, kBurstLeastBlocksF32 = 400;
+// Backward launches of so many blocks, all resident at once, of so many vectors or more take the schedule made for one
+// burst (burst_pays has the figures).
+constexpr unsigned kBurstLeastBlocksF16 = kResidentBlocks + 1, kBurstMostBlocksF16 = 4 * kComputeUnits;
+constexpr unsigned kBurstLeastBlocksF32 = 400, kBurstMostBlocksF32 = kResidentBlocks;
 constexpr unsigned kBurstLeastVecsF16 = 900, kBurstLeastVecsF32 = 600;
 // Channels with more units than this have 16 (32) further 64-bit slots in the workspace.  No kernel uses
 // them; they keep fq_workspace_bytes and fq_layout at the values that callers have sized memory by.

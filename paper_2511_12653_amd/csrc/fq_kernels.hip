@@ -587,8 +587,8 @@ __device__ __forceinline__ double backward_chunk(const DevTensor &d, const Chunk
     return sum;
 }
 
-// The same sum with the schedule for launches of at most three blocks per compute unit, all resident at
-// once (the 1x384x120x160 FP16 tensor).  Such a launch is one burst: every wavefront asks
+// The same sum with the schedule for launches whose blocks are all resident at once (see burst_pays; a
+// 1x384x9600 FP32 tensor).  Such a launch is one burst: every wavefront asks
 // for its whole chunk at the start, the data trickles in over the next microseconds, and whatever a
 // wavefront still has to compute after its last row has landed is added to the kernel's duration,
 // with nothing left to hide it.  So all x rows are requested before all gy rows; what depends on x
@@ -1586,20 +1586,21 @@ static void launch_backward_typed(const DevTensor &d, unsigned blocks, bool fuse
 }
 
 // The burst schedule (backward_chunk_short) pays in launches that are resident at once and move much data: its
-// arithmetic lies in front of the last loads, but it is more arithmetic and more registers.  The line stands at three
-// blocks per compute unit; four FP16 blocks would still be resident, and there it still gains (1024 blocks x 1200
-// vectors 13.3 / 12.9 interleaved / burst, 800 x 1200 11.8 / 11.2), with more than four it loses (1200 x 1200 14.7 / 16.4;
-// FP32 1024 x 1200 no change).  Measured against the interleaved schedule, us, burst / interleaved:
-//   FP16  768 blocks x 1200 vectors 9.2 / 9.65   768 x 1000 7.8 / 8.2   700 x 1200 9.2 / 9.2
-//         600 x 1200 8.7 / 8.3   768 x 800 7.2 / 7.1   768 x 600 6.2 / 5.7   400 x 1200 7.1 / 6.3
-//   FP32  768 x 1200 8.5 / 8.9   512 x 1200 6.2 / 6.5   400 x 1200 5.4 / 5.9   768 x 600 4.95 / 5.3
+// arithmetic lies in front of the last loads, but it is more arithmetic and more registers.  Since gx goes out behind
+// the sum in both schedules, FP16 gains by it only where each compute unit has a fourth block, and loses with three
+// (registers let it hold four blocks of burst FP16, seven interleaved).  Measured against the interleaved schedule, us,
+// burst / interleaved:
+//   FP16  300 x 1200 x 2 (600 blocks) 9.0 / 8.6   660 9.07 / 8.65   768 x 1200 vectors 9.3 to 10.4 / 9.4   768 x 800 7.6 / 7.15
+//         800 x 1200 10.62 / 10.76   800, two units apart 10.89 / 11.10   960 11.74 / 12.05   1000 x 1000 10.14 / 10.31
+//         1024 x 1200 12.5 / 12.5
+//   FP32  768 x 1200 9.53 / 9.77   512 x 1200 6.9 / 7.1   400 x 1200 6.1 / 6.3   768 x 600 4.95 / 5.3
 //         512 x 600 4.2 / 4.3   400 x 600 4.1 / 4.0   768 x 432 5.0 / 4.9   64 x 144 3.0 / 2.9
 // Where the sums are gathered it is not used, and the kernel with it leaves the gathering out (one scale, 153600 FP32
 // elements 4.13 / 3.87, 921600 FP16 4.77 / 4.40, 4915200 FP16 8.6 / 8.0).
 template <typename T> static bool burst_pays(const DevTensor &d, unsigned blocks)
 {
     const bool half = sizeof(T) == 2;
-    return blocks <= kResidentBlocks && blocks >= (half ? kBurstLeastBlocksF16 : kBurstLeastBlocksF32) &&
+    return blocks <= (half ? kBurstMostBlocksF16 : kBurstMostBlocksF32) && blocks >= (half ? kBurstLeastBlocksF16 : kBurstLeastBlocksF32) &&
            chunk_vecs<T>(d) >= (half ? kBurstLeastVecsF16 : kBurstLeastVecsF32);
 }
 
