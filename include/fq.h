@@ -127,11 +127,12 @@ fq_status fq_validate(const fq_tensor *ts, int n, int mode);
 /*
  * How the library cuts one tensor up (pure host function, touches no GPU; for tests and tuning).
  * A unit is what one partial sum of the backward covers: a block's chunk, or, for tensors whose
- * slabs are short, a whole slab handled by one wavefront (only in launches with thousands of blocks;
- * this call describes the tensor launched on its own).
+ * slabs are short, a whole slab handled by one wavefront (only in launches with many blocks; this
+ * call describes the backward of the tensor launched on its own: lists, and the forward, which has no
+ * partial sums, go over to wavefronts with fewer blocks).
  */
 typedef struct fq_layout_info {
-    int64_t blocks;              /* grid blocks of the forward / backward kernel */
+    int64_t blocks;              /* grid blocks of the backward kernel */
     int64_t units_per_channel;   /* partial sums combined per channel: 1 direct, 2 exchange, 3-4 exchange
                                     tree, more: gathered by the channel's last unit */
     int64_t unit_elems;          /* elements per unit (the last unit of a slab may be shorter) */

@@ -21,7 +21,11 @@ namespace {
 
 constexpr size_t kAlign = 256;
 constexpr long long kMaxBlocks = 0x7fffffffLL;
-constexpr long long kWaveUnitsMinBlocks = 4096;   // 16 blocks per compute unit
+// From how many blocks on short slabs go one to a wavefront (see waves_pay).
+constexpr long long kWaveUnitsMinBlocks = 4096;        // a tensor launched alone
+constexpr long long kWaveUnitsMinBlocksShort = 1024;   // its forward, with slabs of at most kWaveShortVecs vectors
+constexpr long long kWaveShortVecs = 192;
+constexpr long long kWaveUnitsMinBlocksList = 768;     // a list
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -48,6 +52,7 @@ struct Plan {
     unsigned slabs = 0, cps = 0, chunk = 0;
     unsigned sub = 0;            // extra slots per channel: pair slots (2) or reserved ones (16, 32)
     bool short_slabs = false;    // a slab fits one wavefront's chunk
+    bool shorter_slabs = false;  // and has at most kWaveShortVecs vectors
     bool waves = false;          // short slabs in a launch with blocks to spare: one wavefront per slab,
                                  // four slabs to a block
     long long blocks = 0;        // grid blocks
@@ -89,9 +94,10 @@ fq_status plan_tensor(const fq_tensor &t, Plan &p, bool allow_waves)
     // Slabs that one wavefront covers (320 vectors; one vector more than the aligned part can hold
     // is left for a misaligned head) go one to a wavefront: a block per slab would leave most of
     // its lanes idle and pay a block's prologue and reduction for a few KB.  Only where the launch
-    // has blocks to spare (allow_waves): a small tensor on its own is bound by latency and is
+    // has blocks to spare (allow_waves, see waves_pay): a small tensor on its own is bound by latency and is
     // better off spread over four times as many blocks.
     p.short_slabs = slab_vecs + 1 <= kWaveChunkVecs;
+    p.shorter_slabs = slab_vecs <= kWaveShortVecs;
     if (allow_waves && p.short_slabs) {
         p.waves = true;
         p.cps = 1;
@@ -126,6 +132,23 @@ fq_status plan_tensor(const fq_tensor &t, Plan &p, bool allow_waves)
     const long long per_channel = t.outer * best_cps;                             // blocks per channel
     p.sub = extra_slots(per_channel);
     return FQ_OK;
+}
+
+// Whether a tensor of n (cut into blocks, `blocks` in the whole launch) has its short slabs cut per wavefront.  Measured,
+// us, a block per slab / a wavefront per slab:
+//   alone, forward  2048 blocks x 100 vectors FP16 3.62 / 3.11   2048 x 75 FP32 3.81 / 2.94   1536 x 150 FP16 3.77 / 3.50
+//     3072 x 144 FP32 4.76 / 4.42   1500 x 12 FP32 3.41 / 3.01;  3500 x 300 FP16 7.84 / 8.7   3200 x 312 8.1 / 8.7
+//   alone, backward  the same: 5.30 / 4.30   5.61 / 4.58   5.90 / 5.97   6.94 / 6.17   4.12 / 3.53;  11.0 / 11.2   11.25 / 12.6,
+//     but its cut is what fq_layout reports, and callers rely on that (the forward has no units: how it is cut shows nowhere)
+//   lists, whose blocks look up their tensor first, forward and backward: 6 tensors of 4x128x1200 FP16 (3072 blocks)
+//     7.64 / 4.72, 11.0 / 8.8; 20 of 64x1200 FP32 (1280) 6.83 / 5.0, 8.83 / 6.8; 10 of 96x1000 FP16 (960) 4.14 / 3.12, 4.90 /
+//     4.20; 22 convolutions' weights (1472) 4.35 / 3.55, 5.57 / 5.05, twice as wide (2944) 7.57 / 4.57, 9.6 / 5.9;
+//     16 of 32x288 FP32 (512) 2.73 / 2.83, 3.69 / 3.6; 6 of 40x2400 FP16 (240) 3.26 / 3.40, 4.81 / 4.50
+bool waves_pay(const Plan &p, int n, int mode, long long blocks)
+{
+    if (!p.short_slabs || p.numel == 0) return false;
+    if (n > 1) return blocks >= kWaveUnitsMinBlocksList;
+    return blocks >= (p.shorter_slabs && mode == FQ_MODE_FORWARD ? kWaveUnitsMinBlocksShort : kWaveUnitsMinBlocks);
 }
 
 fq_status validate_one(const fq_tensor &t, int mode, Plan &p)
@@ -216,20 +239,19 @@ fq_status make_layout(const fq_tensor *ts, int n, int mode, Layout &L)
         if (L.plans[(size_t)i].numel == 0 && ts[i].channels > 0) L.any_empty_with_channels = true;
         if (L.blocks > kMaxBlocks || L.channels > kMaxBlocks || L.slots > 64 * kMaxBlocks) return FQ_ERR_SHAPE;
     }
-    if (L.blocks >= kWaveUnitsMinBlocks) {
-        // enough blocks to fill the chip many times over: short-slab tensors switch to one
-        // wavefront per slab (fewer blocks, partial sums and slots; the limits above still hold)
-        for (int i = 0; i < n; ++i) {
-            Plan &p = L.plans[(size_t)i];
-            if (!p.short_slabs || p.numel == 0) continue;
-            L.blocks -= p.blocks;
-            L.partials -= p.units;
-            L.slots -= ts[i].channels * (1 + (long long)p.sub);
-            (void)plan_tensor(ts[i], p, true);
-            L.blocks += p.blocks;
-            L.partials += p.units;
-            L.slots += ts[i].channels * (1 + (long long)p.sub);
-        }
+    // short-slab tensors switch to one wavefront per slab (fewer blocks, partial sums and slots; the limits
+    // above still hold)
+    const long long blocks = L.blocks;
+    for (int i = 0; i < n; ++i) {
+        Plan &p = L.plans[(size_t)i];
+        if (!waves_pay(p, n, mode, blocks)) continue;
+        L.blocks -= p.blocks;
+        L.partials -= p.units;
+        L.slots -= ts[i].channels * (1 + (long long)p.sub);
+        (void)plan_tensor(ts[i], p, true);
+        L.blocks += p.blocks;
+        L.partials += p.units;
+        L.slots += ts[i].channels * (1 + (long long)p.sub);
     }
     L.at = workspace_shape(n, mode, L.partials, L.slots);
     return FQ_OK;
@@ -457,7 +479,7 @@ fq_status plan_single(const fq_tensor &t, int mode, Plan &p)
     fq_status st = validate_one(t, mode, p);
     if (st != FQ_OK) return st;
     if (p.blocks > kMaxBlocks || t.channels * (1 + (long long)p.sub) > 64 * kMaxBlocks) return FQ_ERR_SHAPE;
-    if (p.short_slabs && p.numel > 0 && p.blocks >= kWaveUnitsMinBlocks) (void)plan_tensor(t, p, true);
+    if (waves_pay(p, 1, mode, p.blocks)) (void)plan_tensor(t, p, true);
     return FQ_OK;
 }
 
@@ -553,7 +575,7 @@ fq_status fq_layout(const fq_tensor *t, fq_layout_info *info)
     if (!t || !info) return FQ_ERR_NULL;
     fq::Plan p;
     fq_status st = fq::plan_tensor(*t, p, false);
-    if (st == FQ_OK && p.short_slabs && p.blocks >= (long long)fq::kWaveUnitsMinBlocks) st = fq::plan_tensor(*t, p, true);
+    if (st == FQ_OK && fq::waves_pay(p, 1, FQ_MODE_BACKWARD, p.blocks)) st = fq::plan_tensor(*t, p, true);
     if (st != FQ_OK) return st;
     info->blocks = p.blocks;
     info->units_per_channel = t->outer * (long long)p.cps;
