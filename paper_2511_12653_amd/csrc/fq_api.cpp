@@ -22,10 +22,10 @@ namespace {
 constexpr size_t kAlign = 256;
 constexpr long long kMaxBlocks = 0x7fffffffLL;
 // From how many blocks on short slabs go one to a wavefront (see waves_pay).
-constexpr long long kWaveUnitsMinBlocks = 4096;        // a tensor launched alone
-constexpr long long kWaveUnitsMinBlocksShort = 1024;   // its forward, with slabs of at most kWaveShortVecs vectors
+constexpr long long kWaveUnitsMinBlocks = 4096;        // of the launch
+constexpr long long kWaveUnitsMinBlocksShort = 1024;   // the forward of one tensor, of slabs of at most kWaveShortVecs vectors
 constexpr long long kWaveShortVecs = 192;
-constexpr long long kWaveUnitsMinBlocksList = 768;     // a list
+constexpr long long kWaveUnitsMinBlocksList = 768;     // of the tensors with short slabs in a list
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -134,7 +134,8 @@ fq_status plan_tensor(const fq_tensor &t, Plan &p, bool allow_waves)
     return FQ_OK;
 }
 
-// Whether a tensor of n (cut into blocks, `blocks` in the whole launch) has its short slabs cut per wavefront.  Measured,
+// Whether a tensor of n (cut into blocks, `blocks` in the whole launch, `short_blocks` of tensors with short slabs) has
+// its short slabs cut per wavefront.  Measured,
 // us, a block per slab / a wavefront per slab:
 //   alone, forward  2048 blocks x 100 vectors FP16 3.62 / 3.11   2048 x 75 FP32 3.81 / 2.94   1536 x 150 FP16 3.77 / 3.50
 //     3072 x 144 FP32 4.76 / 4.42   1500 x 12 FP32 3.41 / 3.01;  3500 x 300 FP16 7.84 / 8.7   3200 x 312 8.1 / 8.7
@@ -143,11 +144,12 @@ fq_status plan_tensor(const fq_tensor &t, Plan &p, bool allow_waves)
 //   lists, whose blocks look up their tensor first, forward and backward: 6 tensors of 4x128x1200 FP16 (3072 blocks)
 //     7.64 / 4.72, 11.0 / 8.8; 20 of 64x1200 FP32 (1280) 6.83 / 5.0, 8.83 / 6.8; 10 of 96x1000 FP16 (960) 4.14 / 3.12, 4.90 /
 //     4.20; 22 convolutions' weights (1472) 4.35 / 3.55, 5.57 / 5.05, twice as wide (2944) 7.57 / 4.57, 9.6 / 5.9;
-//     16 of 32x288 FP32 (512) 2.73 / 2.83, 3.69 / 3.6; 6 of 40x2400 FP16 (240) 3.26 / 3.40, 4.81 / 4.50
-bool waves_pay(const Plan &p, int n, int mode, long long blocks)
+//     16 of 32x288 FP32 (512) 2.73 / 2.83, 3.69 / 3.6; 6 of 40x2400 FP16 (240) 3.26 / 3.40, 4.81 / 4.50.  A few short slabs beside
+//     larger ones end late as wavefronts (384x3456 and 128x1152 FP32, 768 + 128 blocks, backward 6.1 / 6.8)
+bool waves_pay(const Plan &p, int n, int mode, long long blocks, long long short_blocks)
 {
     if (!p.short_slabs || p.numel == 0) return false;
-    if (n > 1) return blocks >= kWaveUnitsMinBlocksList;
+    if (n > 1) return blocks >= kWaveUnitsMinBlocks || short_blocks >= kWaveUnitsMinBlocksList;
     return blocks >= (p.shorter_slabs && mode == FQ_MODE_FORWARD ? kWaveUnitsMinBlocksShort : kWaveUnitsMinBlocks);
 }
 
@@ -242,9 +244,12 @@ fq_status make_layout(const fq_tensor *ts, int n, int mode, Layout &L)
     // short-slab tensors switch to one wavefront per slab (fewer blocks, partial sums and slots; the limits
     // above still hold)
     const long long blocks = L.blocks;
+    long long short_blocks = 0;
+    for (const Plan &p : L.plans)
+        if (p.short_slabs) short_blocks += p.blocks;
     for (int i = 0; i < n; ++i) {
         Plan &p = L.plans[(size_t)i];
-        if (!waves_pay(p, n, mode, blocks)) continue;
+        if (!waves_pay(p, n, mode, blocks, short_blocks)) continue;
         L.blocks -= p.blocks;
         L.partials -= p.units;
         L.slots -= ts[i].channels * (1 + (long long)p.sub);
@@ -479,7 +484,7 @@ fq_status plan_single(const fq_tensor &t, int mode, Plan &p)
     fq_status st = validate_one(t, mode, p);
     if (st != FQ_OK) return st;
     if (p.blocks > kMaxBlocks || t.channels * (1 + (long long)p.sub) > 64 * kMaxBlocks) return FQ_ERR_SHAPE;
-    if (waves_pay(p, 1, mode, p.blocks)) (void)plan_tensor(t, p, true);
+    if (waves_pay(p, 1, mode, p.blocks, p.blocks)) (void)plan_tensor(t, p, true);
     return FQ_OK;
 }
 
@@ -575,7 +580,7 @@ fq_status fq_layout(const fq_tensor *t, fq_layout_info *info)
     if (!t || !info) return FQ_ERR_NULL;
     fq::Plan p;
     fq_status st = fq::plan_tensor(*t, p, false);
-    if (st == FQ_OK && fq::waves_pay(p, 1, FQ_MODE_BACKWARD, p.blocks)) st = fq::plan_tensor(*t, p, true);
+    if (st == FQ_OK && fq::waves_pay(p, 1, FQ_MODE_BACKWARD, p.blocks, p.blocks)) st = fq::plan_tensor(*t, p, true);
     if (st != FQ_OK) return st;
     info->blocks = p.blocks;
     info->units_per_channel = t->outer * (long long)p.cps;

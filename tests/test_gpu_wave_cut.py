@@ -1,4 +1,4 @@
-"""Slabs that go one to a wavefront: in lists from 768 blocks on, and in the forward of one tensor from 1024 blocks of at
+"""Slabs that go one to a wavefront: in lists from 768 blocks of short slabs on, and in the forward of one tensor from 1024 blocks of at
 most 192 vectors on.  Both sides of the lines, slabs off the 16-byte grid, a number of slabs that is no multiple of four
 and members of a list that stay with blocks.  Against the oracle (bars as everywhere); lists also against the same
 tensors launched alone, whose sums are cut and added the same."""
@@ -39,6 +39,7 @@ def test_forward_alone(dtype, outer, channels, inner, what):
     [(np.float32, 1, 383, 49), (np.float16, 1, 384, 800)],                                   # 767 blocks
     [(np.float32, 1, 384, 49), (np.float16, 1, 384, 800)],                                   # 768
     [(np.float16, 4, 65, 1200), (np.float32, 1, 333, 147), (np.float16, 1, 3, 40000), (np.float32, 300, 1, 7)],
+    [(np.float32, 1, 384, 3456), (np.float32, 1, 128, 1152)],                                # few short ones: blocks
     [(np.float32, 1, 700, 319 * 4), (np.float32, 1, 70, 320 * 4), (np.float16, 70, 2, 9)],   # the longest slab, one more
 ])
 def test_lists(shapes):
