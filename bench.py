@@ -46,15 +46,15 @@ SERIES_MIN_PER_TRAIN = 60      # ... of at least this many back-to-back launches
 # known size in the same run); the tables are in profiles/.  An entry is None until its kernel's
 # counters have been taken, and is reset to None whenever that kernel changes.
 TRAFFIC_BYTES_PER_LAUNCH = {
-    ("feature_fp16_per_channel", "train"): 44465427,      # backward_kernel<f16>: 1.005 x the algorithmic bytes
-    ("feature_fp16_per_channel", "forward"): 29592846,    # forward_kernel<f16>: 1.003 x
-    ("feature_fp16_per_channel", "codes"): 22219201,      # forward_kernel<f16, codes only>: 1.005 x
-    ("train_batch_fp16", "train"): 221735108,             # 1.002 x
-    ("multi_tensor_mixed", "train"): 3367183741,          # backward_multi_kernel: 1.014 x
-    ("conv_weights_fp32", "train"): 18018034,             # 1.018 x
-    ("act_fp32_per_tensor", "train"): 1927883,            # 1.046 x (a 1.8 MB launch: theta and the partial sums count)
-    ("feature_fp16_per_channel", "distill"): 44413611,    # fused kernel, one launch: 1.004 x
-    ("train_batch_fp16", "distill"): 221562519,           # fused kernel + the block that adds the tile sums: 1.002 x
+    ("feature_fp16_per_channel", "train"): 44488433,      # backward_kernel<f16>: 1.006 x the algorithmic bytes
+    ("feature_fp16_per_channel", "forward"): 29562988,    # forward_kernel<f16>: 1.002 x
+    ("feature_fp16_per_channel", "codes"): 22207853,      # forward_kernel<f16, codes only>: 1.004 x
+    ("train_batch_fp16", "train"): 221751506,             # 1.002 x
+    ("multi_tensor_mixed", "train"): 3366924826,          # backward_multi_kernel: 1.014 x
+    ("conv_weights_fp32", "train"): 18022814,             # 1.018 x
+    ("act_fp32_per_tensor", "train"): 1914257,            # 1.046 x (a 1.8 MB launch: theta and the partial sums count)
+    ("feature_fp16_per_channel", "distill"): 44420788,    # fused kernel, one launch: 1.004 x
+    ("train_batch_fp16", "distill"): 221419461,           # fused kernel + the block that adds the tile sums: 1.001 x
 }
 
 WORKLOAD_TEXT = {
