@@ -73,13 +73,17 @@ static int is_workspace(PyObject *o)
                                      PyLong_CheckExact(PyTuple_GET_ITEM(o, 0)) && PyLong_CheckExact(PyTuple_GET_ITEM(o, 1)));
 }
 
+/* 0, -1 with an exception set, or 1: an integer that a pointer or a size_t does not hold.  ctypes takes those (it
+ * drops the upper bits), so they are left to the Python form. */
 static int workspace(PyObject *o, void **p, size_t *bytes)
 {
     if (PyTuple_CheckExact(o)) {
         *p = PyLong_AsVoidPtr(PyTuple_GET_ITEM(o, 0));
-        if (*p == NULL && PyErr_Occurred()) return -1;
-        *bytes = PyLong_AsSize_t(PyTuple_GET_ITEM(o, 1));
-        return *bytes == (size_t)-1 && PyErr_Occurred() ? -1 : 0;
+        if (*p != NULL || !PyErr_Occurred()) *bytes = PyLong_AsSize_t(PyTuple_GET_ITEM(o, 1));
+        if (!PyErr_Occurred()) return 0;
+        if (!PyErr_ExceptionMatches(PyExc_OverflowError)) return -1;
+        PyErr_Clear();
+        return 1;
     }
     size_t address, count, each;
     if (method_value(o, str_data_ptr, &address) || method_value(o, str_numel, &count) || method_value(o, str_element_size, &each))
@@ -118,7 +122,10 @@ static PyObject *call_backward(PyObject *self, PyObject *const *args, Py_ssize_t
     void *stream, *ws;
     size_t bytes;
     fq_status status;
-    if (!t || workspace(args[1], &ws, &bytes) || current_stream(&stream)) return NULL;
+    if (!t) return NULL;
+    const int left = workspace(args[1], &ws, &bytes);
+    if (left > 0) return to_python(BACKWARD, args, nargs, kwnames);
+    if (left || current_stream(&stream)) return NULL;
     Py_BEGIN_ALLOW_THREADS
     status = fq_backward(t, ws, bytes, stream);
     Py_END_ALLOW_THREADS
@@ -134,7 +141,10 @@ static PyObject *call_distill(PyObject *self, PyObject *const *args, Py_ssize_t 
     void *stream, *ws;
     size_t bytes;
     fq_status status;
-    if (!d || workspace(args[1], &ws, &bytes) || current_stream(&stream)) return NULL;
+    if (!d) return NULL;
+    const int left = workspace(args[1], &ws, &bytes);
+    if (left > 0) return to_python(DISTILL, args, nargs, kwnames);
+    if (left || current_stream(&stream)) return NULL;
     Py_BEGIN_ALLOW_THREADS
     status = fq_distill_loss(d, ws, bytes, stream);
     Py_END_ALLOW_THREADS
