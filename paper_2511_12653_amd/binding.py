@@ -34,7 +34,10 @@ def _load():
 
 
 _lib = _load()
-from . import _fqcall  # noqa: E402  (native forms of the calls below; it links the library that is loaded above)
+try:
+    from . import _fqcall  # native forms of the calls below; it links the library that is loaded above
+except ImportError:        # not built, or for another interpreter: the Python forms take every call
+    _fqcall = None
 
 
 class FqAdam(ctypes.Structure):
@@ -229,7 +232,7 @@ def _current_stream():
     import torch
     torch.cuda.current_stream()
     _current_stream = _stream_lookup()
-    if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+    if _fqcall and hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
         _fqcall.streams(torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice, torch.Tensor)
     return _current_stream()
 
@@ -255,15 +258,21 @@ def _check(status):
 
 # The calls that a program makes per layer and step have a native form, which takes the usual arguments and
 # leaves all others to the Python one below it.  us of host time per call, Python / native:
-# fq_forward 4.2 / 2.9, fq_backward 4.5 / 3.0, fq_workspace_bytes 0.52 / 0.09 (with the library's single-tensor path, which makes no lists).
-_fqcall.setup(FqTensor, FqDistill, ctypes.c_void_p, _check)
+# fq_forward 4.2 / 2.9, fq_backward 4.5 / 3.0 (with the library's single-tensor path, which makes no lists),
+# fq_workspace_bytes 0.52 / 0.09.
+def _native(function):
+    return _fqcall.wrap(function) if _fqcall else function
+
+
+if _fqcall:
+    _fqcall.setup(FqTensor, FqDistill, ctypes.c_void_p, _check)
 
 
 def fq_status_string(status) -> str:
     return _lib.fq_status_string(int(status)).decode()
 
 
-@_fqcall.wrap
+@_native
 def fq_workspace_bytes(tensors, mode) -> int:
     arr, n = _array(tensors)
     return int(_lib.fq_workspace_bytes(arr, n, mode))
@@ -280,12 +289,12 @@ def fq_workspace_init(workspace, stream=None):
     _check(_lib.fq_workspace_init(p, nbytes, _stream(stream)))
 
 
-@_fqcall.wrap
+@_native
 def fq_forward(t: FqTensor, stream=None):
     _check(_lib.fq_forward(ctypes.byref(t), _stream(stream)))
 
 
-@_fqcall.wrap
+@_native
 def fq_backward(t: FqTensor, workspace, stream=None):
     p, nbytes = _ws(workspace)
     _check(_lib.fq_backward(ctypes.byref(t), p, nbytes, _stream(stream)))
@@ -310,12 +319,12 @@ def fq_plan_create(tensors, mode, workspace, stream=None):
     return plan
 
 
-@_fqcall.wrap
+@_native
 def fq_plan_run(plan, stream=None):
     _check(_lib.fq_plan_run(plan, _stream(stream)))
 
 
-@_fqcall.wrap
+@_native
 def fq_plan_run_adam(plan, step, stream=None):
     _check(_lib.fq_plan_run_adam(plan, int(step), _stream(stream)))
 
@@ -332,7 +341,7 @@ def fq_distill_reads_of_pair(d: FqDistill) -> int:
     return int(_lib.fq_distill_reads_of_pair(ctypes.byref(d)))
 
 
-@_fqcall.wrap
+@_native
 def fq_distill_loss(d: FqDistill, workspace, stream=None):
     p, nbytes = _ws(workspace)
     _check(_lib.fq_distill_loss(ctypes.byref(d), p, nbytes, _stream(stream)))
