@@ -561,6 +561,9 @@ __device__ __forceinline__ unsigned tile_of_block(unsigned block, unsigned tiles
 
 // The leading arguments, which are what the first loads' addresses are made of, come in registers with the launch (see
 // forward_kernel in the other file).  neighbours: 0, or the number of tiles (see tile_of_block).
+// (Known loss: FP16 pairs of 257 to 384 channels with a gradient, in at most 256 tiles the last of which has 4 or 8 positions, take
+// longer with the same instructions when their loads start earlier: 6x300x132 8.7 / 9.3 us, 12x365x68 10.2 / 10.9; with 12 positions
+// 7.9 / 7.8.  Leaving out the loads of absent positions, spreading them, or storing such tiles by plain stores changes nothing or little.)
 template <typename T, int SHAPE, int KCH, bool QUADS, bool WANT_GRAD>
 __global__ __launch_bounds__(kTileThreads[SHAPE], 4)
 void distill_fused_kernel(const void *student, const void *teacher, long long M, unsigned C, unsigned tiles_per_n,
@@ -808,12 +811,21 @@ bool on_quads(const fq_distill *d)
 // (200x16x400 FP16 9.4 / 7.9, 200x32x200 FP32 10.3 / 8.5).  FP32 off the grid with 65 to 128 channels, whose wide
 // tiles go two to a compute unit, stays with those (12x100x4819 20.6 / 22.7), and so do few tiles of the most channels
 // (450, 3x256x9600 19.9 / 20.2).
-bool long_pays(const fq_distill *d, bool quads, long long narrow_tpn, long long wide_tpn)
+//
+// Nor, for FP16 with 193 to 256 channels (or 129 to 192), where rows are whole cache lines and the tiles are more than two to a
+// compute unit: against the narrow ones a median of 1.03 (1.06) without a gradient and 0.99 with one over two thousand pairs, worst
+// 1.12 (1.17).  Nor without a gradient where images have an odd number of positions, or twice an odd one, and the tiles are few, with 97
+// to 128 and 193 to 256 channels (long against narrow, median and worst, tiles of the launch: up to 512 1.035 and 1.12, up to
+// 1024 0.99 and 1.12, up to 1536 1.00 and 1.12, beyond 0.95 and 1.03; 4x180x15730, 492, 16.0 / 17.0).  These two look at nothing but the
+// extents and the type, so that a workspace serves the pair at any alignment.
+bool long_pays(const fq_distill *d, bool quads, long long narrow_tpn, long long wide_tpn, bool grad)
 {
     const int kch = fused_channels_per_lane(d, kLong);
     if (!kch || (2 * wide_tpn - narrow_tpn) * (kch <= 2 ? 4 : 16) > narrow_tpn) return false;
     const long long tiles = wide_tpn * d->n, rounds = (tiles + kComputeUnits - 1) / kComputeUnits;
     if (d->dtype == FQ_F32) return (quads || kch != 4) && (kch < 8 || tiles >= 2 * kComputeUnits);
+    if (kch >= 12 && d->inner % 64 == 0 && tiles > 2 * kComputeUnits) return false;
+    if (!grad && (kch == 8 || kch == 16) && d->inner % kFusedVec != 0 && tiles < 6 * kComputeUnits) return false;
     return 8 * tiles >= 7 * rounds * kComputeUnits || tiles >= (kch <= 4 ? 2 : kch <= 8 ? 4 : 7) * kComputeUnits;
 }
 
@@ -826,6 +838,25 @@ bool small_pays(const fq_distill *d, bool quads, long long tiles)
 {
     const int kch = fused_channels_per_lane(d, kSmall);
     return kch && (kch <= 2 || (quads && tiles >= 2 * kComputeUnits));
+}
+
+// Where rows of 256 bytes pay, but by 1024 threads: with half the channels per lane.  long against wide, time over that of the
+// tiles that the other rule below would take, median and worst of a few hundred pairs each:
+//   without a gradient  FP32 with 193 to 256 channels, any alignment 1.00 to 1.03 and 1.11 / 0.98 to 0.995 and 1.03 (15x249x11944
+//     71.0 / 67.0 us); FP16 with 129 to 192 0.95 to 1.05 and 1.14 / 0.92 to 0.96 and 1.05, with 193 to 256 on the grid
+//     0.93 to 1.00 and 1.05 / 0.90 to 0.97 and 1.00 (off it 0.95 and 1.1 / 1.08 and 1.19)
+//   with one  FP32 on the grid with 65 to 128 or 193 to 256 channels, rows no whole number of 64-byte halves of a line and launches of
+//     many tiles 1.02 and 1.09 / 0.99 and 1.01 (smaller ones 0.97 / 0.99); off the grid with 193 to 256, in the largest 0.99 and 1.08 / 0.99
+//     and 1.00 (smaller ones 0.93 / 0.99).  14x234x17044 203 / 190 us, 8x81x38440 81 / 77.6, 13x254x19507 229 / 216
+constexpr long long kManyElements = 6400000, kMostElements = 33000000;
+bool by_1024_threads(const fq_distill *d, bool quads, bool grad)
+{
+    const int kch = fused_channels_per_lane(d, kLong);
+    if (d->dtype == FQ_F16) return !grad && (kch == 12 || (kch == 16 && quads));
+    if (!grad) return kch == 8;
+    const long long elements = d->n * d->channels * d->inner;
+    if (quads) return (kch == 4 || kch == 8) && d->inner % 16 != 0 && elements > kManyElements;
+    return kch == 8 && elements > kMostElements;
 }
 
 // Where they don't: wide tiles, 1024 threads, for FP32 (us, narrow / wide: 3x384x19200 61 / 55, 12x100x4819 25.8 /
@@ -887,10 +918,12 @@ fq_status make_plan(const fq_distill *d, Plan &pl)
         const long long narrow = tile_positions(d, kNarrow);
         const long long narrow_tpn = (d->inner + narrow - 1) / narrow, wide_tpn = (d->inner + 2 * narrow - 1) / (2 * narrow);
         const long long wide_tiles = wide_tpn * d->n;
+        const bool grad = d->gstudent != nullptr;
         pl.shape = kNarrow;
         if (narrow_tpn * d->n > (long long)kGatherTiles) {
             if (wide_tiles <= (long long)kGatherTiles) pl.shape = kWide;     // one launch (1x384x19200 FP16: 15.9 -> 12.6 us)
-            else if (long_pays(d, pl.quads, narrow_tpn, wide_tpn)) pl.shape = small_pays(d, pl.quads, wide_tiles) ? kSmall : kLong;
+            else if (long_pays(d, pl.quads, narrow_tpn, wide_tpn, grad))
+                pl.shape = small_pays(d, pl.quads, wide_tiles) ? kSmall : by_1024_threads(d, pl.quads, grad) ? kWide : kLong;
             else if (wide_pays(d, pl.quads, narrow_tpn, wide_tpn, pl.fused_kch)) pl.shape = kWide;
         }
         if (pl.shape != kNarrow) pl.fused_kch = fused_channels_per_lane(d, pl.shape);
@@ -903,8 +936,11 @@ fq_status make_plan(const fq_distill *d, Plan &pl)
         pl.groups = pl.per_group = pl.grad_groups = pl.grad_per_group = 0;
         pl.stats_lds = 0;
         pl.off_blocksum = 0;                       // no per-position coefficients leave the block
+        // A workspace serves the pair with its gradient and without: where one of the two has narrow tiles, room for those.
+        const long long most = d->dtype == FQ_F16 && !pl.one_launch && !long_pays(d, pl.quads, narrow_tpn, wide_tpn, !grad)
+                                   ? narrow_tpn * d->n : (long long)pl.tiles;
         pl.bytes = pl.one_launch ? align256(((size_t)pl.tiles * 4 + 1) * sizeof(unsigned long long))
-                           : align256((size_t)pl.tiles * 2 * sizeof(double));
+                           : align256((size_t)most * 2 * sizeof(double));
         if (pl.bytes < 256) pl.bytes = 256;
         return FQ_OK;
     }
