@@ -129,7 +129,8 @@ fq_status fq_validate(const fq_tensor *ts, int n, int mode);
  * A unit is what one partial sum of the backward covers: a block's chunk, or, for tensors whose
  * slabs are short, a whole slab handled by one wavefront (only in launches with many blocks; this
  * call describes the backward of the tensor launched on its own: lists, and the forward, which has no
- * partial sums, go over to wavefronts with fewer blocks).
+ * partial sums, go over to wavefronts with fewer blocks; the last bits of such a tensor's gs and gtheta may
+ * therefore differ between a list and a launch of its own).
  */
 typedef struct fq_layout_info {
     int64_t blocks;              /* grid blocks of the backward kernel */

@@ -146,6 +146,8 @@ fq_status plan_tensor(const fq_tensor &t, Plan &p, bool allow_waves)
 //     4.20; 22 convolutions' weights (1472) 4.35 / 3.55, 5.57 / 5.05, twice as wide (2944) 7.57 / 4.57, 9.6 / 5.9;
 //     16 of 32x288 FP32 (512) 2.73 / 2.83, 3.69 / 3.6; 6 of 40x2400 FP16 (240) 3.26 / 3.40, 4.81 / 4.50.  A few short slabs beside
 //     larger ones end late as wavefronts (384x3456 and 128x1152 FP32, 768 + 128 blocks, backward 6.1 / 6.8)
+// (How a slab is cut decides how its products are added: the last bits of a short-slab tensor's gradients of the scale depend on the
+// list that it is launched in, and on whether it is launched alone.)
 bool waves_pay(const Plan &p, int n, int mode, long long blocks, long long short_blocks)
 {
     if (!p.short_slabs || p.numel == 0) return false;
@@ -241,8 +243,8 @@ fq_status make_layout(const fq_tensor *ts, int n, int mode, Layout &L)
         if (L.plans[(size_t)i].numel == 0 && ts[i].channels > 0) L.any_empty_with_channels = true;
         if (L.blocks > kMaxBlocks || L.channels > kMaxBlocks || L.slots > 64 * kMaxBlocks) return FQ_ERR_SHAPE;
     }
-    // short-slab tensors switch to one wavefront per slab (fewer blocks, partial sums and slots; the limits
-    // above still hold)
+    // short-slab tensors switch to one wavefront per slab (fewer blocks and partial sums, at most two slots more per channel,
+    // where three or four units take the place of more; the limits above hold with room for those)
     const long long blocks = L.blocks;
     long long short_blocks = 0;
     for (const Plan &p : L.plans)

@@ -1550,12 +1550,19 @@ static void launch_forward_full(const DevTensor &d, unsigned blocks, hipStream_t
 //         880 x 1200 7.90 / 8.12   960 7.62 / 8.40   1024 7.65 / 8.35   1280 9.75 / 10.87   1536 11.8 / 12.3
 //         1800 x 1200 14.12 / 13.83   2560 18.5 / 18.2   3840 25.9 / 25.2   2000 x 600 9.07 / 8.35
 //         3000 x 512 10.58 / 9.80   3000 x 375 8.58 / 8.68   4000 x 313 9.71 / 10.54 (three of eight wavefronts idle)
-//   FP32  512 x 576 3.30 / 3.28   512 x 1200 5.03 / 4.95   804 x 824 6.12 / 5.81   1024 x 1200 7.7 / 8.6
+//         200 x 300 2.94 / 2.77   200 x 400 2.70 / 2.53   300 x 263 3.12 / 3.06   300 x 450 3.29 / 3.18   384 x 257 3.19 / 3.14
+//         384 x 375 3.27 / 3.21   512 x 263 3.23 / 3.23   512 x 320 2.94 / 2.94   512 x 450 3.50 / 3.40   (no shape of 128 to 512
+//         blocks of 257 to 512 vectors is slower in either type, three of eight wavefronts idle or not)
+//   FP32  200 x 263 2.82 / 2.66   300 x 300 2.70 / 2.61   384 x 450 3.18 / 3.07   512 x 257 3.10 / 3.07;  200 x 600 2.66 / 2.71
+//         512 x 576 3.30 / 3.28   512 x 1200 5.03 / 4.95   804 x 824 6.12 / 5.81   1024 x 1200 7.7 / 8.6
 //         1800 x 1200 13.6 / 13.4   3000 x 640 12.35 / 11.95;   768 x 432 3.42 / 3.73 (one row each instead of two)
 //   codes alone, FP16  128 x 603 3.22 / 3.08   240 x 1280 3.68 / 3.43   400 x 1200 4.53 / 4.21   768 x 1200 5.90 / 6.14
 //         2000 x 600 7.58 / 8.21   3840 x 1200 20.2 / 20.9
 // With more than kEarlyBlocks blocks theta goes in front of the rows there too (768 x 1200 FP16 6.68 / 6.73 without it and
-// 6.44 with it, FP32 6.39 / 6.75 / 6.05; but 540 x 1200 5.63 without and 5.96 with it).
+// 6.44 with it, FP32 6.39 / 6.75 / 6.05; but 540 x 1200 5.63 without and 5.96 with it).  kEarlyBlocks stands where FP16 stops losing,
+// us, without / with: 576 x 1200 5.97 / 6.14   600 x 1200 6.08 / 6.17   620 x 1200 6.20 / 6.22   640 x 1200 6.38 / 6.33   660 x 1200 6.42 /
+// 6.41   680 x 1200 6.57 / 6.39   704 x 1200 6.70 / 6.38 (1100 vectors: from 600 on 1 to 5 % with it); FP32 gains from about 560 on
+// (540 x 1200 5.63 / 5.80, 600 6.22 / 5.93, 660 6.55 / 6.03).
 constexpr int kWideBlock = 2 * kBlock, kWideRows = (kChunkVecs + kWideBlock - 1) / kWideBlock;
 constexpr unsigned kEarlyBlocks = 640, kWideFewBlocks = 512, kWideManyBlocks = 1800;
 static bool wide_pays(unsigned blocks, unsigned vecs, bool codes)

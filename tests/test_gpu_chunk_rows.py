@@ -1,6 +1,6 @@
 """Single-tensor launches on both sides of the lines that choose a kernel: the number of vectors a lane
-has in a whole chunk (one to five, a kernel for each), and the backward's burst schedule (at most 768
-blocks, from 640 blocks of 900 vectors on for FP16 and 400 blocks of 600 for FP32).  Slabs are a whole
+has in a whole chunk (one to five, a kernel for each), and the backward's burst schedule (769 to 1024 blocks
+of 900 vectors or more for FP16, 400 to 768 of 600 or more for FP32).  Slabs are a whole
 number of vectors, or start off the 16-byte grid so that elements before and behind the vectors are left;
 one slab has a NaN in such an element.  Against the oracle, bars as everywhere; the burst and the
 interleaved schedule are also compared with the two-launch mode bit for bit."""
@@ -19,10 +19,10 @@ N = {np.float16: 8, np.float32: 4}
 
 
 @pytest.mark.parametrize("dtype, channels, vecs", [
-    (np.float16, 640, 900), (np.float16, 639, 900), (np.float16, 640, 899), (np.float16, 768, 1280),
+    (np.float16, 769, 900), (np.float16, 768, 900), (np.float16, 769, 899), (np.float16, 768, 1280),
     (np.float16, 769, 1280), (np.float16, 70, 1025), (np.float16, 70, 1024), (np.float16, 70, 768),
     (np.float16, 70, 512), (np.float16, 70, 257), (np.float16, 70, 1),
-    (np.float32, 400, 600), (np.float32, 399, 600), (np.float32, 400, 599), (np.float32, 500, 769),
+    (np.float32, 400, 600), (np.float32, 399, 600), (np.float32, 400, 599), (np.float32, 768, 600), (np.float32, 769, 600), (np.float32, 500, 769),
     (np.float32, 768, 1025), (np.float32, 70, 1025), (np.float32, 70, 769), (np.float32, 70, 512), (np.float32, 70, 256),
 ])
 @pytest.mark.parametrize("odd", [0, 1, -1])

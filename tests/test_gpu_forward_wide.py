@@ -1,6 +1,6 @@
 """The forward's block widths: 256 or 512 threads share a chunk, by the number of blocks and the vectors of a chunk.
 
-Both sides of each line of the rule, whole vectors and slabs off the 16-byte grid, y, y with codes and codes alone,
+Both sides of each line of the rule (blocks and vectors of a chunk are as listed, one vector more with `odd` elements more), whole vectors and slabs off the 16-byte grid, y, y with codes and codes alone,
 in place, and one linear grid (more channels than a grid's y extent holds).  Against the oracle: y to 1 ulp, codes and
 scales exactly."""
 import numpy as np
@@ -18,9 +18,9 @@ N = {np.float16: 8, np.float32: 4}
 
 
 @pytest.mark.parametrize("dtype, blocks, vecs", [
-    (np.float16, 3, 257), (np.float32, 512, 256), (np.float16, 512, 257), (np.float32, 512, 512), (np.float16, 512, 513),
-    (np.float32, 512, 1024), (np.float16, 512, 1025), (np.float16, 513, 1024), (np.float32, 513, 1025), (np.float32, 640, 1280),
-    (np.float16, 641, 1280), (np.float32, 768, 1280), (np.float16, 769, 1280), (np.float16, 1799, 600), (np.float16, 1800, 448),
+    (np.float16, 225, 512), (np.float32, 512, 256), (np.float16, 512, 257), (np.float32, 512, 512), (np.float16, 512, 513),
+    (np.float32, 512, 1024), (np.float16, 512, 1025), (np.float16, 513, 1024), (np.float32, 513, 1025), (np.float32, 640, 1279),
+    (np.float16, 641, 1279), (np.float32, 768, 1279), (np.float16, 769, 1279), (np.float16, 1799, 600), (np.float16, 1800, 448),
     (np.float32, 1800, 449), (np.float16, 1800, 513), (np.float32, 1801, 1025), (np.float16, 66000, 321),
 ])
 @pytest.mark.parametrize("odd", [0, 3, -1])
@@ -41,8 +41,8 @@ def test_widths(dtype, blocks, vecs, odd):
             continue
         H.say("forward width: %dx%d %s %s" % (blocks, inner, np.dtype(dtype).name, what))
         dc = H.DeviceCase(case, want_q="codes" in what, inplace=what == "inplace")
-        if odd == 0 and 512 <= blocks <= 513:
-            assert fq.fq_layout(dc.desc).blocks == blocks
+        cut = fq.fq_layout(dc.desc)
+        assert (cut.blocks, -(-cut.unit_elems // N[dtype]), cut.wave_units) == (blocks, vecs + (odd > 0), 0)
         if what == "codes":
             dc.desc.y = None
         fq.fq_forward(dc.desc)

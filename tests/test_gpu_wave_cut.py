@@ -1,7 +1,8 @@
 """Slabs that go one to a wavefront: in lists from 768 blocks of short slabs on, and in the forward of one tensor from 1024 blocks of at
 most 192 vectors on.  Both sides of the lines, slabs off the 16-byte grid, a number of slabs that is no multiple of four
-and members of a list that stay with blocks.  Against the oracle (bars as everywhere); lists also against the same
-tensors launched alone, whose sums are cut and added the same."""
+and members of a list that stay with blocks.  Against the oracle (bars as everywhere); lists also against the two-launch
+mode of the same list, which adds the same sums in the same order, bit for bit.  At the line of the lists the cut shows in the
+workspace; how a forward is cut shows nowhere, so there the results on both sides are all that is seen."""
 import numpy as np
 import pytest
 import torch
@@ -35,19 +36,29 @@ def test_forward_alone(dtype, outer, channels, inner, what):
     H.check_forward(dc, None, "wave cut")
 
 
-@pytest.mark.parametrize("shapes", [
-    [(np.float32, 1, 383, 49), (np.float16, 1, 384, 800)],                                   # 767 blocks
-    [(np.float32, 1, 384, 49), (np.float16, 1, 384, 800)],                                   # 768
-    [(np.float16, 4, 65, 1200), (np.float32, 1, 333, 147), (np.float16, 1, 3, 40000), (np.float32, 300, 1, 7)],
-    [(np.float32, 1, 384, 3456), (np.float32, 1, 128, 1152)],                                # few short ones: blocks
-    [(np.float32, 1, 700, 319 * 4), (np.float32, 1, 70, 320 * 4), (np.float16, 70, 2, 9)],   # the longest slab, one more
+def _rounded(values):
+    return -(-8 * values // 256) * 256
+
+
+# units, channels: sums and slots of the list, where the cut shows in them.  Slabs of 2056 FP16 elements are two chunks each for blocks.
+@pytest.mark.parametrize("shapes, units, channels", [
+    ([(np.float16, 1, 64, 2056)] * 5 + [(np.float32, 1, 127, 49)], 5 * 128 + 127, 447),      # 767 blocks: two chunks per slab
+    ([(np.float16, 1, 64, 2056)] * 6, 6 * 64, 384),                                          # 768: a wavefront per slab
+    ([(np.float32, 1, 383, 49), (np.float16, 1, 384, 800)], 767, 767),
+    ([(np.float32, 1, 384, 49), (np.float16, 1, 384, 800)], 768, 768),
+    ([(np.float16, 4, 65, 1200), (np.float32, 1, 333, 147), (np.float16, 1, 3, 40000), (np.float32, 300, 1, 7)], 0, 0),
+    ([(np.float32, 1, 384, 3456), (np.float32, 1, 128, 1152)], 768 + 256, 512),              # few short ones: blocks
+    ([(np.float32, 1, 700, 319 * 4), (np.float32, 1, 70, 320 * 4), (np.float16, 70, 2, 9)], 0, 0),   # the longest slab, one more
 ])
-def test_lists(shapes):
+def test_lists(shapes, units, channels):
     rng = np.random.Generator(np.random.Philox(len(shapes) * 31 + shapes[0][2]))
     cases = [_case(rng, o, c, k, d) for d, o, c, k in shapes]
     H.say("wave cut list: %s" % ([s[1:] for s in shapes],))
     dcs = [H.DeviceCase(c, want_q=False) for c in cases]
     descs = [d.desc for d in dcs]
+    if units:
+        beside_the_table = fq.fq_workspace_bytes(descs, fq.FQ_MODE_BACKWARD) - fq.fq_workspace_bytes(descs, fq.FQ_MODE_FORWARD)
+        assert beside_the_table == _rounded(units) + _rounded(channels)
     ws = H.workspace_for(descs, fq.FQ_MODE_BACKWARD)
     for rep in range(2):
         fq.fq_multi_tensor(descs, fq.FQ_MODE_FORWARD, H.workspace_for(descs, fq.FQ_MODE_FORWARD))
