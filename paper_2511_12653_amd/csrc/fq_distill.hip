@@ -825,7 +825,10 @@ bool on_quads(const fq_distill *d)
 // compute unit: against the narrow ones a median of 1.03 (1.06) without a gradient and 0.99 with one over two thousand pairs, worst
 // 1.12 (1.17).  Nor without a gradient where images have an odd number of positions, or twice an odd one, and the tiles are few, with 97
 // to 128 and 193 to 256 channels (long against narrow, median and worst, tiles of the launch: up to 512 1.035 and 1.12, up to
-// 1024 0.99 and 1.12, up to 1536 1.00 and 1.12, beyond 0.95 and 1.03; 4x180x15730, 492, 16.0 / 17.0).  These two look at nothing but the
+// 1024 0.99 and 1.12, up to 1536 1.00 and 1.12, beyond 0.95 and 1.03; 4x180x15730, 492, 16.0 / 17.0).  Nor with a gradient in such
+// images where the tiles are fewer than two to a compute unit: median and worst with 97 to 128 channels 1.025 and 1.18
+// (23x115x2435, 460, 18.6 / 21.5), 129 to 160 1.02 to 1.04 and 1.18, with more channels in images of up to 56 tiles 1.01 to 1.08 and 1.19; longer images of
+// more than 160 channels gain, 0.97 (6x243x9999, 474, 35.4 / 38.4, is one that loses).  These look at nothing but the
 // extents and the type, so that a workspace serves the pair at any alignment.
 bool long_pays(const fq_distill *d, bool quads, long long narrow_tpn, long long wide_tpn, bool grad)
 {
@@ -835,6 +838,8 @@ bool long_pays(const fq_distill *d, bool quads, long long narrow_tpn, long long 
     if (d->dtype == FQ_F32) return (quads || kch != 4) && (kch < 8 || tiles >= 2 * kComputeUnits);
     if (kch >= 12 && d->inner % 64 == 0 && tiles > 2 * kComputeUnits) return false;
     if (!grad && (kch == 8 || kch == 16) && d->inner % kFusedVec != 0 && tiles < 6 * kComputeUnits) return false;
+    if (grad && d->inner % kFusedVec != 0 && tiles < 2 * kComputeUnits &&
+        (kch == 8 || (kch > 8 && (d->channels <= 160 || wide_tpn <= 56)))) return false;
     return 8 * tiles >= 7 * rounds * kComputeUnits || tiles >= (kch <= 4 ? 2 : kch <= 8 ? 4 : 7) * kComputeUnits;
 }
 

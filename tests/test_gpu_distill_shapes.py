@@ -20,6 +20,10 @@ pytestmark = pytest.mark.gpu
     (np.float16, (512, 97, 127), 2), (np.float16, (1535, 128, 125), 2), (np.float16, (1536, 97, 126), 1),
     (np.float16, (512, 193, 127), 2), (np.float16, (1536, 193, 125), 1),
     (np.float32, (512, 193, 64), 1), (np.float32, (512, 256, 60), 1), (np.float32, (512, 256, 63), 1), (np.float32, (512, 192, 64), 1),
+    # the same with a gradient and fewer than two tiles to a compute unit: 129 to 160 channels, and more in images of up to 56 tiles
+    # (or 57); on the grid; two to each
+    (np.float16, (4, 150, 14527), 227), (np.float16, (9, 161, 7167), 112), (np.float16, (8, 161, 7169), 57),
+    (np.float16, (9, 161, 7164), 56), (np.float16, (512, 150, 125), 1),
     # 6.4 million elements
     (np.float32, (16, 100, 3996), 63), (np.float32, (16, 100, 4004), 63), (np.float32, (16, 200, 2004), 32),
 ])
