@@ -861,8 +861,11 @@ bool small_pays(const fq_distill *d, bool quads, long long tiles)
 //     0.93 to 1.00 and 1.05 / 0.90 to 0.97 and 1.00 (off it 0.95 and 1.1 / 1.08 and 1.19)
 //   with one  FP32 on the grid with 65 to 128 or 193 to 256 channels, rows no whole number of 64-byte halves of a line and launches of
 //     many tiles 1.02 and 1.09 / 0.99 and 1.01 (smaller ones 0.97 / 0.99); off the grid with 193 to 256, in the largest 0.99 and 1.08 / 0.99
-//     and 1.00 (smaller ones 0.93 / 0.99).  14x234x17044 203 / 190 us, 8x81x38440 81 / 77.6, 13x254x19507 229 / 216
-constexpr long long kManyElements = 6400000, kMostElements = 33000000;
+//     and 1.00 (smaller ones 0.93 / 0.99).  14x234x17044 203 / 190 us, 8x81x38440 81 / 77.6, 13x254x19507 229 / 216.  Off the grid with 57
+//     to 64, which fill the 64 rows of 1024 threads, and many elements, in millions, median and worst: 14 to 16 1.00 and 1.03 / 0.984 and
+//     0.99, 20 to 22 1.02 and 1.06, 28 to 30 1.04 and 1.07 / the same 0.984 and 0.99 (10x60x39795 83.9 / 78.6); fewer channels gain up to 26 million
+//     and are level beyond
+constexpr long long kManyElements = 6400000, kMostElements = 33000000, kFewChannelsElements = 14000000;
 bool by_1024_threads(const fq_distill *d, bool quads, bool grad)
 {
     const int kch = fused_channels_per_lane(d, kLong);
@@ -870,7 +873,7 @@ bool by_1024_threads(const fq_distill *d, bool quads, bool grad)
     if (!grad) return kch == 8;
     const long long elements = d->n * d->channels * d->inner;
     if (quads) return (kch == 4 || kch == 8) && d->inner % 16 != 0 && elements > kManyElements;
-    return kch == 8 && elements > kMostElements;
+    return (kch == 8 && elements > kMostElements) || (kch == 2 && d->channels > 56 && elements > kFewChannelsElements);
 }
 
 // Where they don't: wide tiles, 1024 threads, for FP32 (us, narrow / wide: 3x384x19200 61 / 55, 12x100x4819 25.8 /

@@ -24,6 +24,9 @@ pytestmark = pytest.mark.gpu
     # (or 57); on the grid; two to each
     (np.float16, (4, 150, 14527), 227), (np.float16, (9, 161, 7167), 112), (np.float16, (8, 161, 7169), 57),
     (np.float16, (9, 161, 7164), 56), (np.float16, (512, 150, 125), 1),
+    # 14 million elements with 57 to 64 channels, and with 56
+    (np.float32, (3, 64, 72911), 1140), (np.float32, (3, 64, 72929), 1140), (np.float32, (3, 57, 81931), 1281),
+    (np.float32, (3, 56, 83999), 1313),
     # 6.4 million elements
     (np.float32, (16, 100, 3996), 63), (np.float32, (16, 100, 4004), 63), (np.float32, (16, 200, 2004), 32),
 ])
