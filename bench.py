@@ -49,10 +49,10 @@ TRAFFIC_BYTES_PER_LAUNCH = {
     ("feature_fp16_per_channel", "train"): 44488433,      # backward_kernel<f16>: 1.006 x the algorithmic bytes
     ("feature_fp16_per_channel", "forward"): 29562988,    # forward_kernel<f16>: 1.002 x
     ("feature_fp16_per_channel", "codes"): 22207853,      # forward_kernel<f16, codes only>: 1.004 x
-    ("train_batch_fp16", "train"): 221751506,             # 1.002 x
+    ("train_batch_fp16", "train"): 221751506,             # 1.003 x
     ("multi_tensor_mixed", "train"): 3366924826,          # backward_multi_kernel: 1.014 x
-    ("conv_weights_fp32", "train"): 18022814,             # 1.018 x
-    ("act_fp32_per_tensor", "train"): 1914257,            # 1.046 x (a 1.8 MB launch: theta and the partial sums count)
+    ("conv_weights_fp32", "train"): 18022814,             # 1.019 x
+    ("act_fp32_per_tensor", "train"): 1914257,            # 1.039 x (a 1.8 MB launch: theta and the partial sums count)
     ("feature_fp16_per_channel", "distill"): 44420788,    # fused kernel, one launch: 1.004 x
     ("train_batch_fp16", "distill"): 221419461,           # fused kernel + the block that adds the tile sums: 1.001 x
 }

@@ -528,7 +528,7 @@ __device__ __forceinline__ void finish_if_complete(const DistillArgs &k, unsigne
 // A look costs about 0.5 us, and one that comes too early costs that for nothing.  Without a gradient the block that looks is done
 // as soon as the others are, so with more than 64 tiles its first look waits 0.3 us for their records.  Since the first loads no longer
 // wait for the kernel's arguments, the look without the wait came too early for some shapes.  us, loads behind the arguments / loads
-// early / and the wait, without a gradient: 13x45x704 FP16 (143 tiles) 5.00 / 5.56 / 4.7; over 2800 pairs of 65 to 256 tiles,
+// early / and the wait, without a gradient: 13x45x704 FP16 (143 tiles) 5.0 / 5.5 / 4.8; over 2800 pairs of 65 to 256 tiles,
 // against the first, 0.09 less early on average, one shape in twenty 1.05 of the time and the worst 1.10; with the wait 0.33 less, one in
 // twenty above 1.008, worst 1.05.  (A wait of 0.05 or 0.1 us leaves half of that, 0.24 gains 0.06 less.)  Up to 64 tiles nothing was lost.
 // With a gradient, which takes the block longer, a wait of 0.1 us and more only adds to the time of most shapes; there one shape in twenty of
@@ -827,7 +827,7 @@ bool on_quads(const fq_distill *d)
 // to 128 and 193 to 256 channels (long against narrow, median and worst, tiles of the launch: up to 512 1.035 and 1.12, up to
 // 1024 0.99 and 1.12, up to 1536 1.00 and 1.12, beyond 0.95 and 1.03; 4x180x15730, 492, 16.0 / 17.0).  Nor with a gradient in such
 // images where the tiles are fewer than two to a compute unit: median and worst with 97 to 128 channels 1.025 and 1.18
-// (23x115x2435, 460, 18.6 / 21.5), 129 to 160 1.02 to 1.04 and 1.18, with more channels in images of up to 56 tiles 1.01 to 1.08 and 1.19; longer images of
+// (23x115x2435, 460, 18.7 / 21.4), 129 to 160 1.02 to 1.04 and 1.18, with more channels in images of up to 56 tiles 1.01 to 1.08 and 1.19; longer images of
 // more than 160 channels gain, 0.97 (6x243x9999, 474, 35.4 / 38.4, is one that loses).  These look at nothing but the
 // extents and the type, so that a workspace serves the pair at any alignment.
 bool long_pays(const fq_distill *d, bool quads, long long narrow_tpn, long long wide_tpn, bool grad)

@@ -1273,7 +1273,8 @@ forward_kernel(const void *x, void *y, const float *theta, long long inner, unsi
 // The code of the multi-tensor kernels is kept short: blocks of one launch run through different parts of
 // it, and two compute units share 64 KB of instruction cache.  So the number of rows is rounded up to 1, 2 or
 // kMaxRows, and the backward is told at run time which lanes share a chunk (a block's or a wavefront's) and
-// whether gx is written (72 KB -> 45 KB).  The forward, which is shorter, loses by the former (us, told at run
+// whether gx is written (72 KB -> 45 KB at the time; now 61 KB, 31 KB of it without the combination of the units' sums, whose
+// ways for different numbers of units stand apart).  The forward, which is shorter, loses by the former (us, told at run
 // time / compiled in: lists of 16 mixed tensors and 20 M elements 28.2 / 27.7, 40 and 60 M 66.2 / 65.0, 4x(128x9600)
 // FP16 5.72 / 5.64).
 template <typename F> __device__ __forceinline__ void for_rows(int rows, F f)
